@@ -324,6 +324,129 @@ __device__ __forceinline__ void top2(const uint32_t *hkey, const double *hval, i
     }
 }
 
+// Steps 4 of a block of nbk <= NB new rows (positions mo .. mo + nbk - 1, their entries at the
+// old and new positions in NR, a_{u,i} in r_ai): the rows of W, l_i's new entries (r_li), psi and
+// yi = W^T l_i of this step so far.  go: this group takes part; mwb: the most old positions of a
+// group of the wavefront; first: the step's first block (l_i's old entries are added to yi then).
+template <int GS, int MMAX, int NB>
+__device__ __forceinline__ void extend_w(bool go, int mo, int mwb, int nbk, int gl, bool first, double *Wm,
+                                         const double *NR, double *LV, double r_ai, double &r_li, double &yi,
+                                         double &psi, bool &spd, int8_t &status, bool &act) {
+    // pass A: l_v[t] = sum_{j <= t} W[t][j] a_v[j] for the old positions t < m_o
+    double la[NB];
+#pragma unroll
+    for (int v = 0; v < NB; ++v) la[v] = 0.0;
+    {
+        // kPU entries of the row at a time: all loads first (in bounds: at most 7
+        // past the diagonal of the lane's row, or of row 0 for lanes without a row,
+        // within W's padding), then the entries right of the diagonal zeroed
+        const int lim = (go && gl < mo) ? gl : -1;
+        const double *wrow = Wm + tri_w(lim >= 0 ? gl : 0);
+        for (int j0 = 0; j0 < mwb; j0 += kPU) {
+            double wv[kPU];
+#pragma unroll
+            for (int u = 0; u < kPU; ++u) wv[u] = wrow[j0 + u];
+            const int d = lim - j0;
+#pragma unroll
+            for (int u = 0; u < kPU; ++u) wv[u] = u <= d ? wv[u] : 0.0;
+#pragma unroll
+            for (int v = 0; v < NB; ++v)
+                if (v < nbk)
+#pragma unroll
+                    for (int u = 0; u < kPU; ++u) la[v] = fma(wv[u], NR[v * MMAX + j0 + u], la[v]);
+        }
+    }
+    if (go && gl < MMAX) {
+        // every entry of the rows (zeros past the old positions) for pass B's
+        // unrolled reads
+#pragma unroll
+        for (int v = 0; v < NB; ++v) LV[v * MMAX + gl] = gl < mo ? la[v] : 0.0;
+        LV[NB * MMAX + gl] = (first && gl < mo) ? r_li : 0.0;
+    }
+    wsync();
+    // pass B: y_v[j] = sum_{j <= t < m_o} W[t][j] l_v[t], and the same with l_i
+    double yb[NB];
+#pragma unroll
+    for (int v = 0; v < NB; ++v) yb[v] = 0.0;
+    {
+        // all loads first: rows t of the chunk past the old positions read the last
+        // old row, lanes without an old position column 0 (in bounds); then the
+        // entries with t < j or t >= m_o zeroed
+        const int jc = (go && gl < mo) ? gl : 0;
+        const int lo = (go && gl < mo) ? gl : 0x7fffffff;
+        for (int t0 = 0; t0 < mwb; t0 += kPU) {
+            double wv[kPU];
+#pragma unroll
+            for (int u = 0; u < kPU; ++u) {
+                const int tc = min(t0 + u, mo - 1);
+                wv[u] = Wm[tri_w(tc) + jc];
+            }
+#pragma unroll
+            for (int u = 0; u < kPU; ++u) {
+                const int t = t0 + u;
+                wv[u] = (t >= lo && t < mo) ? wv[u] : 0.0;
+            }
+#pragma unroll
+            for (int v = 0; v < NB; ++v)
+                if (v < nbk)
+#pragma unroll
+                    for (int u = 0; u < kPU; ++u) yb[v] = fma(wv[u], LV[v * MMAX + t0 + u], yb[v]);
+#pragma unroll
+            for (int u = 0; u < kPU; ++u) yi = fma(wv[u], LV[NB * MMAX + t0 + u], yi);
+        }
+    }
+    // the new rows one by one: their coupling inside the block, d_u, and row p of W
+    double wn[NB];
+#pragma unroll
+    for (int v = 0; v < NB; ++v) wn[v] = 0.0;
+    if (wu<GS>(go)) {
+#pragma unroll
+        for (int v = 0; v < NB; ++v) {
+            if (v < nbk && wu<GS>(spd)) {
+                const int p = mo + v;
+                const double sq = gred<GS, OpSum>(gl < mo ? la[v] * la[v] : 0.0);
+                double d2 = NR[v * MMAX + p] - sq;
+                const double av_l = gl < MMAX ? NR[v * MMAX + (gl < MMAX ? gl : 0)] : 0.0;
+                double cp[NB];
+#pragma unroll
+                for (int w = 0; w < NB; ++w) {
+                    cp[w] = 0.0;
+                    if (w < v) {
+                        cp[w] = gred<GS, OpSum>(wn[w] * av_l);
+                        d2 = d2 - cp[w] * cp[w];
+                    }
+                }
+                if (!(d2 > 0.0) || !isfinite(d2)) {
+                    spd = false;
+                } else {
+                    const double dinv = rsqrt_nr(d2);
+                    double y = yb[v];
+#pragma unroll
+                    for (int w = 0; w < NB; ++w)
+                        if (w < v) y = fma(wn[w], cp[w], y);
+                    wn[v] = gl < p ? -(y * dinv) : (gl == p ? dinv : 0.0);
+                    if (gl <= p) Wm[tri_w(p) + gl] = wn[v];
+                }
+            }
+        }
+        if (wu<GS>(spd)) {
+            // l_i at the new positions and psi
+#pragma unroll
+            for (int w = 0; w < NB; ++w) {
+                if (w < nbk) {
+                    const double li = gred<GS, OpSum>(wn[w] * r_ai);
+                    if (gl == mo + w) r_li = li;
+                    psi = psi - li * li;
+                    yi = fma(wn[w], li, yi);
+                }
+            }
+        } else {
+            status = ROW_NOT_SPD;
+            act = false;
+        }
+    }
+}
+
 template <int GS, int MMAX, int CAP, int NB, bool G32>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(GS == 8 || (GS == 64 && MMAX <= 24 && CAP <= 512) ? 4 : (CAP <= 512 && MMAX <= 48 ? 3 : 1), 8))) void k_rows_w(
     int n, const int32_t *__restrict__ rp, const int32_t *__restrict__ ci, const double *__restrict__ av,
@@ -741,119 +864,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(GS == 8 || (
                 // a_{u,i} of the new positions
                 if (go && gl >= mo && gl < mo + nbk) r_ai = NAI[gl - mo];
 
-                // pass A: l_v[t] = sum_{j <= t} W[t][j] a_v[j] for the old positions t < m_o
-                double la[NB];
-#pragma unroll
-                for (int v = 0; v < NB; ++v) la[v] = 0.0;
-                {
-                    // kPU entries of the row at a time: all loads first (in bounds: at most 7
-                    // past the diagonal of the lane's row, or of row 0 for lanes without a row,
-                    // within W's padding), then the entries right of the diagonal zeroed
-                    const int lim = (go && gl < mo) ? gl : -1;
-                    const double *wrow = Wm + tri_w(lim >= 0 ? gl : 0);
-                    for (int j0 = 0; j0 < mwb; j0 += kPU) {
-                        double wv[kPU];
-#pragma unroll
-                        for (int u = 0; u < kPU; ++u) wv[u] = wrow[j0 + u];
-                        const int d = lim - j0;
-#pragma unroll
-                        for (int u = 0; u < kPU; ++u) wv[u] = u <= d ? wv[u] : 0.0;
-#pragma unroll
-                        for (int v = 0; v < NB; ++v)
-                            if (v < nbk)
-#pragma unroll
-                                for (int u = 0; u < kPU; ++u) la[v] = fma(wv[u], NR[v * MMAX + j0 + u], la[v]);
-                    }
-                }
-                if (go && gl < MMAX) {
-                    // every entry of the rows (zeros past the old positions) for pass B's
-                    // unrolled reads
-#pragma unroll
-                    for (int v = 0; v < NB; ++v) LV[v * MMAX + gl] = gl < mo ? la[v] : 0.0;
-                    LV[NB * MMAX + gl] = (first && gl < mo) ? r_li : 0.0;
-                }
-                wsync();
-                // pass B: y_v[j] = sum_{j <= t < m_o} W[t][j] l_v[t], and the same with l_i
-                double yb[NB];
-#pragma unroll
-                for (int v = 0; v < NB; ++v) yb[v] = 0.0;
-                {
-                    // all loads first: rows t of the chunk past the old positions read the last
-                    // old row, lanes without an old position column 0 (in bounds); then the
-                    // entries with t < j or t >= m_o zeroed
-                    const int jc = (go && gl < mo) ? gl : 0;
-                    const int lo = (go && gl < mo) ? gl : 0x7fffffff;
-                    for (int t0 = 0; t0 < mwb; t0 += kPU) {
-                        double wv[kPU];
-#pragma unroll
-                        for (int u = 0; u < kPU; ++u) {
-                            const int tc = min(t0 + u, mo - 1);
-                            wv[u] = Wm[tri_w(tc) + jc];
-                        }
-#pragma unroll
-                        for (int u = 0; u < kPU; ++u) {
-                            const int t = t0 + u;
-                            wv[u] = (t >= lo && t < mo) ? wv[u] : 0.0;
-                        }
-#pragma unroll
-                        for (int v = 0; v < NB; ++v)
-                            if (v < nbk)
-#pragma unroll
-                                for (int u = 0; u < kPU; ++u) yb[v] = fma(wv[u], LV[v * MMAX + t0 + u], yb[v]);
-#pragma unroll
-                        for (int u = 0; u < kPU; ++u) yi = fma(wv[u], LV[NB * MMAX + t0 + u], yi);
-                    }
-                }
-                // the new rows one by one: their coupling inside the block, d_u, and row p of W
-                double wn[NB];
-#pragma unroll
-                for (int v = 0; v < NB; ++v) wn[v] = 0.0;
-                if (wu<GS>(go)) {
-#pragma unroll
-                    for (int v = 0; v < NB; ++v) {
-                        if (v < nbk && wu<GS>(spd)) {
-                            const int p = mo + v;
-                            const double sq = gred<GS, OpSum>(gl < mo ? la[v] * la[v] : 0.0);
-                            double d2 = NR[v * MMAX + p] - sq;
-                            const double av_l = gl < MMAX ? NR[v * MMAX + (gl < MMAX ? gl : 0)] : 0.0;
-                            double cp[NB];
-#pragma unroll
-                            for (int w = 0; w < NB; ++w) {
-                                cp[w] = 0.0;
-                                if (w < v) {
-                                    cp[w] = gred<GS, OpSum>(wn[w] * av_l);
-                                    d2 = d2 - cp[w] * cp[w];
-                                }
-                            }
-                            if (!(d2 > 0.0) || !isfinite(d2)) {
-                                spd = false;
-                            } else {
-                                const double dinv = rsqrt_nr(d2);
-                                double y = yb[v];
-#pragma unroll
-                                for (int w = 0; w < NB; ++w)
-                                    if (w < v) y = fma(wn[w], cp[w], y);
-                                wn[v] = gl < p ? -(y * dinv) : (gl == p ? dinv : 0.0);
-                                if (gl <= p) Wm[tri_w(p) + gl] = wn[v];
-                            }
-                        }
-                    }
-                    if (wu<GS>(spd)) {
-                        // l_i at the new positions and psi
-#pragma unroll
-                        for (int w = 0; w < NB; ++w) {
-                            if (w < nbk) {
-                                const double li = gred<GS, OpSum>(wn[w] * r_ai);
-                                if (gl == mo + w) r_li = li;
-                                psi = psi - li * li;
-                                yi = fma(wn[w], li, yi);
-                            }
-                        }
-                    } else {
-                        status = ROW_NOT_SPD;
-                        act = false;
-                    }
-                }
+                extend_w<GS, MMAX, NB>(go, mo, mwb, nbk, gl, first, Wm, NR, LV, r_ai, r_li, yi, psi, spd, status, act);
                 if (blk) {
                     m_o += nbk;
                     nsd += nbk;

@@ -956,3 +956,58 @@ def test_full_size_elasticity150_sampled(af):
     assert info.converged and info.true_relres <= 1.1e-8
     print(f"150^3 27-point: setup {r['info'].ms:.0f} ms, nnz(G) {r['info'].nnz_g}, PCG {info.iters} iterations "
           f"{info.ms:.0f} ms, test {time.time() - t0:.0f} s")
+
+
+def _node_blocks(nodes, per_node, seed):
+    """Random symmetric node graph with a dense 3 x 3 block per edge, diagonally dominant: rows of
+    aligned runs of three columns that reach all over the matrix."""
+    import scipy.sparse as sp
+
+    g = synth.random_sparse_spd(nodes, per_node, seed).to_scipy()
+    g.data[:] = 1.0
+    m = sp.kron(g, np.ones((3, 3)), format="csr")
+    u = sp.triu(m, 1, format="csr")
+    u.data = synth.uniform(seed, 77, u.nnz)
+    m = (u + u.T).tocsr()
+    return synth.CSR.from_scipy(m + sp.diags(1.0 + np.asarray(abs(m).sum(axis=1)).ravel()))
+
+
+@pytest.mark.parametrize("make,kmax,s", [
+    (lambda: synth.elast27(3, 1.0, 2), 1, 1), (lambda: synth.elast27(7, 1.0, 2), 1, 2),
+    (lambda: synth.elast27(9, 1.0, 3), 23, 1), (lambda: synth.elast27(8, 1.0, 4), 8, 3),
+    (lambda: synth.elast27(8, 2.0, 5), 31, 1), (lambda: synth.elast27(8, 1.0, 6), 4, 8),
+    (lambda: synth.elast27(9, 2.0, 7), 15, 3), (lambda: synth.elast27(7, 2.0, 8), 47, 1),
+    (lambda: synth.elast27(7, 2.0, 9), 6, 8), (lambda: synth.elast27(6, 1.0, 10), 21, 3),
+    (lambda: _node_blocks(700, 5, 11), 10, 2), (lambda: _node_blocks(700, 6, 12), 15, 3),
+    (lambda: _node_blocks(150, 1, 13), 10, 2)])
+def test_setup_runs_of_three(af, make, kmax, s):
+    """Matrices of aligned runs of three columns, over the pattern sizes of the run form's instances
+    (24, 32, 48 and 64 positions), one to eight new rows a step, rows of few runs and of the most a
+    lane group takes, and tables that overflow: G, psi, steps and stop reasons equal the general
+    form's (64 lanes a row asked for) bit for bit."""
+    A = make()
+    assert A.n % 3 == 0 and np.all(A.col[::3] % 3 == 0) and np.diff(A.row_ptr).max() <= 96
+    dA = _dev(af, A)
+
+    def run():
+        P = af.setup(dA, kmax, s, 1e-3)
+        return _gpu_factor(af, P) + tuple(t.cpu().numpy() for t in P.export_rows())
+
+    auto = run()
+    try:
+        af.set_option(af.OPT_SETUP_LANES, 64)
+        general = run()
+    finally:
+        af.set_option(af.OPT_SETUP_LANES, 0)
+    for a, b in zip(auto, general):
+        np.testing.assert_array_equal(a.view(np.int64) if a.dtype == np.float64 else a,
+                                      b.view(np.int64) if b.dtype == np.float64 else b)
+
+
+@pytest.mark.parametrize("cut", [1, 3])
+def test_setup_runs_shifted(af, cut):
+    """The leading rows and columns of a 3-dof matrix taken off: by one, its runs no longer start at
+    multiples of three and the general form runs; by a whole node, the run form does.  Both match the oracle."""
+    full = synth.elast27(6, 1.0, 2).to_scipy()
+    A = synth.CSR.from_scipy(full[cut:, cut:])
+    compare_factor(af, A, 10, 2, 1e-2)
