@@ -42,7 +42,8 @@ constexpr int kRunRow = 32;         // runs of a row of A at most (one per lane 
 template <int GS, int MMAX, int CAPT, int NB>
 struct Layout {
     static constexpr int VALB = 3 * CAPT * 8;
-    static constexpr int ALV = (2 * NB + 1) * MMAX + NB;  // NR, LV (with LI), NAI in doubles
+    static constexpr int LDV = MMAX + 2;  // rows of NR and LV (see rows_w.hpp)
+    static constexpr int ALV = (2 * NB + 1) * LDV + NB;  // NR, LV (with LI), NAI in doubles
     static constexpr int O_KEY = 0;
     static constexpr int O_INF = CAPT * 4;
     static constexpr int O_VAL = CAPT * 8;
@@ -54,9 +55,8 @@ struct Layout {
     static_assert(ALV * 8 + 12 * MMAX <= VALB, "the step's vectors fit in the gradient planes");
     static_assert(CAPT % 4 == 0 && CAPT <= 256, "buckets of four keys, slots in a byte");
     // (8 doubles after W: the unrolled products read up to 7 entries past a row's diagonal)
-    static __host__ __device__ constexpr int bytes(int mm) {
-        return FIXED + wform::al16(((mm > 1 ? (mm - 1) * mm / 2 : 0) + 8) * 8);
-    }
+    static __host__ __device__ constexpr int w_entries(int mm) { return mm > 1 ? (mm - 1) * mm / 2 : 0; }
+    static __host__ __device__ constexpr int bytes(int mm) { return FIXED + wform::al16((w_entries(mm) + 8) * 8); }
 };
 
 // Finds the run starting at column c, inserting it when absent; its slot, or -1 when the table
@@ -126,6 +126,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
     static_assert(GS == 32 || GS == 64, "32 lanes take a row of A");
     static_assert(MMAX <= GS, "one lane per pattern position");
     constexpr int RPW = 64 / GS;                   // rows per wavefront
+    constexpr int LDV = LY::LDV;
     constexpr int HPG = GS / 32;                   // rows of A a group takes at once
     constexpr int SPL = (CAPT + GS - 1) / GS;      // table slots per lane
     constexpr int NSL = (MMAX / HPG + 3) / 4;      // slot registers (four bytes each)
@@ -146,10 +147,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
     int32_t *sel = reinterpret_cast<int32_t *>(gbase + LY::O_SEL);  // [MMAX] selected columns
     int32_t *selb = sel + MMAX;                                     // [MMAX] their row starts
     int32_t *sele = selb + MMAX;                                    // [MMAX] their row ends
-    double *NR = hval;                                              // [NB][MMAX]
-    double *LV = NR + NB * MMAX;                                    // [NB+1][MMAX]
-    double *NAI = LV + (NB + 1) * MMAX;                             // [NB]: a_{u,i}
+    double *NR = hval;                                              // [NB][LDV]
+    double *LV = NR + NB * LDV;                                     // [NB+1][LDV]
+    double *NAI = LV + (NB + 1) * LDV;                              // [NB]: a_{u,i}
     const uint64_t gm = wform::group_bits<GS>(grp);
+    const int zslot = LY::w_entries(mmx);  // of the padding after W, zero for the matrix products
+    if (gl == 0) Wm[zslot] = 0.0;
     const double kNaN = __longlong_as_double(0x7FF8000000000000ll);
 
     const int x = blockIdx.x % nxcd;
@@ -385,8 +388,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
                 const int nbk = wu<GS>(blk ? min(NB, ns - nsd) : 0);
                 if (blk) {
 #pragma unroll
-                    for (int jj = 0; jj < (NB * MMAX + GS - 1) / GS; ++jj)
-                        if (gl + GS * jj < NB * MMAX) NR[gl + GS * jj] = 0.0;
+                    for (int jj = 0; jj < (NB * LDV + GS - 1) / GS; ++jj)
+                        if (gl + GS * jj < NB * LDV) NR[gl + GS * jj] = 0.0;
                     if (gl < NB) NAI[gl] = 0.0;
                 }
                 wsync();
@@ -430,7 +433,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
 #pragma unroll
                                 for (int y = 0; y < 3; ++y) {
                                     const int ps = (int)((f >> (8 * y)) & 0xFFu);
-                                    if (ps) NR[v * MMAX + ps - 1] = ga[w][y];
+                                    if (ps) NR[v * LDV + ps - 1] = ga[w][y];
                                 }
                             }
                         }
@@ -464,8 +467,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
                 const bool go = blk && act;
                 // a_{u,i} of the new positions
                 if (go && gl >= mo && gl < mo + nbk) r_ai = NAI[gl - mo];
-                wform::extend_w<GS, MMAX, NB>(go, mo, mwb, nbk, gl, first, Wm, NR, LV, r_ai, r_li, yi, psi, spd, status,
-                                              act);
+                wform::extend_w<GS, MMAX, NB, LDV>(go, mo, mwb, nbk, gl, first, LY::bytes(mmx) / 8, zslot, s >= 4, Wm,
+                                                   NR, LV, r_ai, r_li, yi, psi, spd, status, act);
                 if (blk) {
                     m_o += nbk;
                     nsd += nbk;

@@ -69,7 +69,12 @@ template <int GS, int MMAX, int CAP, int NB>
 struct Layout {
     static constexpr int SPW = spw_of(GS);
     static constexpr int LROW = GS * SPW;
-    static constexpr int ALV = (2 * NB + 1) * MMAX + NB;          // NR, LV (with LI), NAI in doubles
+    // NR and LV rows: whole chunks of the matrix-core products (GS / 4 positions), and two entries
+    // of padding (the four rows read at once then fall in distinct banks) if the vectors still fit
+    // in the gradient array
+    static constexpr int LDM = GS >= 32 ? (MMAX + GS / 4 - 1) / (GS / 4) * (GS / 4) : MMAX;
+    static constexpr int LDV = LDM + (GS >= 32 && ((2 * NB + 1) * (LDM + 2) + NB) * 8 + 12 * MMAX <= CAP * 8 ? 2 : 0);
+    static constexpr int ALV = (2 * NB + 1) * LDV + NB;            // NR, LV (with LI), NAI in doubles
     static constexpr bool ALIAS = ALV * 8 + 12 * MMAX <= CAP * 8;  // beside the selected columns
     static constexpr int O_HKEY = 0;
     static constexpr int O_HVAL = al16(CAP * 4);
@@ -324,75 +329,199 @@ __device__ __forceinline__ void top2(const uint32_t *hkey, const double *hval, i
     }
 }
 
-// Steps 4 of a block of nbk <= NB new rows (positions mo .. mo + nbk - 1, their entries at the
-// old and new positions in NR, a_{u,i} in r_ai): the rows of W, l_i's new entries (r_li), psi and
-// yi = W^T l_i of this step so far.  go: this group takes part; mwb: the most old positions of a
-// group of the wavefront; first: the step's first block (l_i's old entries are added to yi then).
-template <int GS, int MMAX, int NB>
-__device__ __forceinline__ void extend_w(bool go, int mo, int mwb, int nbk, int gl, bool first, double *Wm,
-                                         const double *NR, double *LV, double r_ai, double &r_li, double &yi,
-                                         double &psi, bool &spd, int8_t &status, bool &act) {
-    // pass A: l_v[t] = sum_{j <= t} W[t][j] a_v[j] for the old positions t < m_o
-    double la[NB];
+// Both products with W of a block of new rows, on the matrix cores (groups of 32 or 64 lanes):
+// la[v] = (W a_v)_gl, yb[v] = (W^T l_v)_gl and, for the first block of a step, yi = (W^T l_i)_gl.
+// v_mfma_f64_4x4x4_4b holds four 4 x 4 x 4 products (operand lanes i + 4 block + 16 k, results
+// j + 4 block + 16 i): the blocks of a group take tiles of four rows of W (columns, for W^T), the
+// four columns of a tile are the new rows and l_i.  It adds its four terms in ascending order
+// with one rounding each, so with the tiles in order every result is the same fma chain as a
+// lane's loop over j (or t), bit for bit.  NC: chunks of 4 tiles (2 with 32 lanes) that hold old
+// positions.  Against that loop (eight LDS reads, selects and up to 24 fma per eight entries,
+// half of them above the diagonal): 64^3 setup 15.7 -> 14.5 ms, 150^3 step 1,305 -> 1,101 ms.
+template <int GS, int MMAX, int NB, int LDV, int NC>
+__device__ __forceinline__ void w_products(const double *Wb, const double *NRb, double *LVb, double *LV, int mo_b, int mo,
+                                           int zslot, bool go, bool first, bool sep, int gl, double (&la)[NB],
+                                           double (&yb)[NB], double &yi) {
+    constexpr int BPG = GS / 16;  // blocks of a group
+    int lane = threadIdx.x & 63;
+    // (opaque: the addresses of every tile are otherwise computed once for the whole kernel and
+    // kept in registers, which spills)
+    __asm__ __volatile__("" : "+v"(lane));
+    const int mi = lane >> 4, mj = lane & 3;
+    const int sub = ((lane >> 2) & 3) % BPG;
+    // pass A: rows t of tile tp * BPG + sub, lane i = mj; t < 0: no such row
+    double acc[NC];
+    int tl[NC], tb[NC];
 #pragma unroll
-    for (int v = 0; v < NB; ++v) la[v] = 0.0;
-    {
-        // kPU entries of the row at a time: all loads first (in bounds: at most 7
-        // past the diagonal of the lane's row, or of row 0 for lanes without a row,
-        // within W's padding), then the entries right of the diagonal zeroed
-        const int lim = (go && gl < mo) ? gl : -1;
-        const double *wrow = Wm + tri_w(lim >= 0 ? gl : 0);
-        for (int j0 = 0; j0 < mwb; j0 += kPU) {
-            double wv[kPU];
+    for (int tp = 0; tp < NC; ++tp) {
+        const int t = 4 * (tp * BPG + sub) + mj;
+        acc[tp] = 0.0;
+        tl[tp] = t < mo_b ? t : -1;
+        tb[tp] = tri_w(t);
+    }
+    const double *nr = NRb + (mj < NB ? mj : NB - 1) * LDV + mi;
 #pragma unroll
-            for (int u = 0; u < kPU; ++u) wv[u] = wrow[j0 + u];
-            const int d = lim - j0;
+    for (int c = 0; c < NC; ++c)
 #pragma unroll
-            for (int u = 0; u < kPU; ++u) wv[u] = u <= d ? wv[u] : 0.0;
+        for (int jj = 0; jj < BPG; ++jj) {
+            const int jt = c * BPG + jj, j = 4 * jt + mi;
+            const double bv = nr[4 * jt];
 #pragma unroll
-            for (int v = 0; v < NB; ++v)
-                if (v < nbk)
+            for (int tp = c; tp < NC; ++tp)
+                acc[tp] = __builtin_amdgcn_mfma_f64_4x4x4f64(Wb[j <= tl[tp] ? tb[tp] + j : zslot], bv, acc[tp], 0, 0, 0);
+        }
+    if (mj < NB)
 #pragma unroll
-                    for (int u = 0; u < kPU; ++u) la[v] = fma(wv[u], NR[v * MMAX + j0 + u], la[v]);
+        for (int tp = 0; tp < NC; ++tp) LVb[mj * LDV + 4 * (tp * BPG + sub) + mi] = acc[tp];
+    wsync();
+    // pass B: columns j of tile jp * BPG + sub; column 3 of a tile is l_i (a pass of its own
+    // when four new rows may fill the tile)
+    double y[NC];
+#pragma unroll
+    for (int jp = 0; jp < NC; ++jp) y[jp] = 0.0;
+    const int lrow = mj < NB && (mj < 3 || sep) ? mj : NB;
+    const double *lv = LVb + lrow * LDV + mi;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int tt = c * BPG; tt < (c + 1) * BPG; ++tt) {
+            const int t = 4 * tt + mi;
+            const int row = tri_w(t);
+            const bool in = t < mo_b;
+            const double bv = lv[4 * tt];
+#pragma unroll
+            for (int jp = 0; jp <= c; ++jp) {
+                const int j = 4 * (jp * BPG + sub) + mj;
+                y[jp] = __builtin_amdgcn_mfma_f64_4x4x4f64(Wb[in && (jp < c || j <= t) ? row + j : zslot], bv, y[jp], 0, 0, 0);
+            }
+        }
+    double yl[NC];
+#pragma unroll
+    for (int jp = 0; jp < NC; ++jp) yl[jp] = 0.0;
+    if (NB == 4 && sep) {
+        const double *li = LVb + NB * LDV + mi;
+        for (int tt = 0; tt < NC * BPG; ++tt) {
+            const int t = 4 * tt + mi;
+            const double bl = li[4 * tt];
+#pragma unroll
+            for (int jp = 0; jp < NC; ++jp) {
+                const int j = 4 * (jp * BPG + sub) + mj;
+                yl[jp] = __builtin_amdgcn_mfma_f64_4x4x4f64(Wb[t < mo_b && j <= t ? tri_w(t) + j : zslot], bl, yl[jp], 0, 0, 0);
+            }
         }
     }
-    if (go && gl < MMAX) {
-        // every entry of the rows (zeros past the old positions) for pass B's
-        // unrolled reads
 #pragma unroll
-        for (int v = 0; v < NB; ++v) LV[v * MMAX + gl] = gl < mo ? la[v] : 0.0;
-        LV[NB * MMAX + gl] = (first && gl < mo) ? r_li : 0.0;
+    for (int v = 0; v < NB; ++v) la[v] = go && gl < mo ? LV[v * LDV + gl] : 0.0;
+    wsync();
+    const int yrow = mj == 3 && !sep ? NB : mj;
+#pragma unroll
+    for (int jp = 0; jp < NC; ++jp) {
+        const int j = 4 * (jp * BPG + sub) + mi;
+        if (yrow <= NB) LVb[yrow * LDV + j] = y[jp];
+        if (NB == 4 && sep && mj == 0) LVb[NB * LDV + j] = yl[jp];
     }
     wsync();
-    // pass B: y_v[j] = sum_{j <= t < m_o} W[t][j] l_v[t], and the same with l_i
-    double yb[NB];
 #pragma unroll
-    for (int v = 0; v < NB; ++v) yb[v] = 0.0;
-    {
-        // all loads first: rows t of the chunk past the old positions read the last
-        // old row, lanes without an old position column 0 (in bounds); then the
-        // entries with t < j or t >= m_o zeroed
-        const int jc = (go && gl < mo) ? gl : 0;
-        const int lo = (go && gl < mo) ? gl : 0x7fffffff;
-        for (int t0 = 0; t0 < mwb; t0 += kPU) {
-            double wv[kPU];
+    for (int v = 0; v < NB; ++v) yb[v] = go && gl < mo ? LV[v * LDV + gl] : 0.0;
+    if (go && first) yi = gl < mo ? LV[NB * LDV + gl] : 0.0;
+}
+
+// Step 4 of a block of nbk <= NB new rows (positions mo .. mo + nbk - 1, their entries at the
+// old and new positions in NR, a_{u,i} in r_ai): the rows of W, l_i's new entries (r_li), psi and
+// yi = W^T l_i of this step so far.  go: this group takes part; mwb: the most old positions of a
+// group of the wavefront; first: the step's first block (l_i's old entries are added to yi then);
+// gst: doubles from one group's LDS to the next; zslot: an entry of W that holds zero; sep: steps
+// of four or more new rows.  NR and LV have rows of LDV entries.
+template <int GS, int MMAX, int NB, int LDV>
+__device__ __forceinline__ void extend_w(bool go, int mo, int mwb, int nbk, int gl, bool first, int gst, int zslot,
+                                         bool sep, double *Wm, const double *NR, double *LV, double r_ai, double &r_li,
+                                         double &yi, double &psi, bool &spd, int8_t &status, bool &act) {
+    double la[NB], yb[NB];
 #pragma unroll
-            for (int u = 0; u < kPU; ++u) {
-                const int tc = min(t0 + u, mo - 1);
-                wv[u] = Wm[tri_w(tc) + jc];
+    for (int v = 0; v < NB; ++v) la[v] = yb[v] = 0.0;
+    if constexpr (GS >= 32) {
+        constexpr int BPG = GS / 16, TPC = 4 * BPG;  // positions of a chunk
+        static_assert((MMAX + TPC - 1) / TPC <= 4, "one to four chunks");
+        const int lane = threadIdx.x & 63;
+        const int bg = GS == 32 ? (lane >> 3) & 1 : 0, grp = lane / GS;
+        const int mog = go ? mo : 0;
+        int mo_b = mog;  // old positions of the group that this lane's block works for
+        if constexpr (GS == 32) {
+            const int m0 = rlane(mog, 0), m1 = rlane(mog, 32);
+            mo_b = bg ? m1 : m0;
+        }
+        const double *Wb = Wm + (bg - grp) * gst, *NRb = NR + (bg - grp) * gst;
+        double *LVb = LV + (bg - grp) * gst;
+        if (gl < LDV) LV[NB * LDV + gl] = (go && first && gl < mo) ? r_li : 0.0;
+        const int nc = (mwb + TPC - 1) / TPC;
+        if (nc == 1) {
+            w_products<GS, MMAX, NB, LDV, 1>(Wb, NRb, LVb, LV, mo_b, mo, zslot, go, first, sep, gl, la, yb, yi);
+        } else if (nc == 2) {
+            w_products<GS, MMAX, NB, LDV, 2>(Wb, NRb, LVb, LV, mo_b, mo, zslot, go, first, sep, gl, la, yb, yi);
+        } else if (nc == 3) {
+            if constexpr (MMAX > 2 * TPC)
+                w_products<GS, MMAX, NB, LDV, 3>(Wb, NRb, LVb, LV, mo_b, mo, zslot, go, first, sep, gl, la, yb, yi);
+        } else if (nc == 4) {
+            if constexpr (MMAX > 3 * TPC)
+                w_products<GS, MMAX, NB, LDV, 4>(Wb, NRb, LVb, LV, mo_b, mo, zslot, go, first, sep, gl, la, yb, yi);
+        }
+    } else {
+        // pass A: l_v[t] = sum_{j <= t} W[t][j] a_v[j] for the old positions t < m_o
+        {
+            // kPU entries of the row at a time: all loads first (in bounds: at most 7
+            // past the diagonal of the lane's row, or of row 0 for lanes without a row,
+            // within W's padding), then the entries right of the diagonal zeroed
+            const int lim = (go && gl < mo) ? gl : -1;
+            const double *wrow = Wm + tri_w(lim >= 0 ? gl : 0);
+            for (int j0 = 0; j0 < mwb; j0 += kPU) {
+                double wv[kPU];
+#pragma unroll
+                for (int u = 0; u < kPU; ++u) wv[u] = wrow[j0 + u];
+                const int d = lim - j0;
+#pragma unroll
+                for (int u = 0; u < kPU; ++u) wv[u] = u <= d ? wv[u] : 0.0;
+#pragma unroll
+                for (int v = 0; v < NB; ++v)
+                    if (v < nbk)
+#pragma unroll
+                        for (int u = 0; u < kPU; ++u) la[v] = fma(wv[u], NR[v * LDV + j0 + u], la[v]);
             }
+        }
+        if (go && gl < MMAX) {
+            // every entry of the rows (zeros past the old positions) for pass B's
+            // unrolled reads
 #pragma unroll
-            for (int u = 0; u < kPU; ++u) {
-                const int t = t0 + u;
-                wv[u] = (t >= lo && t < mo) ? wv[u] : 0.0;
+            for (int v = 0; v < NB; ++v) LV[v * LDV + gl] = gl < mo ? la[v] : 0.0;
+            LV[NB * LDV + gl] = (first && gl < mo) ? r_li : 0.0;
+        }
+        wsync();
+        // pass B: y_v[j] = sum_{j <= t < m_o} W[t][j] l_v[t], and the same with l_i
+        {
+            // all loads first: rows t of the chunk past the old positions read the last
+            // old row, lanes without an old position column 0 (in bounds); then the
+            // entries with t < j or t >= m_o zeroed
+            const int jc = (go && gl < mo) ? gl : 0;
+            const int lo = (go && gl < mo) ? gl : 0x7fffffff;
+            for (int t0 = 0; t0 < mwb; t0 += kPU) {
+                double wv[kPU];
+#pragma unroll
+                for (int u = 0; u < kPU; ++u) {
+                    const int tc = min(t0 + u, mo - 1);
+                    wv[u] = Wm[tri_w(tc) + jc];
+                }
+#pragma unroll
+                for (int u = 0; u < kPU; ++u) {
+                    const int t = t0 + u;
+                    wv[u] = (t >= lo && t < mo) ? wv[u] : 0.0;
+                }
+#pragma unroll
+                for (int v = 0; v < NB; ++v)
+                    if (v < nbk)
+#pragma unroll
+                        for (int u = 0; u < kPU; ++u) yb[v] = fma(wv[u], LV[v * LDV + t0 + u], yb[v]);
+#pragma unroll
+                for (int u = 0; u < kPU; ++u) yi = fma(wv[u], LV[NB * LDV + t0 + u], yi);
             }
-#pragma unroll
-            for (int v = 0; v < NB; ++v)
-                if (v < nbk)
-#pragma unroll
-                    for (int u = 0; u < kPU; ++u) yb[v] = fma(wv[u], LV[v * MMAX + t0 + u], yb[v]);
-#pragma unroll
-            for (int u = 0; u < kPU; ++u) yi = fma(wv[u], LV[NB * MMAX + t0 + u], yi);
         }
     }
     // the new rows one by one: their coupling inside the block, d_u, and row p of W
@@ -405,8 +534,8 @@ __device__ __forceinline__ void extend_w(bool go, int mo, int mwb, int nbk, int 
             if (v < nbk && wu<GS>(spd)) {
                 const int p = mo + v;
                 const double sq = gred<GS, OpSum>(gl < mo ? la[v] * la[v] : 0.0);
-                double d2 = NR[v * MMAX + p] - sq;
-                const double av_l = gl < MMAX ? NR[v * MMAX + (gl < MMAX ? gl : 0)] : 0.0;
+                double d2 = NR[v * LDV + p] - sq;
+                const double av_l = gl < MMAX ? NR[v * LDV + (gl < MMAX ? gl : 0)] : 0.0;
                 double cp[NB];
 #pragma unroll
                 for (int w = 0; w < NB; ++w) {
@@ -461,6 +590,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(GS == 8 || (
     constexpr int RPW = 64 / GS;
     constexpr int SPW = LY::SPW;
     constexpr int SLW = SPW / 2;
+    constexpr int LDV = LY::LDV;
     constexpr int SPL = CAP / GS;                 // table slots per lane
     static_assert(12 * MMAX <= CAP * 8, "the selected columns fit in the gradient array");
     constexpr int HMAX = (128 + GS - 1) / GS;     // chunks of a gathered row (rows <= 128 entries)
@@ -481,11 +611,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(GS == 8 || (
     int32_t *sel = reinterpret_cast<int32_t *>(gbase + LY::O_SEL);  // [MMAX] selected columns
     int32_t *selb = sel + MMAX;                                     // [MMAX] their row starts
     int32_t *sele = selb + MMAX;                                    // [MMAX] their row ends
-    double *NR = LY::ALIAS ? hval : reinterpret_cast<double *>(gbase + LY::O_AL);  // [NB][MMAX]
-    double *LV = NR + NB * MMAX;                                                   // [NB+1][MMAX]
-    double *NAI = LV + (NB + 1) * MMAX;                                            // [NB]: a_{u,i}
+    double *NR = LY::ALIAS ? hval : reinterpret_cast<double *>(gbase + LY::O_AL);  // [NB][LDV]
+    double *LV = NR + NB * LDV;                                                    // [NB+1][LDV]
+    double *NAI = LV + (NB + 1) * LDV;                                             // [NB]: a_{u,i}
     const uint64_t gm = group_bits<GS>(grp);
     const double tauv = tau;
+    const int zslot = LY::w_entries(mmx);  // of the padding after W, zero for the matrix products
+    if (gl == 0) Wm[zslot] = 0.0;
 
     const int x = blockIdx.x % nxcd;
     const int64_t per = ((int64_t)nlist + nxcd - 1) / nxcd;
@@ -729,8 +861,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(GS == 8 || (
                 const int nbk = wu<GS>(blk ? min(NB, ns - nsd) : 0);
                 if (blk) {
 #pragma unroll
-                    for (int jj = 0; jj < (NB * MMAX + GS - 1) / GS; ++jj)
-                        if (gl + GS * jj < NB * MMAX) NR[gl + GS * jj] = 0.0;
+                    for (int jj = 0; jj < (NB * LDV + GS - 1) / GS; ++jj)
+                        if (gl + GS * jj < NB * LDV) NR[gl + GS * jj] = 0.0;
                     if (gl < NB) NAI[gl] = 0.0;
                 }
                 wsync();
@@ -789,11 +921,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(GS == 8 || (
                                 } else {
                                     if (l0) {
                                         pk[0] |= (uint32_t)s0;
-                                        if (k0 & kMember) NR[v * MMAX + (int)((k0 >> 24) & 0x7Fu)] = a0;
+                                        if (k0 & kMember) NR[v * LDV + (int)((k0 >> 24) & 0x7Fu)] = a0;
                                     }
                                     if (l1) {
                                         pk[0] |= (uint32_t)s1 << 16;
-                                        if (k1 & kMember) NR[v * MMAX + (int)((k1 >> 24) & 0x7Fu)] = a1;
+                                        if (k1 & kMember) NR[v * LDV + (int)((k1 >> 24) & 0x7Fu)] = a1;
                                     }
                                 }
                                 nlo = __popcll(__ballot(l0) & gm) + __popcll(__ballot(l1) & gm);
@@ -824,7 +956,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(GS == 8 || (
                                                 bad = true;
                                             } else {
                                                 if (h < SPW) pk[(h < SPW ? h : 0) >> 1] |= (uint32_t)slot << (16 * (h & 1));
-                                                if (kf & kMember) NR[v * MMAX + (int)((kf >> 24) & 0x7Fu)] = a;
+                                                if (kf & kMember) NR[v * LDV + (int)((kf >> 24) & 0x7Fu)] = a;
                                             }
                                         }
                                     }
@@ -864,7 +996,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(GS == 8 || (
                 // a_{u,i} of the new positions
                 if (go && gl >= mo && gl < mo + nbk) r_ai = NAI[gl - mo];
 
-                extend_w<GS, MMAX, NB>(go, mo, mwb, nbk, gl, first, Wm, NR, LV, r_ai, r_li, yi, psi, spd, status, act);
+                extend_w<GS, MMAX, NB, LDV>(go, mo, mwb, nbk, gl, first, LY::bytes(mmx) / 8, zslot, s >= 4, Wm, NR, LV, r_ai, r_li, yi, psi, spd, status, act);
                 if (blk) {
                     m_o += nbk;
                     nsd += nbk;
