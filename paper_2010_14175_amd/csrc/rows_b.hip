@@ -5,18 +5,27 @@
 namespace afsai {
 
 template <int GS, int MMAX, int CAPT, int NB, int WPE>
-static RowsKernel b_inst(int mm, int *gs, size_t *lds) {
+static RowsKernel b_inst(int mm, int s, int *gs, size_t *lds) {
     *gs = GS;
-    *lds = (size_t)(64 / GS) * (size_t)bform::Layout<GS, MMAX, CAPT, NB>::bytes(mm);
+    *lds = (size_t)(64 / GS) * (size_t)bform::Layout<GS, MMAX, CAPT, NB>::bytes(mm, s);
     return bform::k_rows_b<GS, MMAX, CAPT, NB, WPE>;
 }
 
-RowsKernel rows_kernel_b(int mmax, int maxlen, int *gs_out, size_t *lds_out) {
+RowsKernel rows_kernel_b(int mmax, int s, int maxlen, int *gs_out, size_t *lds_out) {
     if (maxlen > 3 * bform::kRunRow || mmax > 64) return nullptr;
-    if (mmax <= 24) return b_inst<32, 24, 128, 2, 3>(mmax, gs_out, lds_out);
-    if (mmax <= 32) return b_inst<32, 32, 160, 4, 3>(mmax, gs_out, lds_out);
-    if (mmax <= 48) return b_inst<64, 48, 176, 4, 3>(mmax, gs_out, lds_out);
-    return b_inst<64, 64, 256, 4, 2>(mmax, gs_out, lds_out);
+    // Table slots: what the patterns of the 27-point operators touch (99.9% of their rows: 56 runs
+    // for 11 positions, 90 for 21, 148 for 46), no more: fewer slots are fewer bytes of LDS (64^3:
+    // 12.3 ms with 128 slots, 10.4 ms with 92, 16 wavefronts per CU) and fewer to scan.  150^3: 618 ms
+    // with 176 slots, 654 with 192 (10 wavefronts per CU), 625 with 160 (longer probes).  Rows that
+    // touch more are redone by the general form.  New rows per block: as the general form's (2, 4),
+    // 3 for three or fewer rows a step (the same blocks).
+    if (mmax <= 12) return b_inst<32, 24, 64, 2, 4>(mmax, s, gs_out, lds_out);
+    if (mmax <= 24) return b_inst<32, 24, 92, 2, 4>(mmax, s, gs_out, lds_out);
+    if (mmax <= 32)
+        return s <= 3 ? b_inst<32, 32, 128, 3, 3>(mmax, s, gs_out, lds_out) : b_inst<32, 32, 128, 4, 3>(mmax, s, gs_out, lds_out);
+    if (mmax <= 48)
+        return s <= 3 ? b_inst<64, 48, 176, 3, 3>(mmax, s, gs_out, lds_out) : b_inst<64, 48, 176, 4, 3>(mmax, s, gs_out, lds_out);
+    return s <= 3 ? b_inst<64, 64, 256, 3, 2>(mmax, s, gs_out, lds_out) : b_inst<64, 64, 256, 4, 2>(mmax, s, gs_out, lds_out);
 }
 
 }  // namespace afsai

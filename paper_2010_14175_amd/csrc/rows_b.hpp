@@ -8,8 +8,9 @@
 // serve three entries.  Patterns of up to 32 positions put two rows on a wavefront (32 lanes
 // each); larger ones keep one row per wavefront, whose halves take two member rows (and two
 // gathered rows) at once.  The slot bytes need 6 registers where k_rows_w keeps 24 (48).
-// Measured against k_rows_w: the 64^3 setup (21 positions) 22.0 -> 15.7 ms, the 150^3 step (46
-// positions, 0.98 s of it this kernel before) 1,416 -> 1,305 ms.
+// Measured: this kernel takes 10.4 ms at 64^3 (21 positions) and 594 ms at 150^3 (46 positions),
+// k_rows_w with the same products 20.4 and 985 ms before.  Now bound by instruction issue and
+// LDS alike (each over half busy), with 16 and 11 wavefronts per CU by LDS.
 //
 // Layout of one row group (LDS): per table slot the run's first column, a word with one byte
 // per column (0: candidate, p + 1: member at position p) and three gradients (one plane per
@@ -47,23 +48,27 @@ struct Layout {
     static constexpr int O_KEY = 0;
     static constexpr int O_INF = CAPT * 4;
     static constexpr int O_VAL = CAPT * 8;
-    static constexpr int O_SEL = O_VAL + VALB - 12 * MMAX;  // sel, row start, row end [MMAX]
-    static constexpr int O_MS = O_VAL + VALB;               // Memb[MMAX]
+    static constexpr int O_MS = O_VAL + VALB;  // Memb[MMAX] (product pass)
+    static constexpr int O_SEL = O_MS;         // sel, row start, row end [MMAX] (from the selection on)
     static constexpr int FIXED = wform::al16(O_MS + MMAX * 16);
-    // between the selection and the next product pass the gradient planes hold, from their
-    // start, the gathered rows and product vectors and, at their end, the selected columns
-    static_assert(ALV * 8 + 12 * MMAX <= VALB, "the step's vectors fit in the gradient planes");
+    // between the selection and the next product pass the gradient planes hold the gathered rows
+    // and product vectors
+    static_assert(ALV * 8 <= VALB, "the step's vectors fit in the gradient planes");
     static_assert(CAPT % 4 == 0 && CAPT <= 256, "buckets of four keys, slots in a byte");
     // (8 doubles after W: the unrolled products read up to 7 entries past a row's diagonal)
-    static __host__ __device__ constexpr int w_entries(int mm) { return mm > 1 ? (mm - 1) * mm / 2 : 0; }
-    static __host__ __device__ constexpr int bytes(int mm) { return FIXED + wform::al16((w_entries(mm) + 8) * 8); }
+    // rows of W kept for patterns of at most mm positions grown s at a time: all but the last block
+    // of the last step
+    static __host__ __device__ constexpr int w_rows(int mm, int s) { return mm > 1 ? mm - 1 - ((s - 1) % NB + 1) : 0; }
+    static __host__ __device__ constexpr int bytes(int mm, int s) {
+        return FIXED + wform::al16((wform::tri_w(w_rows(mm, s)) + 8) * 8);
+    }
 };
 
-// Finds the run starting at column c, inserting it when absent; its slot, or -1 when the table
-// is full.  Two lanes looking up one new run at once (two gathered rows) get the same slot:
+// Finds the run starting at column c, inserting it when absent if `add`; its slot, or -1 (when
+// the table is full, or the run is absent and not to be added).  Two lanes looking up one new run at once (two gathered rows) get the same slot:
 // one claim wins, the other returns the slot that now holds its run.
 template <int CAPT>
-__device__ __forceinline__ int bfind(int32_t *hkey, int c) {
+__device__ __forceinline__ int bfind(int32_t *hkey, int c, bool add) {
     constexpr int NBK = CAPT / 4;
     uint32_t b = __umulhi((uint32_t)c * 2654435761u, (uint32_t)NBK);
     for (int probe = 0; probe < NBK;) {
@@ -81,6 +86,7 @@ __device__ __forceinline__ int bfind(int32_t *hkey, int c) {
             ++probe;
             continue;
         }
+        if (!add) return -1;
         const int old = atomicCAS(&hkey[4 * b + empty], kEmpty, c);
         if (old == kEmpty || old == c) return (int)(4 * b) + empty;
     }
@@ -129,8 +135,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
     constexpr int LDV = LY::LDV;
     constexpr int HPG = GS / 32;                   // rows of A a group takes at once
     constexpr int SPL = (CAPT + GS - 1) / GS;      // table slots per lane
+    constexpr int NGR = (NB + HPG - 1) / HPG;      // rounds of gathered rows
     constexpr int NSL = (MMAX / HPG + 3) / 4;      // slot registers (four bytes each)
-    static_assert(MMAX % (4 * HPG) == 0 && NB % HPG == 0, "whole rounds");
+    static_assert(MMAX % (4 * HPG) == 0, "whole rounds");
 
     extern __shared__ __align__(16) unsigned char lds_w[];
     __shared__ int32_t s_row;
@@ -138,7 +145,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
     const int gl = lane & (GS - 1), grp = lane / GS;
     const int hl = lane & 31, half = HPG == 2 ? lane >> 5 : 0;
     const int mmx = kmax > 0 ? 1 + kmax * s : 1;  // largest pattern
-    unsigned char *gbase = lds_w + grp * LY::bytes(mmx);
+    const int wrows = LY::w_rows(mmx, s), gbytes = LY::bytes(mmx, s);
+    unsigned char *gbase = lds_w + grp * gbytes;
     int32_t *hkey = reinterpret_cast<int32_t *>(gbase + LY::O_KEY);
     uint32_t *hinf = reinterpret_cast<uint32_t *>(gbase + LY::O_INF);
     double *hval = reinterpret_cast<double *>(gbase + LY::O_VAL);  // [3][CAPT]
@@ -151,7 +159,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
     double *LV = NR + NB * LDV;                                     // [NB+1][LDV]
     double *NAI = LV + (NB + 1) * LDV;                              // [NB]: a_{u,i}
     const uint64_t gm = wform::group_bits<GS>(grp);
-    const int zslot = LY::w_entries(mmx);  // of the padding after W, zero for the matrix products
+    const int zslot = wform::tri_w(wrows);  // of the padding after W, zero for the matrix products
     if (gl == 0) Wm[zslot] = 0.0;
     const double kNaN = __longlong_as_double(0x7FF8000000000000ll);
 
@@ -214,7 +222,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
             // row i's runs left of the diagonal: the first candidates
             bool bad = ilen > kRunRow;
             if (half == 0 && hl < ilen) {
-                const int slot = bfind<CAPT>(hkey, ci[ibeg + 3 * hl]);
+                const int slot = bfind<CAPT>(hkey, ci[ibeg + 3 * hl], true);
                 if (slot < 0) bad = true;
                 else slr[0] |= (uint32_t)slot;
             }
@@ -364,7 +372,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
                 }
             }
             wsync();
-            // the selected columns into the gradient planes' end (no longer read this step)
+            // the selected columns in the place of the member records (no longer read this step)
             if (act && gl < ns) {
                 sel[gl] = r_js;
                 selb[gl] = r_nb;
@@ -377,6 +385,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
             double yi = 0.0;  // lane j: (W^T l_i)_j, accumulated over the blocks of this step
             int nsd = 0;
             bool first = true;
+            // the last step's rows are looked up but not entered: no product pass follows
+            const bool more = k < kmax;
             const int nsw = GS == 64 ? wu<GS>(ns)
                                      : __builtin_amdgcn_readfirstlane((int)gred<64, OpMax>((double)(act ? ns : 0)));
             for (int nw = 0; nw < nsw; nw += NB) {
@@ -397,10 +407,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
                 // new row v is member mo + v + 1: the half with that parity takes it
                 const int flip = HPG == 2 ? (half ^ ((mo + 1) & 1)) : 0;
                 if (blk) {
-                    int gc[NB / HPG];
-                    double ga[NB / HPG][3];
+                    int gc[NGR];
+                    double ga[NGR][3];
 #pragma unroll
-                    for (int w = 0; w < NB / HPG; ++w) {
+                    for (int w = 0; w < NGR; ++w) {
                         const int v = w * HPG + flip;
                         gc[w] = kEmpty;
 #pragma unroll
@@ -418,16 +428,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
                     }
                     int mylen = 0;  // lane mo + v: runs of new row v left of column i
 #pragma unroll
-                    for (int w = 0; w < NB / HPG; ++w) {
+                    for (int w = 0; w < NGR; ++w) {
                         const int v = w * HPG + flip;
                         const int c0 = gc[w];
                         const bool lo = c0 < i;
                         if (c0 <= i && i < c0 + 3) NAI[v] = c0 == i ? ga[w][0] : (c0 + 1 == i ? ga[w][1] : ga[w][2]);
                         int slot = 0;
                         if (lo) {
-                            slot = bfind<CAPT>(hkey, c0);
+                            slot = bfind<CAPT>(hkey, c0, more);
                             if (slot < 0) {
-                                bad = true;
+                                bad = bad || more;
                             } else {
                                 const uint32_t f = hinf[slot];
 #pragma unroll
@@ -467,7 +477,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
                 const bool go = blk && act;
                 // a_{u,i} of the new positions
                 if (go && gl >= mo && gl < mo + nbk) r_ai = NAI[gl - mo];
-                wform::extend_w<GS, MMAX, NB, LDV>(go, mo, mwb, nbk, gl, first, LY::bytes(mmx) / 8, zslot, s >= 4, Wm,
+                wform::extend_w<GS, MMAX, NB, LDV>(go, mo, mwb, nbk, gl, first, gbytes / 8, zslot, wrows, s >= 4, Wm,
                                                    NR, LV, r_ai, r_li, yi, psi, spd, status, act);
                 if (blk) {
                     m_o += nbk;

@@ -17,7 +17,7 @@
 //
 // Rows per wavefront: GS lanes own one row (lane t = pattern position t), 64 / GS rows share a
 // wavefront, each group with its own LDS table, factor and vectors; reductions stay inside a
-// group (DPP quad and mirror moves, a swizzle across 16 lanes, readlane across 32).  Control
+// group (DPP quad and mirror moves, a row swap across 16 lanes, readlane across 32).  Control
 // flow is uniform inside a group; groups of a wavefront run their growth steps together.
 //
 // Per growth step of a row:
@@ -104,12 +104,18 @@ __device__ __forceinline__ double dmov(double v) {
 }
 template <int CTRL>
 __device__ __forceinline__ uint32_t dmov(uint32_t v) { return (uint32_t)dmov<CTRL>((int)v); }
-// lane ^ 16 inside each half of the wavefront (ds_swizzle bit mode: and 0x1F, xor 0x10)
-__device__ __forceinline__ int xor16(int v) { return __builtin_amdgcn_ds_swizzle(v, 0x401F); }
-__device__ __forceinline__ uint32_t xor16(uint32_t v) { return (uint32_t)xor16((int)v); }
-__device__ __forceinline__ double xor16(double v) {
-    const int lo = xor16(__double2loint(v)), hi = xor16(__double2hiint(v));
-    return __hiloint2double(hi, lo);
+// v of this lane's row of 16 lanes and of its neighbour (rows 0/1 and 2/3), combined: both rows
+// get the same pair (a swap of rows between two copies of v; no LDS-pipe round trip as a swizzle)
+template <class Op>
+__device__ __forceinline__ double pair16(double v) {
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)__double2loint(v), (uint32_t)__double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)__double2hiint(v), (uint32_t)__double2hiint(v), false, false);
+    return Op::f(__hiloint2double((int)hi[0], (int)lo[0]), __hiloint2double((int)hi[1], (int)lo[1]));
+}
+template <class Op>
+__device__ __forceinline__ uint32_t pair16(uint32_t v) {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return Op::f(r[0], r[1]);
 }
 __device__ __forceinline__ int rlane(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
 __device__ __forceinline__ uint32_t rlane(uint32_t v, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); }
@@ -137,7 +143,7 @@ __device__ __forceinline__ T gred(T v) {
     v = Op::f(v, dmov<0x4E>(v));   // quad_perm [2,3,0,1]: lane ^ 2
     v = Op::f(v, dmov<0x141>(v));  // row_half_mirror: quads of one 8-lane half
     if constexpr (GS >= 16) v = Op::f(v, dmov<0x140>(v));  // row_mirror: the two halves of a row
-    if constexpr (GS >= 32) v = Op::f(v, xor16(v));         // rows 0/1 and 2/3
+    if constexpr (GS >= 32) v = pair16<Op>(v);              // rows 0/1 and 2/3
     if constexpr (GS == 64) v = Op::f(rlane(v, 0), rlane(v, 32));
     return v;
 }
@@ -428,13 +434,14 @@ __device__ __forceinline__ void w_products(const double *Wb, const double *NRb, 
 
 // Step 4 of a block of nbk <= NB new rows (positions mo .. mo + nbk - 1, their entries at the
 // old and new positions in NR, a_{u,i} in r_ai): the rows of W, l_i's new entries (r_li), psi and
-// yi = W^T l_i of this step so far.  go: this group takes part; mwb: the most old positions of a
+// yi = W^T l_i of this step so far.  Rows of W from position wrows on are not stored (no later
+// block reads them).  go: this group takes part; mwb: the most old positions of a
 // group of the wavefront; first: the step's first block (l_i's old entries are added to yi then);
 // gst: doubles from one group's LDS to the next; zslot: an entry of W that holds zero; sep: steps
 // of four or more new rows.  NR and LV have rows of LDV entries.
 template <int GS, int MMAX, int NB, int LDV>
 __device__ __forceinline__ void extend_w(bool go, int mo, int mwb, int nbk, int gl, bool first, int gst, int zslot,
-                                         bool sep, double *Wm, const double *NR, double *LV, double r_ai, double &r_li,
+                                         int wrows, bool sep, double *Wm, const double *NR, double *LV, double r_ai, double &r_li,
                                          double &yi, double &psi, bool &spd, int8_t &status, bool &act) {
     double la[NB], yb[NB];
 #pragma unroll
@@ -528,50 +535,96 @@ __device__ __forceinline__ void extend_w(bool go, int mo, int mwb, int nbk, int 
     double wn[NB];
 #pragma unroll
     for (int v = 0; v < NB; ++v) wn[v] = 0.0;
-    if (wu<GS>(go)) {
+    if constexpr (GS >= 32) {
+        // without branches on the rows of the block, so that their reductions run together (150^3,
+        // blocks of three: the setup kernel 617 -> 594 ms)
+        if (wu<GS>(go)) {
+            double sq[NB], av_l[NB], dd[NB];
+            bool ok = true;
 #pragma unroll
-        for (int v = 0; v < NB; ++v) {
-            if (v < nbk && wu<GS>(spd)) {
+            for (int v = 0; v < NB; ++v) {
+                sq[v] = gred<GS, OpSum>(gl < mo ? la[v] * la[v] : 0.0);
+                av_l[v] = gl < MMAX ? NR[v * LDV + (gl < MMAX ? gl : 0)] : 0.0;
+                dd[v] = NR[v * LDV + mo + v];
+            }
+#pragma unroll
+            for (int v = 0; v < NB; ++v) {
+                const bool in = v < nbk;
                 const int p = mo + v;
-                const double sq = gred<GS, OpSum>(gl < mo ? la[v] * la[v] : 0.0);
-                double d2 = NR[v * LDV + p] - sq;
-                const double av_l = gl < MMAX ? NR[v * LDV + (gl < MMAX ? gl : 0)] : 0.0;
-                double cp[NB];
+                double d2 = dd[v] - sq[v], y = yb[v];
+#pragma unroll
+                for (int w = 0; w < v; ++w) {
+                    const double cp = gred<GS, OpSum>(wn[w] * av_l[v]);
+                    d2 = d2 - cp * cp;
+                    y = fma(wn[w], cp, y);
+                }
+                ok = ok && (!in || (d2 > 0.0 && isfinite(d2)));
+                const double dinv = rsqrt_nr(d2);
+                const double r = gl < p ? -(y * dinv) : (gl == p ? dinv : 0.0);
+                wn[v] = in ? r : 0.0;
+                if (in && gl <= p && p < wrows) Wm[tri_w(p) + gl] = wn[v];
+            }
+            if (wu<GS>(ok)) {
+                // l_i at the new positions and psi
 #pragma unroll
                 for (int w = 0; w < NB; ++w) {
-                    cp[w] = 0.0;
-                    if (w < v) {
-                        cp[w] = gred<GS, OpSum>(wn[w] * av_l);
-                        d2 = d2 - cp[w] * cp[w];
-                    }
-                }
-                if (!(d2 > 0.0) || !isfinite(d2)) {
-                    spd = false;
-                } else {
-                    const double dinv = rsqrt_nr(d2);
-                    double y = yb[v];
-#pragma unroll
-                    for (int w = 0; w < NB; ++w)
-                        if (w < v) y = fma(wn[w], cp[w], y);
-                    wn[v] = gl < p ? -(y * dinv) : (gl == p ? dinv : 0.0);
-                    if (gl <= p) Wm[tri_w(p) + gl] = wn[v];
-                }
-            }
-        }
-        if (wu<GS>(spd)) {
-            // l_i at the new positions and psi
-#pragma unroll
-            for (int w = 0; w < NB; ++w) {
-                if (w < nbk) {
                     const double li = gred<GS, OpSum>(wn[w] * r_ai);
-                    if (gl == mo + w) r_li = li;
+                    if (w < nbk && gl == mo + w) r_li = li;
                     psi = psi - li * li;
                     yi = fma(wn[w], li, yi);
                 }
+            } else {
+                spd = false;
+                status = ROW_NOT_SPD;
+                act = false;
             }
-        } else {
-            status = ROW_NOT_SPD;
-            act = false;
+        }
+    } else {
+        if (wu<GS>(go)) {
+#pragma unroll
+            for (int v = 0; v < NB; ++v) {
+                if (v < nbk && wu<GS>(spd)) {
+                    const int p = mo + v;
+                    const double sq = gred<GS, OpSum>(gl < mo ? la[v] * la[v] : 0.0);
+                    double d2 = NR[v * LDV + p] - sq;
+                    const double av_l = gl < MMAX ? NR[v * LDV + (gl < MMAX ? gl : 0)] : 0.0;
+                    double cp[NB];
+#pragma unroll
+                    for (int w = 0; w < NB; ++w) {
+                        cp[w] = 0.0;
+                        if (w < v) {
+                            cp[w] = gred<GS, OpSum>(wn[w] * av_l);
+                            d2 = d2 - cp[w] * cp[w];
+                        }
+                    }
+                    if (!(d2 > 0.0) || !isfinite(d2)) {
+                        spd = false;
+                    } else {
+                        const double dinv = rsqrt_nr(d2);
+                        double y = yb[v];
+#pragma unroll
+                        for (int w = 0; w < NB; ++w)
+                            if (w < v) y = fma(wn[w], cp[w], y);
+                        wn[v] = gl < p ? -(y * dinv) : (gl == p ? dinv : 0.0);
+                        if (gl <= p && p < wrows) Wm[tri_w(p) + gl] = wn[v];
+                    }
+                }
+            }
+            if (wu<GS>(spd)) {
+                // l_i at the new positions and psi
+#pragma unroll
+                for (int w = 0; w < NB; ++w) {
+                    if (w < nbk) {
+                        const double li = gred<GS, OpSum>(wn[w] * r_ai);
+                        if (gl == mo + w) r_li = li;
+                        psi = psi - li * li;
+                        yi = fma(wn[w], li, yi);
+                    }
+                }
+            } else {
+                status = ROW_NOT_SPD;
+                act = false;
+            }
         }
     }
 }
@@ -996,7 +1049,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(GS == 8 || (
                 // a_{u,i} of the new positions
                 if (go && gl >= mo && gl < mo + nbk) r_ai = NAI[gl - mo];
 
-                extend_w<GS, MMAX, NB, LDV>(go, mo, mwb, nbk, gl, first, LY::bytes(mmx) / 8, zslot, s >= 4, Wm, NR, LV, r_ai, r_li, yi, psi, spd, status, act);
+                extend_w<GS, MMAX, NB, LDV>(go, mo, mwb, nbk, gl, first, LY::bytes(mmx) / 8, zslot, mmx, s >= 4, Wm, NR, LV, r_ai, r_li, yi, psi, spd, status, act);
                 if (blk) {
                     m_o += nbk;
                     nsd += nbk;

@@ -414,7 +414,7 @@ __global__ void k_block_check(int n, const int32_t *__restrict__ rp, const int32
 RowsKernel rows_kernel(int mmax_t, int cap, bool rsl, bool f32);
 RowsKernel rows_kernel_w(int mmax, int maxlen, int cap, int lanes, bool g32, int *gs_out, size_t *lds_out);
 RowsKernel rows_kernel_w_large(int mmax, int cap, bool g32, size_t *lds_out);
-RowsKernel rows_kernel_b(int mmax, int maxlen, int *gs_out, size_t *lds_out);
+RowsKernel rows_kernel_b(int mmax, int s, int maxlen, int *gs_out, size_t *lds_out);
 
 // Launch of a per-row kernel over `nlist` rows.  Inverse-factor form: wdyn > 0 is its dynamic
 // LDS per block and rpw its rows per wavefront; the Cholesky form sizes its LDS from the
@@ -694,7 +694,7 @@ static int setup_core(const afsai_csr *A, const afsai_params *p, int nsys, const
         // groups of 32 and 64 lanes take tables from 128 slots
         if (wcap < 128 && (lanes >= 32 || mmax > 16 || maxlen > 64)) wcap = 128;
         int gs = 64;
-        if (runs && !so.noruns) k1 = rows_kernel_b(mmax, maxlen, &gs, &wdyn);
+        if (runs && !so.noruns) k1 = rows_kernel_b(mmax, p->s, maxlen, &gs, &wdyn);
         if (!k1) k1 = rows_kernel_w(mmax, maxlen, wcap, lanes, (p->flags & AFSAI_GRAD_F32) != 0, &gs, &wdyn);
         if (k1) {
             wrpw = 64 / gs;
