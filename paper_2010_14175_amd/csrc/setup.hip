@@ -524,9 +524,9 @@ static int build_transpose(afsai_precond_s *P, const DeviceInfo &di, hipStream_t
 }
 
 static int alloc_workspace(afsai_precond_s *P, const DeviceInfo &di) {
-    // PCG: r, r', z, p, p', q, t (n each) + partial sums + scalars (the solver's layout)
-    const size_t np = (size_t)2 * di.num_cus * 16 + 64;
-    P->work_elems = (size_t)7 * P->n + np + 16;
+    // PCG: r, r', z, p, p', q, t (n each) + three arrays of partial sums + scalars (the solver's
+    // layout for one system)
+    P->work_elems = (size_t)7 * P->n + (size_t)3 * di.num_cus * 16 + 64;
     P->work = (double *)pool_alloc(P->work_elems * sizeof(double));
     if (!P->work) AFSAI_FAIL(AFSAI_ERR_NO_MEMORY, "out of device memory for the solver workspace");
     return AFSAI_OK;

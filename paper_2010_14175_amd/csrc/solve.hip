@@ -14,13 +14,16 @@
 // system's iterates do not depend on its batch-mates (bit for bit).
 //
 // PCG: all scalars (rho, alpha, beta, ||r||) live on the device.  Dot products are fused into
-// the kernel that produces one of their operands, which stores one partial sum per block; a
-// one-block kernel then adds the partials in block order (results do not depend on
-// scheduling) and updates the scalars.  (A last-block-done reduction inside the producing
-// kernel needs a device-scope release per block, which on this 8-XCD part writes back the
-// L2 and cost more than the extra launch.)  A device flag ends the iteration: kernels that
-// see it return at once, so the host enqueues chunks of iterations and reads the flag once
-// per chunk, one chunk behind.
+// the kernel that produces one of their operands, which stores one partial sum per block.  With
+// the fused products (small systems) every block of the kernel that needs the sum adds the
+// partials itself, in block order (results do not depend on scheduling), and takes the scalar
+// step in registers: three launches an iteration instead of six, the 20^3 solve 1.03 -> 0.82 ms.
+// Larger systems have thousands of partials, added by one block per system in the same order.
+// The scalars are kept in two buffers used in turn: a kernel that advances them reads one and
+// its first block writes the other.  (A last-block-done reduction inside the producing kernel needs a device-scope
+// release per block, which on this 8-XCD part writes back the L2 and cost more than the extra
+// launch.)  A device flag ends the iteration: kernels that see it return at once, so the host
+// enqueues chunks of iterations and reads the flag once per chunk, one chunk behind.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -33,16 +36,17 @@ namespace afsai {
 
 constexpr int kThreads = 256;
 constexpr int kFusedMaxRows = 200000;  // automatic PCG form: fused products below this size
+constexpr int64_t kGateEntries = 1 << 26;  // factors whose products look at r.r before they start
 // resumable solver: iterations of the first chunk, least GPU time of a chunk and its share of
 // the GPU time so far
 constexpr int kFirstChunk = 4;
 constexpr double kMinChunkUs = 100.0;
 constexpr double kChunkShare = 0.125;
 
-enum : int { FIN_NONE = 0, FIN_ALPHA = 1, FIN_BETA = 2, FIN_RHO0 = 3, FIN_INIT = 4, FIN_UPDATE = 5, FIN_RESID = 6 };
+enum : int { FIN_NONE = 0, FIN_RHO0 = 3, FIN_INIT = 4, FIN_RESID = 6 };
 enum : int { DONE_NO = 0, DONE_CONVERGED = 1, DONE_NOT_SPD = 2, DONE_MAXIT = 3, DONE_ZERO_RHS = 4 };
 
-struct PcgScalars {  // 80 bytes: copied as 10 double words
+struct PcgScalars {  // 88 bytes: copied as 11 double words
     double rho;      // r.z of the current iterate
     double alpha;
     double beta;
@@ -55,8 +59,10 @@ struct PcgScalars {  // 80 bytes: copied as 10 double words
     int32_t done;    // DONE_*
     int32_t plain;   // 1: M = I (z = r)
     double resid;    // ||b - A x||^2 of the final check
+    int32_t fresh;   // 1: the scalar step after the last iteration has been taken
+    int32_t pad;
 };
-static_assert(sizeof(PcgScalars) == 80, "PcgScalars is copied as 10 double words");
+static_assert(sizeof(PcgScalars) == 88, "PcgScalars is copied as 11 double words");
 
 // Systems of a batch (device arrays; nullptr: one system covering everything)
 struct Systems {
@@ -131,61 +137,124 @@ __device__ __forceinline__ void store_partials(double *partials, int slots, cons
         for (int k = 0; k < slots; ++k) partials[(size_t)k * gridDim.x + gb] = mine[k];
 }
 
-// One block per system: sums the system's partials of the previous launch (nblocks blocks in
-// all) in block order and updates its scalars.
-__global__ __launch_bounds__(kThreads) void k_finalize(const double *__restrict__ partials, int nblocks, Map mp,
-                                                       int fin, PcgScalars *scs) {
+// The partial sums that a launch of nblocks blocks stored (nblocks = 0: sums, one per system)
+struct Parts {
+    const double *p = nullptr;
+    Map mp;
+    int nblocks = 0;
+};
+
+// The sums of system k's partials of two launches, each in block order (every thread adds a
+// contiguous run, then the runs are added in thread order); every thread of the block gets
+// them.  b without partials: its sum is 0.
+__device__ __forceinline__ void parts_sum(const Parts &a, const Parts &b, int k, double *sh /* 2 * kThreads / 64 */,
+                                          double &sa, double &sb) {
+    if (a.nblocks == 0) {  // added before
+        sa = a.p[k];
+        sb = b.p ? b.p[k] : 0.0;
+        return;
+    }
+    double v[2] = {0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const Parts &pt = q ? b : a;
+        if (pt.p) {
+            const int b0 = pt.mp.blk_sys ? pt.mp.sys_b0[k] : 0;
+            const int np = pt.mp.blk_sys ? pt.mp.sys_nb[k] : pt.nblocks;
+            const int per = (np + kThreads - 1) / kThreads;
+            const int lo = threadIdx.x * per, hi = min(np, lo + per);
+            for (int j = lo; j < hi; ++j) v[q] += pt.p[b0 + j];
+        }
+    }
+    const int w = threadIdx.x >> 6;
+    v[0] = wave_sum(v[0]);
+    if (b.p) v[1] = wave_sum(v[1]);
+    if ((threadIdx.x & 63) == 0) {
+        sh[w] = v[0];
+        sh[kThreads / 64 + w] = v[1];
+    }
+    __syncthreads();
+    sa = sb = 0.0;
+#pragma unroll
+    for (int j = 0; j < kThreads / 64; ++j) {
+        sa += sh[j];
+        sb += sh[kThreads / 64 + j];
+    }
+    __syncthreads();
+}
+
+// The same, where few kernels or many blocks need a sum: one block per system stores the
+// system's sums of one or two launches
+__global__ __launch_bounds__(kThreads) void k_reduce(Parts a, Parts b, double *oa, double *ob, const PcgScalars *scs) {
+    const int k = blockIdx.x;
+    if (scs[k].done) return;
+    __shared__ double sh[2 * kThreads / 64];
+    double sa, sb;
+    parts_sum(a, b, k, sh, sa, sb);
+    if (threadIdx.x == 0) {
+        oa[k] = sa;
+        if (b.p) ob[k] = sb;
+    }
+}
+
+// The scalar step after an iteration: rr = ||r||^2, rz = r.z (unused with M = I); bad: p.Ap <= 0
+__device__ __forceinline__ void advance(PcgScalars &s, double rr, double rz, int bad) {
+    s.fresh = 1;
+    if (bad) {
+        s.done = DONE_NOT_SPD;
+        return;
+    }
+    s.rr = rr;
+    s.it += 1;
+    if (sqrt(rr) <= s.tol) {
+        s.done = DONE_CONVERGED;
+    } else if (s.it >= s.maxit) {
+        s.done = DONE_MAXIT;
+    } else {
+        const double z = s.plain ? rr : rz;
+        s.beta = z / s.rho;
+        s.rho = z;
+    }
+}
+
+// alpha = rho / p.q of the system, or false when p.q <= 0: the system's block 0 then marks it
+__device__ __forceinline__ bool step_alpha(const PcgScalars &s, const Parts &pq, int k, int lb, int32_t *bad, double *sh,
+                                           double &alpha) {
+    double v, u;
+    parts_sum(pq, Parts(), k, sh, v, u);
+    if (!(v > 0.0) || !isfinite(v)) {
+        if (lb == 0 && threadIdx.x == 0) bad[k] = 1;
+        return false;
+    }
+    alpha = s.rho / v;
+    return true;
+}
+
+// One block per system: the sums of the start and of the final check (partials of the previous
+// launch; FIN_INIT has two of them, b.b and then r.r).
+__global__ __launch_bounds__(kThreads) void k_finalize(Parts pa, Parts pb, int fin, PcgScalars *scs) {
     const int k = blockIdx.x;
     PcgScalars *sc = scs + k;
-    if ((fin == FIN_ALPHA || fin == FIN_BETA || fin == FIN_UPDATE || fin == FIN_RHO0) && sc->done) return;
-    const int b0 = mp.blk_sys ? mp.sys_b0[k] : 0;
-    const int nparts = mp.blk_sys ? mp.sys_nb[k] : nblocks;
-    __shared__ double sh[kThreads / 64];
-    const int slots = (fin == FIN_INIT) ? 2 : 1;
-    double tot[2] = {0.0, 0.0};
-    const int per = (nparts + kThreads - 1) / kThreads;
-    const int lo = threadIdx.x * per, hi = min(nparts, lo + per);
-    for (int sl = 0; sl < slots; ++sl) {
-        double v = 0.0;
-        for (int j = lo; j < hi; ++j) v += partials[(size_t)sl * nblocks + b0 + j];
-        tot[sl] = block_sum(v, sh);
-    }
+    if (fin == FIN_RHO0 && sc->done) return;
+    __shared__ double sh[2 * kThreads / 64];
+    double v, rr;
+    parts_sum(pa, pb, k, sh, v, rr);
     if (threadIdx.x != 0) return;
-    const double v = tot[0];
     switch (fin) {
-        case FIN_ALPHA:  // v = p.q
-            if (!(v > 0.0) || !isfinite(v)) sc->done = DONE_NOT_SPD;
-            else sc->alpha = sc->rho / v;
-            break;
-        case FIN_BETA:  // v = r.z
-            sc->beta = v / sc->rho;
-            sc->rho = v;
-            break;
         case FIN_RHO0:
             sc->rho = v;
             break;
-        case FIN_INIT: {  // v = b.b, tot[1] = r.r
-            const double bb = v, rr = tot[1];
-            sc->bb = bb;
+        case FIN_INIT: {  // v = b.b, rr = r.r
+            sc->bb = v;
             sc->rr = rr;
-            sc->tol = sc->rtol * sqrt(bb);
+            sc->tol = sc->rtol * sqrt(v);
             sc->it = 0;
-            if (bb == 0.0) sc->done = DONE_ZERO_RHS;
+            if (v == 0.0) sc->done = DONE_ZERO_RHS;
             else if (sqrt(rr) <= sc->tol) sc->done = DONE_CONVERGED;
             else if (sc->maxit == 0) sc->done = DONE_MAXIT;
             if (sc->plain) sc->rho = rr;
             break;
         }
-        case FIN_UPDATE:  // v = r.r after the update
-            sc->rr = v;
-            sc->it += 1;
-            if (sqrt(v) <= sc->tol) sc->done = DONE_CONVERGED;
-            else if (sc->it >= sc->maxit) sc->done = DONE_MAXIT;
-            else if (sc->plain) {
-                sc->beta = v / sc->rho;
-                sc->rho = v;
-            }
-            break;
         case FIN_RESID:
             sc->resid = v;
             break;
@@ -360,10 +429,13 @@ __global__ __launch_bounds__(kThreads) void k_sell_spmv(int n, int nslices, cons
                                                          const uint32_t *__restrict__ tsptr,
                                                          const int32_t *__restrict__ tcol,
                                                          const VT *__restrict__ tval,
-                                                         const int32_t *__restrict__ toff) {
+                                                         const int32_t *__restrict__ toff,
+                                                         const double *__restrict__ rr) {
     const Job jb = block_job(mp, nxcd);
     if (scs && scs[jb.k].done) return;
     __shared__ double sh[kThreads / 64];
+    // converged by this iteration's r.r (one sum per system): the product is not needed
+    if (rr && sqrt(rr[jb.k]) <= scs[jb.k].tol) return;
     const int sb = sy.slice0 ? sy.slice0[jb.k] : 0;
     const int sn = sy.slice0 ? sy.slice0[jb.k + 1] - sb : nslices;
     static_assert(kWin == kThreads / 64, "a window holds one slice per wavefront of a block");
@@ -374,11 +446,13 @@ __global__ __launch_bounds__(kThreads) void k_sell_spmv(int n, int nslices, cons
         static_assert(kWin * kSlice % kThreads == 0, "the wavefronts of a block take a window's slices in turn");
         constexpr int UO = U >= 8 ? 16 : U;
         __shared__ double sy_win[kWin * kSlice];
-        const int wa = wofs[sb], wb = wofs[sb + sn];
+        // (slices of one system: window w holds slices kWin w to kWin w + kWin - 1, no look-ups)
+        const bool one = !srow0;
+        const int wa = one ? 0 : wofs[sb], wb = one ? (sn + kWin - 1) / kWin : wofs[sb + sn];
         int w0, w1, wstep;
         window_walk(wb - wa, jb.lb, jb.nb, nxcd, w0, w1, wstep);
         for (int wi = wa + w0; wi < wa + w1; wi += wstep) {
-            const int ws = wsl[wi], we = wsl[wi + 1];
+            const int ws = one ? wi * kWin : wsl[wi], we = one ? min(ws + kWin, sn) : wsl[wi + 1];
             int wr0, u0;
             sell_slice_rows(srow0, n, ws, wr0, u0);
             for (int sl = ws + wv; sl < we; sl += kThreads / 64) {
@@ -557,8 +631,10 @@ __global__ __launch_bounds__(kThreads) void k_sell_spmv_runs(int n, const uint32
 // kernel would use, so the result is identical to update-then-multiply; the owner lane of
 // each row also stores the updated entry.
 //   FUSE_AP:  p_new = z + beta p_old (p_new = z on the first iteration); q = A p_new;
-//             partial sums of p_new.q
+//             partial sums of p_new.q; takes the scalar step of the iteration before (pa: its
+//             r.r, pb: its r.z) from s_in to s_out
 //   FUSE_GR:  r_new = r_old - alpha q; x += alpha p_new; t = G r_new; partial sums of r_new.r_new
+//             (pa: p.q)
 enum : int { FUSE_AP = 1, FUSE_GR = 2 };
 
 template <int U, typename VT, int MODE>
@@ -573,14 +649,26 @@ __global__ __launch_bounds__(kThreads) void k_sell_fused(int n, int nslices, con
                                                           const double *__restrict__ pn,   // - | p_new
                                                           double *__restrict__ y,          // q | t
                                                           double *__restrict__ partials,
-                                                          const PcgScalars *scs, int first, Map mp, Systems sy,
+                                                          const PcgScalars *s_in, PcgScalars *s_out, int32_t *bad,
+                                                          Parts pa, Parts pb, int first, Map mp, Systems sy,
                                                           int nxcd) {
     const Job jb = block_job(mp, nxcd);
-    const PcgScalars *sc = scs + jb.k;
-    if (sc->done) return;
-    __shared__ double sh[kThreads / 64];
-    const double alpha = sc->alpha;
-    const double coef = (MODE == FUSE_AP) ? sc->beta : -alpha;
+    __shared__ double sh[2 * kThreads / 64];
+    PcgScalars st = s_in[jb.k];
+    double alpha = 0.0;
+    if (MODE == FUSE_AP) {
+        if (!st.done && !st.fresh) {
+            double rr, rz;
+            parts_sum(pa, pb, jb.k, sh, rr, rz);
+            advance(st, rr, rz, bad[jb.k]);
+        }
+        if (!st.done) st.fresh = 0;
+        if (jb.lb == 0 && threadIdx.x == 0) s_out[jb.k] = st;
+        if (st.done) return;
+    } else {
+        if (st.done || !step_alpha(st, pa, jb.k, jb.lb, bad, sh, alpha)) return;
+    }
+    const double coef = (MODE == FUSE_AP) ? st.beta : -alpha;
     const int sb = sy.slice0 ? sy.slice0[jb.k] : 0;
     const int sn = sy.slice0 ? sy.slice0[jb.k + 1] - sb : nslices;
     const int wv = wave_index(), lane = threadIdx.x & 63;
@@ -683,18 +771,19 @@ __global__ __launch_bounds__(kThreads) void k_init_residual(int n, const double 
     store_partials(partials, 2, mine, jb.gb);
 }
 
-// x += alpha p ; r -= alpha q ; ||r||^2 ; convergence test; (plain CG) beta = rr'/rr
+// x += alpha p ; r -= alpha q ; partials of ||r||^2  (pq: the partials of p.q)
 __global__ __launch_bounds__(kThreads) void k_update_xr(int n, double *__restrict__ x,
                                                          double *__restrict__ r,
                                                          const double *__restrict__ p,
                                                          const double *__restrict__ q,
                                                          double *__restrict__ partials,
-                                                         PcgScalars *scs, Map mp, Systems sy, int nxcd) {
+                                                         const PcgScalars *scs, int32_t *bad, Parts pq, Map mp,
+                                                         Systems sy, int nxcd) {
     const Job jb = block_job(mp, nxcd);
-    const PcgScalars *sc = scs + jb.k;
-    if (sc->done) return;
-    __shared__ double sh[kThreads / 64];
-    const double alpha = sc->alpha;
+    const PcgScalars st = scs[jb.k];
+    __shared__ double sh[2 * kThreads / 64];
+    double alpha;
+    if (st.done || !step_alpha(st, pq, jb.k, jb.lb, bad, sh, alpha)) return;
     int a0, a1, i0, i1;
     sys_rows(sy, n, jb.k, a0, a1);
     block_range(a0, a1 - a0, jb.lb, jb.nb, i0, i1);
@@ -709,15 +798,25 @@ __global__ __launch_bounds__(kThreads) void k_update_xr(int n, double *__restric
     store_partials(partials, 1, &bs, jb.gb);
 }
 
-// p = z + beta p   (first = 1: p = z)
+// The scalar step of the iteration (rr, rz: its partials) from s_in to s_out, then p = z + beta p
+// (first = 1: no step, p = z)
 __global__ __launch_bounds__(kThreads) void k_update_p(int n, double *__restrict__ p,
                                                         const double *__restrict__ z,
-                                                        const PcgScalars *scs, int first, Map mp, Systems sy,
-                                                        int nxcd) {
+                                                        const PcgScalars *s_in, PcgScalars *s_out, const int32_t *bad,
+                                                        Parts rr, Parts rz, int first, Map mp, Systems sy, int nxcd) {
     const Job jb = block_job(mp, nxcd);
-    const PcgScalars *sc = scs + jb.k;
-    if (sc->done) return;
-    const double beta = first ? 0.0 : sc->beta;
+    __shared__ double sh[2 * kThreads / 64];
+    PcgScalars st = s_in[jb.k];
+    if (!first) {
+        if (!st.done) {
+            double vr, vz;
+            parts_sum(rr, rz, jb.k, sh, vr, vz);
+            advance(st, vr, vz, bad[jb.k]);
+        }
+        if (jb.lb == 0 && threadIdx.x == 0) s_out[jb.k] = st;
+    }
+    if (st.done) return;
+    const double beta = st.beta;
     int a0, a1, i0, i1;
     sys_rows(sy, n, jb.k, a0, a1);
     block_range(a0, a1 - a0, jb.lb, jb.nb, i0, i1);
@@ -738,22 +837,33 @@ __global__ __launch_bounds__(kThreads) void k_zero_rhs(int n, double *__restrict
     for (int i = i0 + threadIdx.x; i < i1; i += kThreads) x[i] = 0.0;
 }
 
-// Copies the scalars of every system into pinned host memory (mapped), where the host reads
-// them once the chunk's event has completed; a kernel is cheaper here than a copy engine
-// transfer of a few hundred bytes.
-__global__ void k_publish(const PcgScalars *__restrict__ sc, int nwords, PcgScalars *__restrict__ host) {
-    const double *src = reinterpret_cast<const double *>(sc);
-    double *dst = reinterpret_cast<double *>(host);
-    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < nwords; k += gridDim.x * blockDim.x) dst[k] = src[k];
+// One block per system: takes the scalar step of the last iteration where no kernel has yet (the
+// fused form takes it at the start of the next one), then copies the scalars into pinned
+// host memory (mapped), where the host reads them once the chunk's event has completed; a
+// kernel is cheaper here than a copy engine transfer of a few hundred bytes.
+__global__ __launch_bounds__(kThreads) void k_publish(PcgScalars *scs, const int32_t *bad, Parts rr, Parts rz,
+                                                      PcgScalars *__restrict__ host) {
+    __shared__ double sh[2 * kThreads / 64];
+    const int k = blockIdx.x;
+    PcgScalars st = scs[k];
+    if (!st.done && !st.fresh) {
+        double vr, vz;
+        parts_sum(rr, rz, k, sh, vr, vz);
+        advance(st, vr, vz, bad[k]);
+        if (threadIdx.x == 0) scs[k] = st;
+    }
+    if (threadIdx.x == 0) host[k] = st;
 }
 
-__global__ void k_set_scalars(PcgScalars *scs, int nsys, double rtol, int maxit, int plain) {
+__global__ void k_set_scalars(PcgScalars *scs, int32_t *bad, int nsys, double rtol, int maxit, int plain) {
     for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < nsys; k += gridDim.x * blockDim.x) {
         PcgScalars s{};
         s.rtol = rtol;
         s.maxit = maxit;
         s.plain = plain;
+        s.fresh = 1;
         scs[k] = s;
+        bad[k] = 0;
     }
 }
 
@@ -858,9 +968,16 @@ static void launch_spmv_v(const Csr &A, int gs, int un, const double *x, double 
     }
 }
 
-// y = A x, CSR (one system; optionally fused dot y.w finalised into sc)
+// blocks of the CSR product
+static int spmv_blocks(const Csr &A, const DeviceInfo &di) {
+    int gs, un;
+    spmv_shape(A.n ? (double)A.nnz / A.n : 0.0, &gs, &un);
+    return blocks_for_rows(A.n, gs, di);
+}
+
+// y = A x, CSR (one system; optionally fused dot y.w: one partial sum per block)
 static void spmv(const char *name, const Csr &A, const double *x, double *y, const double *w,
-                 double *partials, PcgScalars *sc, int fin, const DeviceInfo &di, hipStream_t s) {
+                 double *partials, PcgScalars *sc, const DeviceInfo &di, hipStream_t s) {
     const double avg = A.n ? (double)A.nnz / A.n : 0.0;
     int gs, un;
     spmv_shape(avg, &gs, &un);
@@ -872,7 +989,6 @@ static void spmv(const char *name, const Csr &A, const double *x, double *y, con
         else
             launch_spmv_v<double>(A, gs, un, x, y, w, partials, sc, nb, di.num_xcds, s);
     }
-    if (w) hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kThreads), 0, s, partials, nb, Map(), fin, sc);
 }
 
 // Block maps of a batch for the three launch shapes (SELL products, vector kernels), held on
@@ -953,7 +1069,7 @@ static int make_batch_maps(int n, int nsys, const int32_t *row0, const DeviceInf
 template <int U, typename VT>
 static void launch_sell_t(const Sell &S, const double *x, double *y, const double *w, double *partials,
                           PcgScalars *scs, const Map &mp, const Systems &sy, int nb, int nxcd, hipStream_t s,
-                          bool fused) {
+                          bool fused, const double *rr) {
     const Sell *T = fused ? S.tail : nullptr;
     const uint32_t *tsp = T ? T->sptr : nullptr;
     const int32_t *tcl = T ? T->col : nullptr;
@@ -974,32 +1090,32 @@ static void launch_sell_t(const Sell &S, const double *x, double *y, const doubl
         if (w)
             hipLaunchKernelGGL((k_sell_spmv<U, VT, true, true>), dim3(nb), dim3(kThreads), 0, s, S.n, S.nslices,
                                S.sptr, S.srow0, S.perm, S.rowmap, S.init, S.col, (const VT *)S.val, x, y, w, partials,
-                               scs, mp, sy, nxcd, S.lens, S.wsl, S.wofs, tsp, tcl, tvl, tof);
+                               scs, mp, sy, nxcd, S.lens, S.wsl, S.wofs, tsp, tcl, tvl, tof, rr);
         else
             hipLaunchKernelGGL((k_sell_spmv<U, VT, false, true>), dim3(nb), dim3(kThreads), 0, s, S.n, S.nslices,
                                S.sptr, S.srow0, S.perm, S.rowmap, S.init, S.col, (const VT *)S.val, x, y, w, partials,
-                               scs, mp, sy, nxcd, S.lens, S.wsl, S.wofs, tsp, tcl, tvl, tof);
+                               scs, mp, sy, nxcd, S.lens, S.wsl, S.wofs, tsp, tcl, tvl, tof, rr);
         return;
     }
     if (w)
         hipLaunchKernelGGL((k_sell_spmv<U, VT, true>), dim3(nb), dim3(kThreads), 0, s, S.n, S.nslices, S.sptr,
                            S.srow0, S.perm, S.rowmap, S.init, S.col, (const VT *)S.val, x, y, w, partials, scs, mp,
-                           sy, nxcd, S.lens, S.wsl, S.wofs, tsp, tcl, tvl, tof);
+                           sy, nxcd, S.lens, S.wsl, S.wofs, tsp, tcl, tvl, tof, rr);
     else
         hipLaunchKernelGGL((k_sell_spmv<U, VT, false>), dim3(nb), dim3(kThreads), 0, s, S.n, S.nslices, S.sptr,
                            S.srow0, S.perm, S.rowmap, S.init, S.col, (const VT *)S.val, x, y, w, partials, scs, mp,
-                           sy, nxcd, S.lens, S.wsl, S.wofs, tsp, tcl, tvl, tof);
+                           sy, nxcd, S.lens, S.wsl, S.wofs, tsp, tcl, tvl, tof, rr);
 }
 
 template <typename VT>
 static void launch_sell_v(const Sell &S, int un, const double *x, double *y, const double *w, double *partials,
                           PcgScalars *scs, const Map &mp, const Systems &sy, int nb, int nxcd, hipStream_t s,
-                          bool fused = false) {
+                          bool fused = false, const double *rr = nullptr) {
     switch (un) {
-        case 1: launch_sell_t<1, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused); break;
-        case 2: launch_sell_t<2, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused); break;
-        case 4: launch_sell_t<4, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused); break;
-        default: launch_sell_t<8, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused); break;
+        case 1: launch_sell_t<1, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr); break;
+        case 2: launch_sell_t<2, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr); break;
+        case 4: launch_sell_t<4, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr); break;
+        default: launch_sell_t<8, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr); break;
     }
 }
 
@@ -1013,11 +1129,11 @@ static int sell_unroll(const Sell &S) {
     return (S.n > 0 && S.entries <= 8 * (int64_t)S.n) ? 4 : 8;
 }
 
-// y = S x for a SELL-64 matrix laid out for the batch (optionally fused dot y.w finalised into
-// the systems' scalars); a split layout's tail is multiplied first
+// y = S x for a SELL-64 matrix laid out for the batch (optionally fused dot y.w: one partial sum
+// per block, finalised into the systems' scalars when fin says so); a split layout's tail is multiplied first
 static void sell_spmv(const char *name, const Sell &S, const BatchMaps &bm, const double *x, double *y,
                       const double *w, double *partials, PcgScalars *scs, int fin, const DeviceInfo &di,
-                      hipStream_t s) {
+                      hipStream_t s, const double *rr = nullptr) {
     const int un = sell_unroll(S);
     // a split layout's tail runs in a launch of its own first; inside the slices' product when
     // asked for (measured slower: the lanes of long rows serialise their tails while the rest of
@@ -1039,50 +1155,54 @@ static void sell_spmv(const char *name, const Sell &S, const BatchMaps &bm, cons
     {
         ProfScope ps(name, s);
         if (S.f32)
-            launch_sell_v<float>(S, un, x, y, w, partials, scs, bm.sell.mp, bm.sy, nb, di.num_xcds, s, fused);
+            launch_sell_v<float>(S, un, x, y, w, partials, scs, bm.sell.mp, bm.sy, nb, di.num_xcds, s, fused, rr);
         else
-            launch_sell_v<double>(S, un, x, y, w, partials, scs, bm.sell.mp, bm.sy, nb, di.num_xcds, s, fused);
+            launch_sell_v<double>(S, un, x, y, w, partials, scs, bm.sell.mp, bm.sy, nb, di.num_xcds, s, fused, rr);
     }
-    if (w)
-        hipLaunchKernelGGL(k_finalize, dim3(bm.nsys), dim3(kThreads), 0, s, partials, nb, bm.sell.mp, fin, scs);
+    if (w && fin != FIN_NONE)
+        hipLaunchKernelGGL(k_finalize, dim3(bm.nsys), dim3(kThreads), 0, s, Parts{partials, bm.sell.mp, nb}, Parts(), fin,
+                           scs);
 }
+
+// the scalars a fused product reads and writes
+struct FusedScal {
+    const PcgScalars *in = nullptr;
+    PcgScalars *out = nullptr;
+    int32_t *bad = nullptr;
+    Parts pa, pb;
+};
 
 template <int U, typename VT, int MODE>
 static void launch_fused_t(const Sell &S, const double *va, const double *vb, double *own, double *x,
-                           const double *pn, double *y, double *partials, PcgScalars *scs, int first,
+                           const double *pn, double *y, double *partials, const FusedScal &fs, int first,
                            const BatchMaps &bm, int nxcd, hipStream_t s) {
     hipLaunchKernelGGL((k_sell_fused<U, VT, MODE>), dim3(bm.sell.nblocks), dim3(kThreads), 0, s, S.n, S.nslices,
-                       S.sptr, S.srow0, S.col, (const VT *)S.val, va, vb, own, x, pn, y, partials, scs, first,
-                       bm.sell.mp, bm.sy, nxcd);
+                       S.sptr, S.srow0, S.col, (const VT *)S.val, va, vb, own, x, pn, y, partials, fs.in, fs.out, fs.bad,
+                       fs.pa, fs.pb, first, bm.sell.mp, bm.sy, nxcd);
 }
 
 template <typename VT, int MODE>
 static void launch_fused_v(const Sell &S, int un, const double *va, const double *vb, double *own, double *x,
-                           const double *pn, double *y, double *partials, PcgScalars *scs, int first,
+                           const double *pn, double *y, double *partials, const FusedScal &fs, int first,
                            const BatchMaps &bm, int nxcd, hipStream_t s) {
     switch (un) {
-        case 1: launch_fused_t<1, VT, MODE>(S, va, vb, own, x, pn, y, partials, scs, first, bm, nxcd, s); break;
-        case 2: launch_fused_t<2, VT, MODE>(S, va, vb, own, x, pn, y, partials, scs, first, bm, nxcd, s); break;
-        case 4: launch_fused_t<4, VT, MODE>(S, va, vb, own, x, pn, y, partials, scs, first, bm, nxcd, s); break;
-        default: launch_fused_t<8, VT, MODE>(S, va, vb, own, x, pn, y, partials, scs, first, bm, nxcd, s); break;
+        case 1: launch_fused_t<1, VT, MODE>(S, va, vb, own, x, pn, y, partials, fs, first, bm, nxcd, s); break;
+        case 2: launch_fused_t<2, VT, MODE>(S, va, vb, own, x, pn, y, partials, fs, first, bm, nxcd, s); break;
+        case 4: launch_fused_t<4, VT, MODE>(S, va, vb, own, x, pn, y, partials, fs, first, bm, nxcd, s); break;
+        default: launch_fused_t<8, VT, MODE>(S, va, vb, own, x, pn, y, partials, fs, first, bm, nxcd, s); break;
     }
 }
 
-// fused product followed by the finalisation of its dot
 template <int MODE>
 static void sell_fused(const char *name, const Sell &S, const BatchMaps &bm, const double *va, const double *vb,
-                       double *own, double *x, const double *pn, double *y, double *partials, PcgScalars *scs,
-                       int first, int fin, const DeviceInfo &di, hipStream_t s) {
+                       double *own, double *x, const double *pn, double *y, double *partials, const FusedScal &fs,
+                       int first, const DeviceInfo &di, hipStream_t s) {
     const int un = sell_unroll(S);
-    {
-        ProfScope ps(name, s);
-        if (S.f32)
-            launch_fused_v<float, MODE>(S, un, va, vb, own, x, pn, y, partials, scs, first, bm, di.num_xcds, s);
-        else
-            launch_fused_v<double, MODE>(S, un, va, vb, own, x, pn, y, partials, scs, first, bm, di.num_xcds, s);
-    }
-    hipLaunchKernelGGL(k_finalize, dim3(bm.nsys), dim3(kThreads), 0, s, partials, bm.sell.nblocks, bm.sell.mp, fin,
-                       scs);
+    ProfScope ps(name, s);
+    if (S.f32)
+        launch_fused_v<float, MODE>(S, un, va, vb, own, x, pn, y, partials, fs, first, bm, di.num_xcds, s);
+    else
+        launch_fused_v<double, MODE>(S, un, va, vb, own, x, pn, y, partials, fs, first, bm, di.num_xcds, s);
 }
 
 // Y = A X for K vectors stored row by row (entry (i, j) at i * K + j): one wavefront per
@@ -1562,9 +1682,11 @@ class PcgRun {
         seg.nsys = nsys_;
         seg.row0 = row0_.data();
 
-        const size_t np = (size_t)2 * std::max(bm_.sell.nblocks, std::max(bm_.vec.nblocks, di_.num_cus * 16)) + 64;
-        const size_t nsc_elems = (sizeof(PcgScalars) * (size_t)nsys_ + sizeof(double) - 1) / sizeof(double);
-        const size_t need = (size_t)kWorkVectors * n + np + nsc_elems + 16;
+        // partial sums: p.q, r.r and r.z (the start and the final check use them in turn); scalars: two
+        // buffers and the marks of systems with p.Ap <= 0
+        const size_t maxb = std::max(bm_.sell.nblocks, std::max(bm_.vec.nblocks, di_.num_cus * 16));
+        const size_t nsc_elems = (2 * (sizeof(PcgScalars) / sizeof(double)) + 3) * (size_t)nsys_ + ((size_t)nsys_ + 1) / 2;
+        const size_t need = (size_t)kWorkVectors * n + 3 * maxb + nsc_elems;
         double *ws = nullptr;
         if (P_ && P_->work_elems >= need) {
             ws = P_->work;
@@ -1580,7 +1702,11 @@ class PcgRun {
         q_ = ws + 5 * (size_t)n;
         t_ = ws + 6 * (size_t)n;
         partials_ = ws + kWorkVectors * (size_t)n;
-        sc_ = (PcgScalars *)(partials_ + np);
+        pa_rr_ = partials_ + maxb;
+        pa_rz_ = partials_ + 2 * maxb;
+        sc_ = (PcgScalars *)(partials_ + 3 * maxb);
+        red_ = (double *)(sc_ + 2 * (size_t)nsys_);
+        bad_ = (int32_t *)(red_ + 3 * (size_t)nsys_);
 
         // A in the SELL-64 layout for the iteration (one conversion per solve); CSR only for one
         // system when asked for
@@ -1594,19 +1720,19 @@ class PcgRun {
         }
         const dim3 gv(bm_.vec.nblocks), gs(bm_.nsys);
         const int plain = P_ ? 0 : 1;
-        hipLaunchKernelGGL(k_set_scalars, dim3((nsys_ + 255) / 256), dim3(256), 0, s_, sc_, nsys_, rtol_, maxit_,
+        hipLaunchKernelGGL(k_set_scalars, dim3((nsys_ + 255) / 256), dim3(256), 0, s_, sc_, bad_, nsys_, rtol_, maxit_,
                            plain);
         // r0 = b - A x0
-        spmv_A("spmv_A", x_, q_, nullptr, FIN_NONE, false);
+        spmv_A("spmv_A", x_, q_, nullptr, nullptr);
         hipLaunchKernelGGL(k_init_residual, gv, dim3(kThreads), 0, s_, n, b_, q_, r_, partials_, bm_.vec.mp, bm_.sy,
                            di_.num_xcds);
-        hipLaunchKernelGGL(k_finalize, gs, dim3(kThreads), 0, s_, partials_, bm_.vec.nblocks, bm_.vec.mp,
-                           (int)FIN_INIT, sc_);
+        hipLaunchKernelGGL(k_finalize, gs, dim3(kThreads), 0, s_, vec_parts(partials_),
+                           vec_parts(partials_ + bm_.vec.nblocks), (int)FIN_INIT, sc_);
         // z0 = M^-1 r0, rho0 = r0.z0, p0 = z0
         zz_ = z_;
         if (P_) {
             sell_spmv("spmv_G", P_->sg, bm_, r_, t_, nullptr, nullptr, sc_, FIN_NONE, di_, s_);
-            sell_spmv("spmv_GT_dot", P_->sgt, bm_, t_, z_, r_, partials_, sc_, FIN_RHO0, di_, s_);
+            sell_spmv("spmv_GT_dot", P_->sgt, bm_, t_, z_, r_, pa_rz_, sc_, FIN_RHO0, di_, s_);
         } else {
             zz_ = r_;
         }
@@ -1630,8 +1756,8 @@ class PcgRun {
         // kernels measured faster than replaying graphs at every size tried
         use_graph_ = !profiling_on() && option(AFSAI_OPT_PCG_GRAPH) == 2;
         if (!fused_)
-            hipLaunchKernelGGL(k_update_p, gv, dim3(kThreads), 0, s_, n, p_, zz_, sc_, 1, bm_.vec.mp, bm_.sy,
-                               di_.num_xcds);
+            hipLaunchKernelGGL(k_update_p, gv, dim3(kThreads), 0, s_, n, p_, zz_, sc_, (PcgScalars *)nullptr, bad_,
+                               Parts(), Parts(), 1, bm_.vec.mp, bm_.sy, di_.num_xcds);
         mark0_ = prof_mark();
         prev_it_.assign(nsys_, 0);
         prev_rr_.assign(nsys_, 0.0);
@@ -1721,7 +1847,7 @@ class PcgRun {
         AFSAI_HIP_TRY(hipStreamSynchronize(s_));
         std::vector<PcgScalars> fin_s(nsys_);
         const size_t scbytes = sizeof(PcgScalars) * (size_t)nsys_;
-        AFSAI_HIP_TRY(hipMemcpyAsync(fin_s.data(), sc_, scbytes, hipMemcpyDeviceToHost, s_));
+        AFSAI_HIP_TRY(hipMemcpyAsync(fin_s.data(), scal(iter_no_), scbytes, hipMemcpyDeviceToHost, s_));
         AFSAI_HIP_TRY(hipStreamSynchronize(s_));
         int it_max = 0;
         for (int k = 0; k < nsys_; ++k) it_max = std::max(it_max, (int)fin_s[k].it);
@@ -1730,14 +1856,15 @@ class PcgRun {
             prof_drop(keep_to, prof_mark());
         }
         const dim3 gv(bm_.vec.nblocks), gs(bm_.nsys);
-        hipLaunchKernelGGL(k_zero_rhs, gv, dim3(kThreads), 0, s_, n, x_, sc_, bm_.vec.mp, bm_.sy, di_.num_xcds);
+        hipLaunchKernelGGL(k_zero_rhs, gv, dim3(kThreads), 0, s_, n, x_, scal(iter_no_), bm_.vec.mp, bm_.sy,
+                           di_.num_xcds);
         // true residuals ||b - A x||
-        spmv_A("spmv_A", x_, q_, nullptr, FIN_NONE, false);
+        spmv_A("spmv_A", x_, q_, nullptr, nullptr);
         hipLaunchKernelGGL(k_resid_norm, gv, dim3(kThreads), 0, s_, n, b_, q_, partials_, bm_.vec.mp, bm_.sy,
                            di_.num_xcds);
-        hipLaunchKernelGGL(k_finalize, gs, dim3(kThreads), 0, s_, partials_, bm_.vec.nblocks, bm_.vec.mp,
-                           (int)FIN_RESID, sc_);
-        AFSAI_HIP_TRY(hipMemcpyAsync(hs_[0], sc_, scbytes, hipMemcpyDeviceToHost, s_));
+        hipLaunchKernelGGL(k_finalize, gs, dim3(kThreads), 0, s_, vec_parts(partials_), Parts(), (int)FIN_RESID,
+                           scal(iter_no_));
+        AFSAI_HIP_TRY(hipMemcpyAsync(hs_[0], scal(iter_no_), scbytes, hipMemcpyDeviceToHost, s_));
         AFSAI_HIP_TRY(hipEventRecord(t1_, s_));
         AFSAI_HIP_TRY(hipStreamSynchronize(s_));
         AFSAI_HIP_TRY(hipGetLastError());
@@ -1774,12 +1901,20 @@ class PcgRun {
     }
 
   private:
-    // products inside the iteration stop with their system (gate); the first and the final
-    // A x run for every system
-    void spmv_A(const char *name, const double *xin, double *yout, const double *w, int fin, bool gate) {
-        PcgScalars *g = gate ? sc_ : nullptr;
-        if (use_sell_) sell_spmv(name, As_, bm_, xin, yout, w, w ? partials_ : nullptr, g, fin, di_, s_);
-        else spmv(name, csr_of(&A_), xin, yout, w, w ? partials_ : nullptr, g, fin, di_, s_);
+    // the scalars before iteration it (0-based): two buffers in turn
+    PcgScalars *scal(int it) const { return sc_ + (size_t)(it & 1) * nsys_; }
+    Parts sell_parts(const double *p) const { return Parts{p, bm_.sell.mp, bm_.sell.nblocks}; }
+    Parts vec_parts(const double *p) const { return Parts{p, bm_.vec.mp, bm_.vec.nblocks}; }
+    Parts red_parts(int j) const { return Parts{red_ + (size_t)j * nsys_, Map(), 0}; }
+    // partials of r.r (the fused form's product sums it, else the vector update) and of r.z
+    Parts rr_parts() const { return fused_ ? sell_parts(pa_rr_) : vec_parts(pa_rr_); }
+    Parts rz_parts() const { return P_ ? sell_parts(pa_rz_) : Parts(); }
+
+    // products inside the iteration stop with their system (gate: its scalars); the first and the
+    // final A x run for every system
+    void spmv_A(const char *name, const double *xin, double *yout, const double *w, PcgScalars *gate) {
+        if (use_sell_) sell_spmv(name, As_, bm_, xin, yout, w, w ? partials_ : nullptr, gate, FIN_NONE, di_, s_);
+        else spmv(name, csr_of(&A_), xin, yout, w, w ? partials_ : nullptr, gate, di_, s_);
     }
 
     // One iteration: from the captured graph of its buffer parity (captured at its first use;
@@ -1787,7 +1922,7 @@ class PcgRun {
     // Capture runs on a private stream of this thread (the caller's stream may be the null
     // stream, which cannot capture); nothing executes there, the graph is launched on s_.
     int launch_iteration() {
-        const int par = fused_ ? (iter_no_ & 1) : 0;
+        const int par = iter_no_ & 1;
         if (!use_graph_ || (fused_ && iter_no_ == 0)) {
             enqueue_iteration();
             return AFSAI_OK;
@@ -1827,39 +1962,55 @@ class PcgRun {
 
     void enqueue_iteration() {
         const int n = A_.n;
-        const dim3 gv(bm_.vec.nblocks), gs(bm_.nsys);
+        const dim3 gv(bm_.vec.nblocks), gs(nsys_);
+        PcgScalars *s_in = scal(iter_no_), *s_out = scal(iter_no_ + 1);
         if (fused_) {
             // p and r are double-buffered: the products read neighbours' old entries while
             // owners store the new ones
             const bool odd = (iter_no_ & 1) == 0;  // iteration 1, 3, ...: p -> p2, r -> r2
             double *p_old = odd ? p_ : p2_, *p_new = odd ? p2_ : p_;
             double *r_old = odd ? r_ : r2_, *r_new = odd ? r2_ : r_;
-            sell_fused<FUSE_AP>("spmv_A_dot", As_, bm_, z_, p_old, p_new, nullptr, nullptr, q_, partials_, sc_,
-                                iter_no_ == 0 ? 1 : 0, FIN_ALPHA, di_, s_);
-            sell_fused<FUSE_GR>("spmv_G_upd", P_->sg, bm_, r_old, q_, r_new, x_, p_new, t_, partials_, sc_, 0,
-                                FIN_UPDATE, di_, s_);
+            sell_fused<FUSE_AP>("spmv_A_dot", As_, bm_, z_, p_old, p_new, nullptr, nullptr, q_, partials_,
+                                FusedScal{s_in, s_out, bad_, rr_parts(), rz_parts()}, iter_no_ == 0 ? 1 : 0, di_, s_);
+            sell_fused<FUSE_GR>("spmv_G_upd", P_->sg, bm_, r_old, q_, r_new, x_, p_new, t_, pa_rr_,
+                                FusedScal{s_out, nullptr, bad_, sell_parts(partials_), Parts()}, 0, di_, s_);
             marks_.push_back(prof_mark());
-            sell_spmv("spmv_GT_dot", P_->sgt, bm_, t_, z_, r_new, partials_, sc_, FIN_BETA, di_, s_);
+            sell_spmv("spmv_GT_dot", P_->sgt, bm_, t_, z_, r_new, pa_rz_, s_out, FIN_NONE, di_, s_);
             ++iter_no_;
             return;
         }
-        spmv_A("spmv_A_dot", p_, q_, p_, FIN_ALPHA, true);
+        // the sums are added by launches of their own here: thousands of blocks would each read
+        // thousands of partials (121^3: 23.4 -> 25.9 ms)
+        spmv_A("spmv_A_dot", p_, q_, p_, s_in);
+        const Parts pq = use_sell_ ? sell_parts(partials_) : Parts{partials_, Map(), spmv_blocks(csr_of(&A_), di_)};
+        hipLaunchKernelGGL(k_reduce, gs, dim3(kThreads), 0, s_, pq, Parts(), red_, (double *)nullptr, s_in);
         {
             ProfScope ps("update_xr", s_);
-            hipLaunchKernelGGL(k_update_xr, gv, dim3(kThreads), 0, s_, n, x_, r_, p_, q_, partials_, sc_, bm_.vec.mp,
-                               bm_.sy, di_.num_xcds);
+            hipLaunchKernelGGL(k_update_xr, gv, dim3(kThreads), 0, s_, n, x_, r_, p_, q_, pa_rr_, s_in, bad_,
+                               red_parts(0), bm_.vec.mp, bm_.sy, di_.num_xcds);
         }
-        hipLaunchKernelGGL(k_finalize, gs, dim3(kThreads), 0, s_, partials_, bm_.vec.nblocks, bm_.vec.mp,
-                           (int)FIN_UPDATE, sc_);
         marks_.push_back(prof_mark());
+        // the iteration that converges needs no z: with a large G (the two products cost more than a
+        // launch per iteration) r.r is summed before them and they return; else with r.z
+        const bool gate = P_ && P_->sg.entries >= kGateEntries;
+        if (gate)
+            hipLaunchKernelGGL(k_reduce, gs, dim3(kThreads), 0, s_, vec_parts(pa_rr_), Parts(), red_ + nsys_,
+                               (double *)nullptr, s_in);
         if (P_) {
-            sell_spmv("spmv_G", P_->sg, bm_, r_, t_, nullptr, nullptr, sc_, FIN_NONE, di_, s_);
-            sell_spmv("spmv_GT_dot", P_->sgt, bm_, t_, z_, r_, partials_, sc_, FIN_BETA, di_, s_);
+            const double *rr = gate ? red_ + nsys_ : nullptr;
+            sell_spmv("spmv_G", P_->sg, bm_, r_, t_, nullptr, nullptr, s_in, FIN_NONE, di_, s_, rr);
+            sell_spmv("spmv_GT_dot", P_->sgt, bm_, t_, z_, r_, pa_rz_, s_in, FIN_NONE, di_, s_, rr);
         }
+        if (gate)
+            hipLaunchKernelGGL(k_reduce, gs, dim3(kThreads), 0, s_, rz_parts(), Parts(), red_ + 2 * (size_t)nsys_,
+                               (double *)nullptr, s_in);
+        else
+            hipLaunchKernelGGL(k_reduce, gs, dim3(kThreads), 0, s_, vec_parts(pa_rr_), rz_parts(), red_ + nsys_,
+                               red_ + 2 * (size_t)nsys_, s_in);
         {
             ProfScope ps("update_p", s_);
-            hipLaunchKernelGGL(k_update_p, gv, dim3(kThreads), 0, s_, n, p_, zz_, sc_, 0, bm_.vec.mp, bm_.sy,
-                               di_.num_xcds);
+            hipLaunchKernelGGL(k_update_p, gv, dim3(kThreads), 0, s_, n, p_, zz_, s_in, s_out, bad_, red_parts(1),
+                               P_ ? red_parts(2) : Parts(), 0, bm_.vec.mp, bm_.sy, di_.num_xcds);
         }
         ++iter_no_;
     }
@@ -1874,8 +2025,7 @@ class PcgRun {
         }
         enqueued_ += todo;
         const int slot = c_ & 1;
-        const int nw = nsys_ * (int)(sizeof(PcgScalars) / sizeof(double));
-        hipLaunchKernelGGL(k_publish, dim3((nw + kThreads - 1) / kThreads), dim3(kThreads), 0, s_, sc_, nw,
+        hipLaunchKernelGGL(k_publish, dim3(nsys_), dim3(kThreads), 0, s_, scal(iter_no_), bad_, rr_parts(), rz_parts(),
                            dhs_[slot]);
         its_[c_ & 3] = todo;
         AFSAI_HIP_TRY(hipEventRecord(ev_[c_ & 3], s_));
@@ -1902,8 +2052,10 @@ class PcgRun {
     hipGraphExec_t gexec_[2] = {nullptr, nullptr};
     double *r_ = nullptr, *r2_ = nullptr, *z_ = nullptr, *p_ = nullptr, *p2_ = nullptr, *q_ = nullptr, *t_ = nullptr;
     const double *zz_ = nullptr;
-    double *partials_ = nullptr;
-    PcgScalars *sc_ = nullptr;
+    double *partials_ = nullptr, *pa_rr_ = nullptr, *pa_rz_ = nullptr;
+    double *red_ = nullptr;     // [3][nsys]: the sums p.q, r.r, r.z of the separate form
+    PcgScalars *sc_ = nullptr;  // [2][nsys]
+    int32_t *bad_ = nullptr;    // [nsys]
     PcgScalars *hsc_ = nullptr;
     PcgScalars *hs_[2] = {nullptr, nullptr};
     PcgScalars *dhs_[2] = {nullptr, nullptr};  // device addresses of hs_
@@ -1963,7 +2115,7 @@ int afsai_spmv(const afsai_csr *A, const double *x, double *y, void *stream) {
     DeviceInfo di;
     if ((rc = device_info(&di))) return rc;
     hipStream_t s = (hipStream_t)stream;
-    spmv("spmv_A", csr_of(A), x, y, nullptr, nullptr, nullptr, FIN_NONE, di, s);
+    spmv("spmv_A", csr_of(A), x, y, nullptr, nullptr, nullptr, di, s);
     AFSAI_HIP_TRY(hipGetLastError());
     return AFSAI_OK;
 }
