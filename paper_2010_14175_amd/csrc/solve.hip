@@ -25,6 +25,7 @@
 // launch.)  A device flag ends the iteration: kernels that see it return at once, so the host
 // enqueues chunks of iterations and reads the flag once per chunk, one chunk behind.
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <mutex>
@@ -36,6 +37,8 @@ namespace afsai {
 
 constexpr int kThreads = 256;
 constexpr int kFusedMaxRows = 200000;  // automatic PCG form: fused products below this size
+constexpr int64_t kSmallBytes = 4 << 20;       // one-launch solve: matrix bytes of an iteration at most
+constexpr int kSmallIters = 1024;              // and iterations of a launch
 constexpr int64_t kGateEntries = 1 << 26;  // factors whose products look at r.r before they start
 // resumable solver: iterations of the first chunk, least GPU time of a chunk and its share of
 // the GPU time so far
@@ -230,6 +233,18 @@ __device__ __forceinline__ bool step_alpha(const PcgScalars &s, const Parts &pq,
     return true;
 }
 
+// The scalars at the start, from b.b and r.r
+__device__ __forceinline__ void init_scalars(PcgScalars &s, double bb, double rr) {
+    s.bb = bb;
+    s.rr = rr;
+    s.tol = s.rtol * sqrt(bb);
+    s.it = 0;
+    if (bb == 0.0) s.done = DONE_ZERO_RHS;
+    else if (sqrt(rr) <= s.tol) s.done = DONE_CONVERGED;
+    else if (s.maxit == 0) s.done = DONE_MAXIT;
+    if (s.plain) s.rho = rr;
+}
+
 // One block per system: the sums of the start and of the final check (partials of the previous
 // launch; FIN_INIT has two of them, b.b and then r.r).
 __global__ __launch_bounds__(kThreads) void k_finalize(Parts pa, Parts pb, int fin, PcgScalars *scs) {
@@ -244,17 +259,9 @@ __global__ __launch_bounds__(kThreads) void k_finalize(Parts pa, Parts pb, int f
         case FIN_RHO0:
             sc->rho = v;
             break;
-        case FIN_INIT: {  // v = b.b, rr = r.r
-            sc->bb = v;
-            sc->rr = rr;
-            sc->tol = sc->rtol * sqrt(v);
-            sc->it = 0;
-            if (v == 0.0) sc->done = DONE_ZERO_RHS;
-            else if (sqrt(rr) <= sc->tol) sc->done = DONE_CONVERGED;
-            else if (sc->maxit == 0) sc->done = DONE_MAXIT;
-            if (sc->plain) sc->rho = rr;
+        case FIN_INIT:  // v = b.b, rr = r.r
+            init_scalars(*sc, v, rr);
             break;
-        }
         case FIN_RESID:
             sc->resid = v;
             break;
@@ -855,7 +862,8 @@ __global__ __launch_bounds__(kThreads) void k_publish(PcgScalars *scs, const int
     if (threadIdx.x == 0) host[k] = st;
 }
 
-__global__ void k_set_scalars(PcgScalars *scs, int32_t *bad, int nsys, double rtol, int maxit, int plain) {
+__global__ void k_set_scalars(PcgScalars *scs, int32_t *bad, int32_t *ctl, int nsys, double rtol, int maxit, int plain) {
+    if (blockIdx.x == 0 && threadIdx.x < 4) ctl[threadIdx.x] = 0;
     for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < nsys; k += gridDim.x * blockDim.x) {
         PcgScalars s{};
         s.rtol = rtol;
@@ -885,6 +893,12 @@ __global__ __launch_bounds__(kThreads) void k_resid_norm(int n, const double *__
     const double bs = block_sum(pr, sh);
     store_partials(partials, 1, &bs, jb.gb);
 }
+
+}  // namespace afsai
+
+#include "pcg_small.hpp"
+
+namespace afsai {
 
 // ---------------------------------------------------------------------------------------
 // host side
@@ -924,6 +938,29 @@ static int blocks_for_slices(int nslices, const DeviceInfo &di) {
     if (nb > cap) nb = cap;
     if (nb < 1) nb = 1;
     return (int)nb;
+}
+
+// the device's XCDs as bits of their hardware numbers (looked up on the first call)
+static int xcc_mask(const DeviceInfo &di, hipStream_t s, uint32_t *mask) {
+    constexpr int kMaxDev = 64;
+    static std::mutex mu;
+    static uint32_t known[kMaxDev] = {};
+    *mask = 0;
+    if (di.device < 0 || di.device >= kMaxDev) return AFSAI_OK;
+    std::lock_guard<std::mutex> lk(mu);
+    if (!known[di.device]) {
+        DevBuf m;
+        int rc;
+        uint32_t h = 0;
+        if ((rc = dalloc(m, sizeof(uint32_t), s))) return rc;
+        AFSAI_HIP_TRY(hipMemcpyAsync(m.p, &h, sizeof h, hipMemcpyHostToDevice, s));
+        hipLaunchKernelGGL(k_xcc_mask, dim3(di.num_cus * 4), dim3(64), 0, s, m.as<uint32_t>());
+        AFSAI_HIP_TRY(hipMemcpyAsync(&h, m.p, sizeof h, hipMemcpyDeviceToHost, s));
+        AFSAI_HIP_TRY(hipStreamSynchronize(s));
+        known[di.device] = h;
+    }
+    *mask = known[di.device];
+    return AFSAI_OK;
 }
 
 struct Csr {
@@ -1685,7 +1722,7 @@ class PcgRun {
         // partial sums: p.q, r.r and r.z (the start and the final check use them in turn); scalars: two
         // buffers and the marks of systems with p.Ap <= 0
         const size_t maxb = std::max(bm_.sell.nblocks, std::max(bm_.vec.nblocks, di_.num_cus * 16));
-        const size_t nsc_elems = (2 * (sizeof(PcgScalars) / sizeof(double)) + 3) * (size_t)nsys_ + ((size_t)nsys_ + 1) / 2;
+        const size_t nsc_elems = (2 * (sizeof(PcgScalars) / sizeof(double)) + 3) * (size_t)nsys_ + ((size_t)nsys_ + 1) / 2 + 2;
         const size_t need = (size_t)kWorkVectors * n + 3 * maxb + nsc_elems;
         double *ws = nullptr;
         if (P_ && P_->work_elems >= need) {
@@ -1706,7 +1743,8 @@ class PcgRun {
         pa_rz_ = partials_ + 2 * maxb;
         sc_ = (PcgScalars *)(partials_ + 3 * maxb);
         red_ = (double *)(sc_ + 2 * (size_t)nsys_);
-        bad_ = (int32_t *)(red_ + 3 * (size_t)nsys_);
+        ctl_ = (int32_t *)(red_ + 3 * (size_t)nsys_);  // control words of the one-launch solve
+        bad_ = ctl_ + 4;
 
         // A in the SELL-64 layout for the iteration (one conversion per solve); CSR only for one
         // system when asked for
@@ -1718,10 +1756,26 @@ class PcgRun {
             if ((rc = sell_from_csr(n, A_.nnz, A_.row_ptr, A_.col_idx, A_.val, false, false, &As_, di_, s_, seg)))
                 return rc;
         }
+        // fused products where launches dominate (small systems), separate updates where the
+        // fused products' second gather costs more than the update kernels; the fused kernels
+        // need layouts without a tail
+        const int64_t form = option(AFSAI_OPT_PCG_FORM);
+        int nmax = 0;
+        for (int k = 0; k < nsys_; ++k) nmax = std::max(nmax, row0_[k + 1] - row0_[k]);
+        const bool want_fused = form == 2 || (form == 0 && nmax < kFusedMaxRows);
+        fused_ = P_ && use_sell_ && want_fused && !As_.tail && !P_->sg.tail && !As_.perm && !P_->sg.perm;
+        if ((rc = choose_small())) return rc;
+        return small_ ? enqueue_small() : start();
+    }
+
+    // The start of the iteration and its first chunk
+    int start() {
+        const int n = A_.n;
+        int rc;
         const dim3 gv(bm_.vec.nblocks), gs(bm_.nsys);
         const int plain = P_ ? 0 : 1;
-        hipLaunchKernelGGL(k_set_scalars, dim3((nsys_ + 255) / 256), dim3(256), 0, s_, sc_, bad_, nsys_, rtol_, maxit_,
-                           plain);
+        hipLaunchKernelGGL(k_set_scalars, dim3((nsys_ + 255) / 256), dim3(256), 0, s_, sc_, bad_, ctl_, nsys_, rtol_,
+                           maxit_, plain);
         // r0 = b - A x0
         spmv_A("spmv_A", x_, q_, nullptr, nullptr);
         hipLaunchKernelGGL(k_init_residual, gv, dim3(kThreads), 0, s_, n, b_, q_, r_, partials_, bm_.vec.mp, bm_.sy,
@@ -1736,14 +1790,6 @@ class PcgRun {
         } else {
             zz_ = r_;
         }
-        // fused products where launches dominate (small systems), separate updates where the
-        // fused products' second gather costs more than the update kernels; the fused kernels
-        // need layouts without a tail
-        const int64_t form = option(AFSAI_OPT_PCG_FORM);
-        int nmax = 0;
-        for (int k = 0; k < nsys_; ++k) nmax = std::max(nmax, row0_[k + 1] - row0_[k]);
-        const bool want_fused = form == 2 || (form == 0 && nmax < kFusedMaxRows);
-        fused_ = P_ && use_sell_ && want_fused && !As_.tail && !P_->sg.tail && !As_.perm && !P_->sg.perm;
         // A's product with one column index per run of three consecutive columns where every
         // row is made of such runs (3 x 3 blocks): 9.3 instead of 12 bytes per FP64 entry, the
         // same sums (the fused kernels keep the plain layout)
@@ -1779,6 +1825,7 @@ class PcgRun {
             *finished = true;
             return AFSAI_OK;
         }
+        if (small_) return advance_small(block, finished);
         const int slot = (c_ - 2) & 1;  // state after the oldest chunk in flight
         hipEvent_t ev = ev_[(c_ - 2) & 3];
         if (!block) {
@@ -1847,6 +1894,12 @@ class PcgRun {
         AFSAI_HIP_TRY(hipStreamSynchronize(s_));
         std::vector<PcgScalars> fin_s(nsys_);
         const size_t scbytes = sizeof(PcgScalars) * (size_t)nsys_;
+        float ms = 0.f;
+        if (small_) {  // the launch has left the final scalars and the true residual
+            fin_s[0] = hs_[0][0];
+            AFSAI_HIP_TRY(hipEventElapsedTime(&ms, t0_, ev_[0]));
+            return report(fin_s, ms, info);
+        }
         AFSAI_HIP_TRY(hipMemcpyAsync(fin_s.data(), scal(iter_no_), scbytes, hipMemcpyDeviceToHost, s_));
         AFSAI_HIP_TRY(hipStreamSynchronize(s_));
         int it_max = 0;
@@ -1868,9 +1921,14 @@ class PcgRun {
         AFSAI_HIP_TRY(hipEventRecord(t1_, s_));
         AFSAI_HIP_TRY(hipStreamSynchronize(s_));
         AFSAI_HIP_TRY(hipGetLastError());
-        float ms = 0.f;
         AFSAI_HIP_TRY(hipEventElapsedTime(&ms, t0_, t1_));
         prof_flush();
+        return report(fin_s, ms, info);
+    }
+
+  private:
+    // status and results from the final scalars (the true residuals in the host copy)
+    int report(const std::vector<PcgScalars> &fin_s, float ms, afsai_pcg_info *info) {
         int status = AFSAI_OK;
         for (int k = 0; k < nsys_ && status == AFSAI_OK; ++k) {
             const PcgScalars &f = fin_s[k];
@@ -1900,7 +1958,83 @@ class PcgRun {
         return status;
     }
 
-  private:
+    // The one-launch solve for systems that one XCD reads faster than the launches of an iteration
+    // take (TODO), when the automatic forms are in force and the kernel timer is off
+    int choose_small() {
+        small_ = false;
+        if (!fused_ || P_->sgt.tail || nsys_ != 1 || option(AFSAI_OPT_PCG_FORM) != 0 || option(AFSAI_OPT_PCG_GRAPH) == 2 || profiling_on())
+            return AFSAI_OK;
+        const int vb = P_->sg.f32 ? 4 : 8;
+        if (12 * As_.entries + (4 + vb) * (P_->sg.entries + P_->nnz_g) > kSmallBytes || P_->sgt.entries > (1 << 24))
+            return AFSAI_OK;
+        uint32_t mask = 0;
+        int rc;
+        if ((rc = xcc_mask(di_, s_, &mask))) return rc;
+        const int nx = __builtin_popcount(mask);
+        if (nx < 1) return AFSAI_OK;
+        const int cus = std::max(1, di_.num_cus / nx), nw = (As_.nslices + kWin - 1) / kWin;
+        const int ng = std::min(kSmallWin, (nw + cus - 1) / cus);
+        const int blocks = std::min(cus, (nw + ng - 1) / ng);
+        if (nw > blocks * ng) return AFSAI_OK;
+        // solves take the XCDs in turn
+        static std::atomic<uint32_t> turn{0};
+        int pick = (int)(turn.fetch_add(1, std::memory_order_relaxed) % (uint32_t)nx), xcc = 0;
+        for (uint32_t m = mask;; m &= m - 1) {
+            xcc = __builtin_ctz(m);
+            if (pick-- == 0) break;
+        }
+        sa_ = SmallArgs{A_.n, As_.nslices, (int)As_.entries, (int)P_->sg.entries, (int)P_->sgt.entries, As_.sptr, P_->sg.sptr, P_->sgt.sptr, As_.col, P_->sg.col, P_->sgt.col,
+                        (const double *)As_.val, P_->sg.val, P_->sgt.val, P_->sgt.perm, P_->sgt.lens, b_, x_, r_, r2_, z_,
+                        p_, p2_, q_, t_, partials_, pa_rr_, pa_rz_, sc_, dhs_[0], (SmallCtl *)ctl_, blocks, xcc,
+                        bm_.vec.nblocks, 0, kSmallIters};
+        small_grid_ = dim3((unsigned)(blocks * nx));
+        small_block_ = dim3((unsigned)(ng * kThreads));
+        small_ = true;
+        return AFSAI_OK;
+    }
+
+    // up to kSmallIters iterations from sa_.iter0 on
+    int enqueue_small() {
+        if (sa_.iter0 == 0)
+            hipLaunchKernelGGL(k_set_scalars, dim3(1), dim3(256), 0, s_, sc_, bad_, ctl_, 1, rtol_, maxit_, 0);
+        else
+            hipLaunchKernelGGL(k_small_again, dim3(1), dim3(64), 0, s_, (SmallCtl *)ctl_);
+        const bool ord = sa_.t_perm != nullptr;
+        if (P_->sg.f32) {
+            if (ord) hipLaunchKernelGGL((k_pcg_small<float, true>), small_grid_, small_block_, 0, s_, sa_);
+            else hipLaunchKernelGGL((k_pcg_small<float, false>), small_grid_, small_block_, 0, s_, sa_);
+        } else {
+            if (ord) hipLaunchKernelGGL((k_pcg_small<double, true>), small_grid_, small_block_, 0, s_, sa_);
+            else hipLaunchKernelGGL((k_pcg_small<double, false>), small_grid_, small_block_, 0, s_, sa_);
+        }
+        AFSAI_HIP_TRY(hipGetLastError());
+        AFSAI_HIP_TRY(hipEventRecord(ev_[0], s_));
+        return AFSAI_OK;
+    }
+
+    int advance_small(bool block, bool *finished) {
+        if (block) {
+            AFSAI_HIP_TRY(hipEventSynchronize(ev_[0]));
+        } else {
+            const hipError_t q = hipEventQuery(ev_[0]);
+            if (q == hipErrorNotReady) return AFSAI_OK;
+            if (q != hipSuccess) AFSAI_HIP_TRY(q);
+        }
+        const PcgScalars &st = hs_[0][0];
+        if (st.pad == 1) {  // its blocks did not come together (x is untouched): the usual launches
+            small_ = false;
+            return start();
+        }
+        if (st.pad) AFSAI_FAIL(AFSAI_ERR_HIP, "pcg_solve: the blocks of a one-launch solve lost each other");
+        if (st.done != DONE_NO) {
+            done_ = true;
+            *finished = true;
+            return AFSAI_OK;
+        }
+        sa_.iter0 += sa_.iters;
+        return enqueue_small();
+    }
+
     // the scalars before iteration it (0-based): two buffers in turn
     PcgScalars *scal(int it) const { return sc_ + (size_t)(it & 1) * nsys_; }
     Parts sell_parts(const double *p) const { return Parts{p, bm_.sell.mp, bm_.sell.nblocks}; }
@@ -2056,6 +2190,10 @@ class PcgRun {
     double *red_ = nullptr;     // [3][nsys]: the sums p.q, r.r, r.z of the separate form
     PcgScalars *sc_ = nullptr;  // [2][nsys]
     int32_t *bad_ = nullptr;    // [nsys]
+    int32_t *ctl_ = nullptr;
+    bool small_ = false;        // the whole solve in one launch (pcg_small.hpp)
+    SmallArgs sa_{};
+    dim3 small_grid_, small_block_;
     PcgScalars *hsc_ = nullptr;
     PcgScalars *hs_[2] = {nullptr, nullptr};
     PcgScalars *dhs_[2] = {nullptr, nullptr};  // device addresses of hs_

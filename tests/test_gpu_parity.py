@@ -1011,3 +1011,57 @@ def test_setup_runs_shifted(af, cut):
     full = synth.elast27(6, 1.0, 2).to_scipy()
     A = synth.CSR.from_scipy(full[cut:, cut:])
     compare_factor(af, A, 10, 2, 1e-2)
+
+
+@pytest.mark.parametrize("sides,sigma,kmax,g", [
+    ((1, 1, 1), 0.0, 1, 0), ((5, 4, 3), 1.0, 5, 0), ((8, 8, 4), 0.0, 5, 1), ((257, 1, 1), 1.0, 2, 0), ((13, 13, 13), 1.0, 5, 0),
+    ((20, 20, 20), 0.0, 5, 1), ((16, 32, 16), 1.0, 0, 0), ((25, 25, 26), 1.0, 5, 0), ((26, 26, 26), 1.0, 5, 0)])
+def test_pcg_one_launch(af, sides, sigma, kmax, g):
+    """Small systems solved in one launch (one row to a window, one window to a block, two windows to
+    a block, and just above the limit) against the launches of the fused form: the same status, iterations,
+    residuals and x bit for bit, from a zero and a given x0, for maxit stops, a zero right-hand side
+    and a start that has converged."""
+    import torch
+
+    A = synth.lap7(*sides) if sigma == 0.0 else synth.lap7_lognormal(*sides, sigma, 3)
+    dA = _dev(af, A)
+    P = af.setup(dA, kmax, 1, 1e-2, g_prec=g)
+    b = _vec(synth.matvec(A, synth.uniform(5, 1, A.n)))
+    x0 = _vec(synth.uniform(6, 2, A.n))
+    exact = _vec(np.linalg.solve(A.to_scipy().toarray(), b.cpu().numpy())) if A.n <= 256 else None
+
+    def runs():
+        out = []
+        for rhs, start, rtol, maxit in [(b, None, 1e-8, None), (b, x0, 1e-8, None), (b, x0, 1e-8, 3), (b, x0, 1e-8, 1),
+                                        (b, x0, 1e-8, 0), (torch.zeros_like(b), x0, 1e-8, None)] + (
+                                            [(b, exact, 1e-8, None)] if exact is not None else []):
+            x, i = af.pcg_solve(dA, P, rhs, x=None if start is None else start.clone(), rtol=rtol, maxit=maxit)
+            out.append((i.status, i.iters, i.converged, i.relres, i.true_relres, x.cpu().numpy().view(np.int64)))
+        return out
+
+    auto = runs()
+    try:
+        af.set_option(af.OPT_PCG_FORM, 2)
+        launches = runs()
+    finally:
+        af.set_option(af.OPT_PCG_FORM, 0)
+    for p, q in zip(auto, launches):
+        assert p[:5] == q[:5], (p[:5], q[:5])
+        np.testing.assert_array_equal(p[5], q[5])
+
+
+def test_pcg_one_launch_continued(af):
+    """More iterations than one launch takes (a 1D Laplacian with a diagonal G): the next launch goes on
+    from the state of the one before."""
+    A = synth.lap7(3000, 1, 1, (1.0, 1e-9, 1e-9))
+    dA = _dev(af, A)
+    P = af.setup(dA, 0, 1, 1e-2)
+    b = _vec(synth.uniform(5, 1, A.n))
+    x, i = af.pcg_solve(dA, P, b, rtol=1e-10)
+    try:
+        af.set_option(af.OPT_PCG_FORM, 2)
+        y, j = af.pcg_solve(dA, P, b, rtol=1e-10)
+    finally:
+        af.set_option(af.OPT_PCG_FORM, 0)
+    assert i.iters == j.iters and i.iters > 1024 and i.converged and i.true_relres == j.true_relres
+    np.testing.assert_array_equal(x.cpu().numpy().view(np.int64), y.cpu().numpy().view(np.int64))
