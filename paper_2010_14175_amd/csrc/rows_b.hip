@@ -11,7 +11,7 @@ static RowsKernel b_inst(int mm, int s, int *gs, size_t *lds) {
     return bform::k_rows_b<GS, MMAX, CAPT, NB, WPE>;
 }
 
-RowsKernel rows_kernel_b(int mmax, int s, int maxlen, int *gs_out, size_t *lds_out) {
+RowsKernel rows_kernel_b(int n, int mmax, int s, int maxlen, int *gs_out, size_t *lds_out) {
     if (maxlen > 3 * bform::kRunRow || mmax > 64) return nullptr;
     // Table slots: what the patterns of the 27-point operators touch (99.9% of their rows: 56 runs
     // for 11 positions, 90 for 21, 148 for 46), no more: fewer slots are fewer bytes of LDS (64^3:
@@ -19,7 +19,13 @@ RowsKernel rows_kernel_b(int mmax, int s, int maxlen, int *gs_out, size_t *lds_o
     // with 176 slots, 654 with 192 (10 wavefronts per CU), 625 with 160 (longer probes).  Rows that
     // touch more are redone by the general form.  New rows per block: as the general form's (2, 4),
     // 3 for three or fewer rows a step (the same blocks).
-    if (mmax <= 12) return b_inst<32, 24, 64, 2, 4>(mmax, s, gs_out, lds_out);
+    // Small systems take the next larger table: redoing even a few rows costs 0.15 ms (a launch and its
+    // host round trip), more than 128 slots cost at 24,000 rows (21 positions: kernel 0.39 -> 0.46 ms,
+    // setup 0.92 -> 0.84 ms) and less than they cost at 100,000.
+    const bool roomy = n < 65536;
+    if (mmax <= 12 && !roomy) return b_inst<32, 24, 64, 2, 4>(mmax, s, gs_out, lds_out);
+    if (mmax <= 12) return b_inst<32, 24, 92, 2, 4>(mmax, s, gs_out, lds_out);
+    if (mmax <= 24 && roomy) return b_inst<32, 24, 128, 2, 3>(mmax, s, gs_out, lds_out);
     if (mmax <= 24) return b_inst<32, 24, 92, 2, 4>(mmax, s, gs_out, lds_out);
     if (mmax <= 32)
         return s <= 3 ? b_inst<32, 32, 128, 3, 3>(mmax, s, gs_out, lds_out) : b_inst<32, 32, 128, 4, 3>(mmax, s, gs_out, lds_out);

@@ -92,23 +92,22 @@ __global__ void k_row_ptr_check(int n, const int32_t *__restrict__ rp, int nnz, 
 
 // Whether every row is made of runs (3c, 3c+1, 3c+2): row pointers and entry offsets are then
 // multiples of three, so thread t checks entries 3t..3t+2 (a streaming read of the columns:
-// 0.07 ms at 61.7M entries).  Stops early where another block has found otherwise.
+// 0.07 ms at 61.7M entries).  A wavefront stops at the first round with another entry, and blocks
+// that start later see its mark; the mark is a plain store (an atomic from every wavefront of a
+// 7-point matrix took 0.1 ms).
 __global__ __launch_bounds__(256) void k_run_check(int n, int64_t nruns, const int32_t *__restrict__ rp,
                                                    const int32_t *__restrict__ ci, ScanOut *out) {
-    constexpr int kStep = 16;  // rounds between looks at the flag
-    bool bad = false;
-    for (int64_t t0 = 0; t0 < max(nruns, (int64_t)n + 1); t0 += (int64_t)gridDim.x * blockDim.x * kStep) {
-        if (__hip_atomic_load(&out->noruns, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
-        for (int k = 0; k < kStep; ++k) {
-            const int64_t t = t0 + ((int64_t)k * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x;
-            if (t <= n && rp[t] % 3 != 0) bad = true;
-            if (t < nruns) {
-                const int32_t *c = ci + 3 * t;
-                if (c[0] % 3 != 0 || c[1] != c[0] + 1 || c[2] != c[0] + 2) bad = true;
-            }
+    if (__hip_atomic_load(&out->noruns, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
+    for (int64_t t0 = (int64_t)blockIdx.x * blockDim.x; t0 < max(nruns, (int64_t)n + 1);
+         t0 += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t t = t0 + threadIdx.x;
+        bool bad = t <= n && rp[min(t, (int64_t)n)] % 3 != 0;
+        if (t < nruns) {
+            const int32_t *c = ci + 3 * t;
+            if (c[0] % 3 != 0 || c[1] != c[0] + 1 || c[2] != c[0] + 2) bad = true;
         }
         if (__any(bad)) {
-            if ((threadIdx.x & 63) == 0) atomicOr(&out->noruns, 1);
+            if ((threadIdx.x & 63) == 0) out->noruns = 1;
             return;
         }
     }
@@ -414,7 +413,7 @@ __global__ void k_block_check(int n, const int32_t *__restrict__ rp, const int32
 RowsKernel rows_kernel(int mmax_t, int cap, bool rsl, bool f32);
 RowsKernel rows_kernel_w(int mmax, int maxlen, int cap, int lanes, bool g32, int *gs_out, size_t *lds_out);
 RowsKernel rows_kernel_w_large(int mmax, int cap, bool g32, size_t *lds_out);
-RowsKernel rows_kernel_b(int mmax, int s, int maxlen, int *gs_out, size_t *lds_out);
+RowsKernel rows_kernel_b(int n, int mmax, int s, int maxlen, int *gs_out, size_t *lds_out);
 
 // Launch of a per-row kernel over `nlist` rows.  Inverse-factor form: wdyn > 0 is its dynamic
 // LDS per block and rpw its rows per wavefront; the Cholesky form sizes its LDS from the
@@ -694,7 +693,7 @@ static int setup_core(const afsai_csr *A, const afsai_params *p, int nsys, const
         // groups of 32 and 64 lanes take tables from 128 slots
         if (wcap < 128 && (lanes >= 32 || mmax > 16 || maxlen > 64)) wcap = 128;
         int gs = 64;
-        if (runs && !so.noruns) k1 = rows_kernel_b(mmax, p->s, maxlen, &gs, &wdyn);
+        if (runs && !so.noruns) k1 = rows_kernel_b(n, mmax, p->s, maxlen, &gs, &wdyn);
         if (!k1) k1 = rows_kernel_w(mmax, maxlen, wcap, lanes, (p->flags & AFSAI_GRAD_F32) != 0, &gs, &wdyn);
         if (k1) {
             wrpw = 64 / gs;
