@@ -301,7 +301,9 @@ typedef struct afsai_matrix_s *afsai_matrix;
  * afsai_matrix_prepare -- converts A to its SELL-64 layout on the current device.
  *   A's arrays are read during the call only; the handle owns a device copy (about
  *   12 bytes per entry plus padding, 13.3 when A's rows are made of runs of three
- *   consecutive columns and run indices are kept beside the columns) and A's values may change afterwards without affecting it
+ *   consecutive columns and run indices are kept beside the columns; 8.5 bytes more when A
+ *   is made of 3 x 3 blocks that three consecutive rows share, for the block products, if that
+ *   memory is there) and A's values may change afterwards without affecting it
  *   (prepare again to take them).  *out = NULL on failure.  Synchronous on stream.
  *   Errors: AFSAI_ERR_INVALID_ARG, AFSAI_ERR_NO_MEMORY, AFSAI_ERR_TOO_LARGE, AFSAI_ERR_HIP.
  */
@@ -336,8 +338,7 @@ int pcg_solve_prepared(afsai_matrix M, afsai_precond P, const double *b, double 
  *   such blocks with each row's entries contiguous).  A column that has stopped keeps its x.
  *   B, X (device): n x k row-major, caller-owned, must not alias; X0 = 0 (X is overwritten).
  *   k: 1, 2, 4 or 8.  P: a single-system preconditioner of A (not a batch, no split layouts).
- *   info (host, may be NULL): k entries.  Synchronous (the host reads the stop flags after
- *   every iteration).
+ *   info (host, may be NULL): k entries.  Synchronous.
  *   Returns AFSAI_OK, AFSAI_ERR_NOT_CONVERGED (some column reached maxit), AFSAI_ERR_NOT_SPD
  *   (p.Ap <= 0 in some column), AFSAI_ERR_INVALID_ARG, AFSAI_ERR_NO_MEMORY, AFSAI_ERR_HIP.
  */

@@ -383,6 +383,9 @@ void sell_free(Sell *S) {
     pool_free(S->col);
     pool_free(S->col3);
     pool_free(S->val);
+    pool_free(S->bptr);
+    pool_free(S->bcol);
+    pool_free(S->bval);
     pool_free(S->perm);
     pool_free(S->lens);
     pool_free(S->wsl);
@@ -500,6 +503,23 @@ static void make_windows(int nslices, int n, const Segments &seg, std::vector<in
     hw.push_back(nslices);
 }
 
+// plain slices of `cols` columns in all would store (and read) too much padding
+static bool much_padding(int64_t cols, int64_t nnz, int n) { return cols * kSlice > nnz + nnz / 10 && n > kSlice; }
+
+int sell_ordered(int n, int64_t nnz, const int32_t *rp, bool *ordered, const DeviceInfo &di, hipStream_t s) {
+    const int nsl = (n + kSlice - 1) / kSlice;
+    DevBuf width;
+    int rc;
+    if ((rc = dalloc(width, sizeof(int32_t) * (2 * (size_t)nsl + 1), s))) return rc;
+    hipLaunchKernelGGL(k_sell_width, dim3(grid1d((int64_t)nsl * 64, di)), dim3(256), 0, s, n, nsl, rp,
+                       (const int32_t *)nullptr, (const int32_t *)nullptr, (const int32_t *)nullptr, 0x7fffffff,
+                       width.as<int32_t>());
+    int64_t cols = 0;
+    if ((rc = scan_counts(nsl, width.as<int32_t>(), width.as<int32_t>() + nsl, &cols, di, s))) return rc;
+    *ordered = much_padding(cols, nnz, n);
+    return AFSAI_OK;
+}
+
 static int sell_build(int n, int64_t nnz, const int32_t *rp, const int32_t *m, int ld, const int32_t *ci,
                       const void *val, bool val_f32, bool out_f32, bool top, Sell *out, const DeviceInfo &di,
                       hipStream_t s, const Segments &seg) {
@@ -539,7 +559,7 @@ static int sell_build(int n, int64_t nnz, const int32_t *rp, const int32_t *m, i
     int64_t cols = 0;
     if ((rc = scan_counts(S.nslices, width.as<int32_t>(), (int32_t *)S.sptr, &cols, di, s))) return fail(rc);
     int cap = kNoCap;
-    const bool padded = cols * kSlice > nnz + nnz / 10 && n > kSlice;
+    const bool padded = much_padding(cols, nnz, n);
     if (top) {
         const int forced = (int)option(AFSAI_OPT_SELL_WIDTH);
         if (forced > 0) {
@@ -728,6 +748,127 @@ int sell_group_runs(Sell *S, const DeviceInfo &di, hipStream_t s, bool keep_col)
         S->col = nullptr;
     }
     S->col3 = c3;
+    return AFSAI_OK;
+}
+
+// ---------------------------------------------------------------------------------------
+// 3 x 3 blocks
+// ---------------------------------------------------------------------------------------
+// whether the three rows of every node hold the same aligned runs of three columns (32 lanes a
+// node), and the blocks of each slice's widest node
+__global__ __launch_bounds__(256) void k_node_check(int nodes, const int32_t *__restrict__ rp,
+                                                    const int32_t *__restrict__ ci, int32_t *__restrict__ width,
+                                                    int32_t *__restrict__ bad) {
+    const int l = threadIdx.x & 31;
+    for (int a = (blockIdx.x * blockDim.x + threadIdx.x) >> 5; a < nodes; a += (gridDim.x * blockDim.x) >> 5) {
+        const int s0 = rp[3 * a], s1 = rp[3 * a + 1], s2 = rp[3 * a + 2], len = s1 - s0;
+        bool err = len < 0 || len % 3 != 0 || s2 - s1 != len || rp[3 * a + 3] - s2 != len;
+        if (!err)
+            for (int k = 3 * l; k < len; k += 96) {
+                const int c = ci[s0 + k];
+                err = err || c % 3 != 0;
+                for (int e = 0; e < 3; ++e) err = err || ci[s0 + k + e] != c + e || ci[s1 + k + e] != c + e || ci[s2 + k + e] != c + e;
+            }
+        if (err) *bad = 1;
+        if (l == 0) atomicMax(&width[a / kSlice], len / 3);
+    }
+}
+
+// One block of 256 threads per slice of 64 nodes: its 192 rows are staged through LDS eight runs at
+// a time (192-byte pieces of the rows in, 512-byte stores out).  A padding block's column is -1 less
+// three bits: the rows of the node that the plain slices of 64 rows (`plain`) pad with zero times
+// x of the row, so that an infinite x leaves the same NaN here.
+__global__ __launch_bounds__(256) void k_node_fill(int nodes, int nslices, bool plain, const int32_t *__restrict__ rp,
+                                                   const int32_t *__restrict__ ci, const double *__restrict__ val,
+                                                   const int32_t *__restrict__ bptr, int32_t *__restrict__ bcol,
+                                                   double *__restrict__ bval) {
+    constexpr int R = 8, W = 3 * R, ROWS = 3 * kSlice;
+    __shared__ double lv[ROWS][W + 1];
+    __shared__ int32_t st[ROWS + 1], wide[3], flag[kSlice];
+    for (int sl = blockIdx.x; sl < nslices; sl += gridDim.x) {
+        const int a0 = sl * kSlice, na = min(kSlice, nodes - a0);
+        for (int t = threadIdx.x; t <= 3 * na; t += blockDim.x) st[t] = rp[3 * a0 + t];
+        if (threadIdx.x < 3) wide[threadIdx.x] = 0;
+        __syncthreads();
+        for (int t = threadIdx.x; t < 3 * na; t += blockDim.x) atomicMax(&wide[t / kSlice], st[t + 1] - st[t]);
+        __syncthreads();
+        for (int t = threadIdx.x; t < kSlice; t += blockDim.x) {
+            int f = 0;
+            for (int d = 0; d < 3; ++d)
+                if (plain && t < na && st[3 * t + d + 1] - st[3 * t + d] < wide[(3 * t + d) / kSlice]) f |= 1 << d;
+            flag[t] = f;
+        }
+        __syncthreads();
+        const int b0 = bptr[sl], nb = bptr[sl + 1] - b0;
+        for (int j0 = 0; j0 < nb; j0 += R) {
+            for (int t = threadIdx.x; t < ROWS * W; t += blockDim.x) {
+                const int r = t / W, k = t - r * W;
+                lv[r][k] = (r < 3 * na && 3 * j0 + k < st[r + 1] - st[r]) ? val[(int64_t)st[r] + 3 * j0 + k] : 0.0;
+            }
+            __syncthreads();
+            const int jn = min(R, nb - j0);
+            for (int t = threadIdx.x; t < jn * 9 * kSlice; t += blockDim.x) {
+                const int l = t % kSlice, q = t / kSlice, j = q / 9, d = (q % 9) / 3, e = q % 3;
+                bval[((int64_t)(b0 + j0) * 9 + q) * kSlice + l] = lv[3 * l + d][3 * j + e];
+            }
+            for (int t = threadIdx.x; t < jn * kSlice; t += blockDim.x) {
+                const int l = t % kSlice, j = j0 + t / kSlice;
+                int c = -1 - flag[l];
+                if (l < na && 3 * j < st[3 * l + 1] - st[3 * l]) c = ci[(int64_t)st[3 * l] + 3 * j];
+                bcol[(int64_t)(b0 + j) * kSlice + l] = c;
+            }
+            __syncthreads();
+        }
+    }
+}
+
+int sell_node_blocks(int n, int64_t nnz, const int32_t *rp, const int32_t *ci, const double *val, Sell *S,
+                     const DeviceInfo &di, hipStream_t s) {
+    if (n % 3 != 0 || nnz % 9 != 0) return AFSAI_OK;
+    const int nodes = n / 3, nsl = (nodes + kSlice - 1) / kSlice;
+    DevBuf width;  // of each slice, then the mark of a matrix that does not qualify
+    int rc;
+    if ((rc = dalloc(width, sizeof(int32_t) * ((size_t)nsl + 1), s))) return rc;
+    std::vector<int32_t> zero((size_t)nsl + 1, 0);
+    AFSAI_HIP_TRY(hipMemcpyAsync(width.p, zero.data(), sizeof(int32_t) * zero.size(), hipMemcpyHostToDevice, s));
+    hipLaunchKernelGGL(k_node_check, dim3(grid1d((int64_t)nodes * 32, di)), dim3(256), 0, s, nodes, rp, ci,
+                       width.as<int32_t>(), width.as<int32_t>() + nsl);
+    int32_t bad = 1;
+    AFSAI_HIP_TRY(hipMemcpyAsync(&bad, width.as<int32_t>() + nsl, sizeof bad, hipMemcpyDeviceToHost, s));
+    AFSAI_HIP_TRY(hipStreamSynchronize(s));
+    AFSAI_HIP_TRY(hipGetLastError());
+    if (bad) return AFSAI_OK;
+    uint32_t *bptr = (uint32_t *)pool_alloc(sizeof(uint32_t) * ((size_t)nsl + 1));
+    int64_t blocks = 0;
+    if (!bptr) return AFSAI_OK;
+    if ((rc = scan_counts(nsl, width.as<int32_t>(), (int32_t *)bptr, &blocks, di, s))) {
+        pool_free(bptr);
+        return rc;
+    }
+    int32_t *bcol = nullptr;
+    double *bval = nullptr;
+    if (blocks > 0 && blocks < ((int64_t)1 << 31)) {
+        bcol = (int32_t *)pool_alloc(sizeof(int32_t) * (size_t)blocks * kSlice);
+        bval = bcol ? (double *)pool_alloc(sizeof(double) * 9 * (size_t)blocks * kSlice) : nullptr;
+    }
+    if (!bval) {
+        pool_free(bptr);
+        pool_free(bcol);
+        return AFSAI_OK;
+    }
+    hipLaunchKernelGGL(k_node_fill, dim3(std::min(nsl, di.num_cus * 16)), dim3(256), 0, s, nodes, nsl, !S->lens, rp, ci, val,
+                       (const int32_t *)bptr, bcol, bval);
+    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
+        pool_free(bptr);
+        pool_free(bcol);
+        pool_free(bval);
+        return set_error_code(AFSAI_ERR_HIP, "SELL blocks: conversion failed");
+    }
+    S->n = n;
+    S->bptr = bptr;
+    S->bcol = bcol;
+    S->bval = bval;
+    S->bentries = blocks * 9 * kSlice;
     return AFSAI_OK;
 }
 

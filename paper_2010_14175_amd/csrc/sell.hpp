@@ -48,6 +48,13 @@ struct Sell {
                                 // rows of a slice marked in init are consecutive tail rows)
     int32_t *srow0 = nullptr;   // [nslices + 1] first row of each slice (nullptr: 64 * slice);
                                 // set when slices follow the systems of a batch
+    // the same matrix in 3 x 3 blocks (sell_node_blocks; nullptr: none): slices of 64 nodes (rows 3a,
+    // 3a+1, 3a+2), block j of a slice with one column index per node and its nine values row by
+    // row, each 64 nodes wide
+    uint32_t *bptr = nullptr;   // [ceil(n / 192) + 1] offsets in blocks
+    int32_t *bcol = nullptr;    // [bptr[last] * 64] first column of each block (negative: padding)
+    double *bval = nullptr;     // [bptr[last] * 9 * 64]
+    int64_t bentries = 0;       // entries of bval
     bool f32 = false;
     int64_t entries = 0;        // stored entries including padding (tail included)
     int width_cap = 0;          // entries per row held by the slices (0: all)
@@ -79,5 +86,14 @@ void sell_free(Sell *S);
 // not qualify.  With keep_col the per-entry columns stay beside the run indices (for kernels
 // that read them, such as the block products of a prepared matrix).  Synchronous on s.
 int sell_group_runs(Sell *S, const DeviceInfo &di, hipStream_t s, bool keep_col = false);
+// Whether the layout of a CSR matrix would order its rows by length (padding above a tenth of the
+// entries).  Synchronous on s.
+int sell_ordered(int n, int64_t nnz, const int32_t *rp, bool *ordered, const DeviceInfo &di, hipStream_t s);
+// Adds the 3 x 3 block form of a CSR matrix (device arrays, FP64) to S when the matrix is made of
+// such blocks: aligned runs of three columns, the same in the three rows of a node.  Leaves S
+// without it when the matrix does not qualify or the memory for it is not there.  Sets S->n.
+// Synchronous on s.
+int sell_node_blocks(int n, int64_t nnz, const int32_t *rp, const int32_t *ci, const double *val, Sell *S,
+                     const DeviceInfo &di, hipStream_t s);
 
 }  // namespace afsai

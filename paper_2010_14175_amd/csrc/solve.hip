@@ -1242,10 +1242,26 @@ static void sell_fused(const char *name, const Sell &S, const BatchMaps &bm, con
         launch_fused_v<double, MODE>(S, un, va, vb, own, x, pn, y, partials, fs, first, bm, di.num_xcds, s);
 }
 
+struct MultiScal {
+    double bb, rho, alpha, beta, rr, tr;
+    int32_t done, iters, status, pad;
+};
+
+// every column of the block has stopped (sc null: there are no columns to ask)
+template <int K>
+__device__ __forceinline__ bool all_stopped(const MultiScal *sc) {
+    if (!sc) return false;
+    int done = 1;
+#pragma unroll
+    for (int j = 0; j < K; ++j) done &= sc[j].done;
+    return done != 0;
+}
+
 // Y = A X for K vectors stored row by row (entry (i, j) at i * K + j): one wavefront per
 // SELL-64 slice, one lane per row; every matrix entry is read once for the K vectors and the
 // K values of a gathered row are contiguous.  Each output is the same sequential chain over
-// the row's entries as in the single-vector product.
+// the row's entries as in the single-vector product.  sc given: nothing is done when every column
+// has stopped.
 template <int K, typename VT, bool DOT = false>
 __global__ __launch_bounds__(kThreads) void k_sell_spmm(int n, int nslices, const uint32_t *__restrict__ sptr,
                                                          const int32_t *__restrict__ perm,
@@ -1253,8 +1269,9 @@ __global__ __launch_bounds__(kThreads) void k_sell_spmm(int n, int nslices, cons
                                                          const int32_t *__restrict__ col,
                                                          const VT *__restrict__ val, const double *__restrict__ x,
                                                          double *__restrict__ y, int nxcd,
-                                                         const double *__restrict__ w = nullptr,
-                                                         double *__restrict__ partials = nullptr) {
+                                                         const double *__restrict__ w, double *__restrict__ partials,
+                                                         const MultiScal *sc) {
+    if (all_stopped<K>(sc)) return;
     constexpr int U = K <= 2 ? 8 : 4;  // entries in flight per lane (fewer for wide blocks: registers)
     __shared__ double sh[kThreads / 64];
     double part[K];
@@ -1347,8 +1364,9 @@ __global__ __launch_bounds__(kThreads) void k_sell_spmm_runs(int n, int nslices,
                                                               const int32_t *__restrict__ col3,
                                                               const double *__restrict__ val,
                                                               const double *__restrict__ x, double *__restrict__ y,
-                                                              int nxcd, const double *__restrict__ w = nullptr,
-                                                              double *__restrict__ partials = nullptr) {
+                                                              int nxcd, const double *__restrict__ w,
+                                                              double *__restrict__ partials, const MultiScal *sc) {
+    if (all_stopped<K>(sc)) return;
     constexpr int UR = K <= 2 ? 3 : 1;  // runs in flight per lane (9 or 3 entries)
     __shared__ double sh[kThreads / 64];
     double part[K];
@@ -1430,16 +1448,121 @@ __global__ __launch_bounds__(kThreads) void k_sell_spmm_runs(int n, int nslices,
     }
 }
 
+// Block product over A in 3 x 3 blocks (sell_node_blocks): a lane takes the three rows of a node (L
+// lanes share a node, K / L columns each), so that one gathered block row of X serves nine
+// entries.  The products with a lane per row are bound by the bytes the L1 returns: 64 gathered
+// bytes per entry for K = 8; here 21, and 8.4 bytes of matrix instead of 9.3 or 12.  K = 8 at 680,943
+// rows (54 M entries): 231 -> 187 us, 2.5 TB/s of matrix; L = 1 spills and L = 4 takes 249 us (the
+// columns and values come four times); four lanes on one row with two columns each, 423 us.  Per
+// column and row the sum is the chain of k_sell_spmm_runs: Y is identical bit for bit.
+template <int K, int L>
+__global__ __launch_bounds__(kThreads) void k_node_spmm(int n, int nslices, const uint32_t *__restrict__ bptr,
+                                                        const int32_t *__restrict__ bcol,
+                                                        const double *__restrict__ bval, const double *__restrict__ x,
+                                                        double *__restrict__ y, int nxcd, const MultiScal *sc) {
+    constexpr int C = K / L;
+    if (all_stopped<K>(sc)) return;
+    const int lb = xcd_block(blockIdx.x, gridDim.x, nxcd);
+    const int wv = wave_index(), lane = threadIdx.x & 63;
+    int w0, w1, wstep;
+    window_walk((nslices * L + kWin - 1) / kWin, lb, gridDim.x, nxcd, w0, w1, wstep);
+    for (int wi = w0; wi < w1; wi += wstep) {
+        const int unit = wi * kWin + wv, sl = unit / L;
+        if (sl >= nslices) break;
+        const int l = (unit % L) * (64 / L) + lane / L;  // node of the slice
+        const int r = 3 * (sl * kSlice + l);
+        const int b0 = (int)bptr[sl], b1 = (int)bptr[sl + 1];
+        const double *xj = x + (lane % L) * C;
+        double acc[3][C];
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+#pragma unroll
+            for (int j = 0; j < C; ++j) acc[d][j] = 0.0;
+        // the next block's index and values are loaded behind this one's gathers
+        int c = 0, cn;
+        double v[9], vn[9];
+        if (b0 < b1) {
+            c = __builtin_nontemporal_load(&bcol[(int64_t)b0 * kSlice + l]);
+#pragma unroll
+            for (int q = 0; q < 9; ++q) v[q] = __builtin_nontemporal_load(&bval[((int64_t)b0 * 9 + q) * kSlice + l]);
+        }
+        cn = c;
+        for (int b = b0; b < b1; ++b) {
+            const double *xc = xj + (int64_t)(c < 0 ? 0 : c) * K;
+            double xv[3][C];
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+#pragma unroll
+                for (int j = 0; j < C; ++j) xv[e][j] = xc[e * K + j];
+            if (b + 1 < b1) {
+                cn = __builtin_nontemporal_load(&bcol[(int64_t)(b + 1) * kSlice + l]);
+#pragma unroll
+                for (int q = 0; q < 9; ++q) vn[q] = __builtin_nontemporal_load(&bval[((int64_t)(b + 1) * 9 + q) * kSlice + l]);
+            }
+            if (c >= 0) {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+#pragma unroll
+                    for (int d = 0; d < 3; ++d)
+#pragma unroll
+                        for (int j = 0; j < C; ++j) acc[d][j] = fma(v[3 * d + e], xv[e][j], acc[d][j]);
+            }
+            c = cn;
+#pragma unroll
+            for (int q = 0; q < 9; ++q) v[q] = vn[q];
+        }
+        // the zeros times x that the rows' plain slices hold (k_node_fill)
+        if (c < -1)
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+                if ((-1 - c) >> d & 1)
+#pragma unroll
+                    for (int j = 0; j < C; ++j) acc[d][j] = fma(0.0, xj[(int64_t)(r + d) * K + j], acc[d][j]);
+        if (r < n)
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+#pragma unroll
+                for (int j = 0; j < C; ++j) y[(int64_t)(r + d) * K + (lane % L) * C + j] = acc[d][j];
+    }
+}
+
+// per column the partial sums of y.w over the windows of 256 rows, in the order of k_sell_spmm's dots
+template <int K>
+__global__ __launch_bounds__(kThreads) void k_window_dot(int n, int nslices, const double *__restrict__ y,
+                                                         const double *__restrict__ w, double *__restrict__ partials,
+                                                         int nxcd, const MultiScal *sc) {
+    __shared__ double sh[kThreads / 64];
+    if (all_stopped<K>(sc)) return;
+    double part[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) part[j] = 0.0;
+    const int lb = xcd_block(blockIdx.x, gridDim.x, nxcd);
+    int w0, w1, wstep;
+    window_walk((nslices + kWin - 1) / kWin, lb, gridDim.x, nxcd, w0, w1, wstep);
+    for (int wi = w0; wi < w1; wi += wstep) {
+        const int r = wi * kWin * kSlice + threadIdx.x;
+        if (r < n)
+#pragma unroll
+            for (int j = 0; j < K; ++j) part[j] = fma(y[(int64_t)r * K + j], w[(int64_t)r * K + j], part[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+        const double bs = block_sum(part[j], sh);
+        if (threadIdx.x == 0) partials[(size_t)j * gridDim.x + lb] = bs;
+    }
+}
+
 // ---------------------------------------------------------------------------------------
 // PCG over a block of K right-hand sides (x0 = 0): K independent recurrences with their own
 // scalars and stopping tests; the vectors are n x K row-major blocks and every product reads
 // its matrix once for the K columns.
 // ---------------------------------------------------------------------------------------
-struct MultiScal {
-    double bb, rho, alpha, beta, rr, tr;
-    int32_t done, iters, status, pad;
-};
 enum : int { MF_BB = 0, MF_RHO0 = 1, MF_PQ = 2, MF_RR = 3, MF_RZ = 4, MF_TRUE = 5 };
+
+// the columns' scalars into pinned host memory
+__global__ void k_multi_publish(int k, const MultiScal *__restrict__ sc, MultiScal *__restrict__ host) {
+    if ((int)threadIdx.x < k) host[threadIdx.x] = sc[threadIdx.x];
+}
 
 // One block per column: the column's partial sums (nb per column) added in block order, then
 // the scalar step of the textbook recurrence for that column.
@@ -1569,6 +1692,7 @@ __global__ __launch_bounds__(kThreads) void k_multi_xr(int n, double *__restrict
                                                         const double *__restrict__ p, const double *__restrict__ q,
                                                         const MultiScal *__restrict__ sc, double *__restrict__ partials) {
     __shared__ double sh[kThreads / 64 * K];
+    if (all_stopped<K>(sc)) return;
     int64_t e0, e1;
     multi_range<K>(n, e0, e1);
     const int j = threadIdx.x % K;
@@ -1616,16 +1740,25 @@ __global__ __launch_bounds__(kThreads) void k_multi_resid(int n, const double *_
 
 template <int K, bool DOT>
 static void spmm_launch(const Sell &S, const double *x, double *y, const double *w, double *partials, int nb,
-                        const DeviceInfo &di, hipStream_t s) {
-    if (S.col3 && !S.f32 && !S.lens)
-        hipLaunchKernelGGL((k_sell_spmm_runs<K, DOT>), dim3(nb), dim3(kThreads), 0, s, S.n, S.nslices, S.sptr, S.col3,
-                           (const double *)S.val, x, y, di.num_xcds, w, partials);
+                          const DeviceInfo &di, hipStream_t s, const MultiScal *sc = nullptr) {
+    const dim3 bt(kThreads);
+    if (S.bptr) {
+        constexpr int L = K >= 8 ? 2 : 1;
+        const int nsl = (S.n / 3 + kSlice - 1) / kSlice;
+        hipLaunchKernelGGL((k_node_spmm<K, L>), dim3(blocks_for_slices(nsl * L, di)), bt, 0, s, S.n, nsl, S.bptr,
+                           S.bcol, S.bval, x, y, di.num_xcds, sc);
+        if (DOT)
+            hipLaunchKernelGGL((k_window_dot<K>), dim3(nb), bt, 0, s, S.n, (S.n + kSlice - 1) / kSlice, y, w, partials,
+                               di.num_xcds, sc);
+    } else if (S.col3 && !S.f32 && !S.lens)
+        hipLaunchKernelGGL((k_sell_spmm_runs<K, DOT>), dim3(nb), bt, 0, s, S.n, S.nslices, S.sptr, S.col3,
+                           (const double *)S.val, x, y, di.num_xcds, w, partials, sc);
     else if (S.f32)
-        hipLaunchKernelGGL((k_sell_spmm<K, float, DOT>), dim3(nb), dim3(kThreads), 0, s, S.n, S.nslices, S.sptr, S.perm,
-                           S.lens, S.col, (const float *)S.val, x, y, di.num_xcds, w, partials);
+        hipLaunchKernelGGL((k_sell_spmm<K, float, DOT>), dim3(nb), bt, 0, s, S.n, S.nslices, S.sptr, S.perm, S.lens,
+                           S.col, (const float *)S.val, x, y, di.num_xcds, w, partials, sc);
     else
-        hipLaunchKernelGGL((k_sell_spmm<K, double, DOT>), dim3(nb), dim3(kThreads), 0, s, S.n, S.nslices, S.sptr, S.perm,
-                           S.lens, S.col, (const double *)S.val, x, y, di.num_xcds, w, partials);
+        hipLaunchKernelGGL((k_sell_spmm<K, double, DOT>), dim3(nb), bt, 0, s, S.n, S.nslices, S.sptr, S.perm, S.lens,
+                           S.col, (const double *)S.val, x, y, di.num_xcds, w, partials, sc);
 }
 
 static int check_csr_arg(const afsai_csr *A, const char *who) {
@@ -2268,20 +2401,30 @@ static int pcg_multi(const afsai_csr *A, afsai_precond P, const double *B, doubl
     const int n = A->n;
     int rc;
     Sell SA;
-    {
-        ProfScope ps("sell_A", s);
-        if ((rc = sell_from_csr(n, A->nnz, A->row_ptr, A->col_idx, A->val, false, false, &SA, di, s))) return rc;
-    }
     struct Free {
         Sell *S;
         ~Free() { sell_free(S); }
     } free_sa{&SA};
-    if (SA.tail) AFSAI_FAIL(AFSAI_ERR_INVALID_ARG, "pcg_solve_multi: split SELL layouts are not supported");
-    if (option(AFSAI_OPT_SELL_RUNS) != 1) {
-        ProfScope ps("sell_A_runs", s);
-        if ((rc = sell_group_runs(&SA, di, s))) return rc;
+    if (option(AFSAI_OPT_SELL_RUNS) != 1 && option(AFSAI_OPT_SELL_WIDTH) == 0 && n % 3 == 0) {
+        // 3 x 3 blocks, unless the rows would be ordered by length (the dots of that layout are
+        // summed in another order)
+        ProfScope ps("sell_A_blocks", s);
+        bool ordered = true;
+        if ((rc = sell_ordered(n, A->nnz, A->row_ptr, &ordered, di, s))) return rc;
+        if (!ordered && (rc = sell_node_blocks(n, A->nnz, A->row_ptr, A->col_idx, A->val, &SA, di, s))) return rc;
     }
-    const int nbA = blocks_for_slices(SA.nslices, di), nbv = blocks_for_vec(n, di);
+    if (!SA.bptr) {
+        {
+            ProfScope ps("sell_A", s);
+            if ((rc = sell_from_csr(n, A->nnz, A->row_ptr, A->col_idx, A->val, false, false, &SA, di, s))) return rc;
+        }
+        if (SA.tail) AFSAI_FAIL(AFSAI_ERR_INVALID_ARG, "pcg_solve_multi: split SELL layouts are not supported");
+        if (option(AFSAI_OPT_SELL_RUNS) != 1) {
+            ProfScope ps("sell_A_runs", s);
+            if ((rc = sell_group_runs(&SA, di, s))) return rc;
+        }
+    }
+    const int nbA = blocks_for_slices((n + kSlice - 1) / kSlice, di), nbv = blocks_for_vec(n, di);
     const int nbG = P ? blocks_for_slices(P->sg.nslices, di) : 0;
     const int nbGT = P ? blocks_for_slices(P->sgt.nslices, di) : 0;
     const int nbmax = std::max(std::max(nbA, nbv), std::max(nbG, nbGT));
@@ -2297,47 +2440,63 @@ static int pcg_multi(const afsai_csr *A, afsai_precond P, const double *B, doubl
         hipLaunchKernelGGL(k_fin_multi, dim3(K), dim3(kThreads), 0, s, pa, nb, mode, rtol, (int)maxit, sc);
     };
     // Z = M R with partial sums of R.Z; returns the blocks of that launch
-    auto precond = [&]() {
+    auto precond = [&](const MultiScal *gate) {
         if (P) {
-            spmm_launch<K, false>(P->sg, R, T, nullptr, nullptr, nbG, di, s);
-            spmm_launch<K, true>(P->sgt, T, Z, R, pa, nbGT, di, s);
+            spmm_launch<K, false>(P->sg, R, T, nullptr, nullptr, nbG, di, s, gate);
+            spmm_launch<K, true>(P->sgt, T, Z, R, pa, nbGT, di, s, gate);
             return nbGT;
         }
         hipLaunchKernelGGL((k_multi_dot<K>), dim3(nbv), dim3(kThreads), 0, s, n, R, R, Z, pa);
         return nbv;
     };
-    std::vector<MultiScal> h(K);
-    auto read = [&]() -> int {
-        AFSAI_HIP_TRY(hipGetLastError());
-        AFSAI_HIP_TRY(hipMemcpyAsync(h.data(), sc, sizeof(MultiScal) * K, hipMemcpyDeviceToHost, s));
-        AFSAI_HIP_TRY(hipStreamSynchronize(s));
-        return AFSAI_OK;
-    };
-    auto all_done = [&]() {
-        for (int j = 0; j < K; ++j)
-            if (!h[j].done) return false;
-        return true;
-    };
+    // the scalars after each iteration, in pinned host memory (two slots in turn)
+    struct Host {
+        MultiScal *h = nullptr, *d = nullptr;
+        hipEvent_t ev[2] = {nullptr, nullptr};
+        hipStream_t s;
+        ~Host() {
+            (void)hipStreamSynchronize(s);
+            for (hipEvent_t e : ev)
+                if (e) (void)hipEventDestroy(e);
+            pinned_free(h);
+        }
+    } host;
+    host.s = s;
+    host.h = (MultiScal *)pinned_alloc(2 * K * sizeof(MultiScal));
+    if (!host.h) return set_error_code(AFSAI_ERR_NO_MEMORY, "pcg_solve_multi: out of pinned host memory");
+    AFSAI_HIP_TRY(hipHostGetDevicePointer((void **)&host.d, host.h, 0));
+    for (hipEvent_t &e : host.ev) AFSAI_HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     hipLaunchKernelGGL((k_multi_init<K>), dim3(nbv), dim3(kThreads), 0, s, n, B, X, R, pa);
     fin(nbv, MF_BB);
-    fin(precond(), MF_RHO0);
+    fin(precond(nullptr), MF_RHO0);
     AFSAI_HIP_TRY(hipMemcpyAsync(Pv, Z, sizeof(double) * blk, hipMemcpyDeviceToDevice, s));
-    if ((rc = read())) return rc;
-    for (int it = 0; it < maxit && !all_done(); ++it) {
-        spmm_launch<K, true>(SA, Pv, Q, Pv, pa, nbA, di, s);
+    // The host reads the scalars one iteration behind (waiting for each iteration before the next
+    // left the GPU idle for about 45 us of 300 at 250,000 rows); the iteration that is then queued past the
+    // last column's end returns at once
+    for (int it = 0; it < maxit; ++it) {
+        spmm_launch<K, true>(SA, Pv, Q, Pv, pa, nbA, di, s, sc);
         fin(nbA, MF_PQ);
         hipLaunchKernelGGL((k_multi_xr<K>), dim3(nbv), dim3(kThreads), 0, s, n, X, R, Pv, Q, sc, pa);
         fin(nbv, MF_RR);
-        if ((rc = read())) return rc;
-        if (all_done()) break;
-        fin(precond(), MF_RZ);
+        fin(precond(sc), MF_RZ);
         hipLaunchKernelGGL((k_multi_p<K>), dim3(nbv), dim3(kThreads), 0, s, n, Z, Pv, sc);
+        hipLaunchKernelGGL(k_multi_publish, dim3(1), dim3(64), 0, s, K, sc, host.d + (it & 1) * K);
+        AFSAI_HIP_TRY(hipGetLastError());
+        AFSAI_HIP_TRY(hipEventRecord(host.ev[it & 1], s));
+        if (it == 0) continue;
+        AFSAI_HIP_TRY(hipEventSynchronize(host.ev[(it - 1) & 1]));
+        bool all = true;
+        for (int j = 0; j < K; ++j) all = all && host.h[((it - 1) & 1) * K + j].done;
+        if (all) break;
     }
     // true residuals ||b - A x|| per column
     spmm_launch<K, false>(SA, X, Q, nullptr, nullptr, nbA, di, s);
     hipLaunchKernelGGL((k_multi_resid<K>), dim3(nbv), dim3(kThreads), 0, s, n, B, Q, pa);
     fin(nbv, MF_TRUE);
-    if ((rc = read())) return rc;
+    std::vector<MultiScal> h(K);
+    AFSAI_HIP_TRY(hipGetLastError());
+    AFSAI_HIP_TRY(hipMemcpyAsync(h.data(), sc, sizeof(MultiScal) * K, hipMemcpyDeviceToHost, s));
+    AFSAI_HIP_TRY(hipStreamSynchronize(s));
     int worst = AFSAI_OK;
     for (int j = 0; j < K; ++j) {
         const MultiScal &m = h[j];
@@ -2458,6 +2617,9 @@ int afsai_matrix_prepare(const afsai_csr *A, void *stream, afsai_matrix *out) {
         // run indices for pcg_solve_prepared's products, the per-entry columns kept for the
         // block products
         if (rc == AFSAI_OK && option(AFSAI_OPT_SELL_RUNS) != 1) rc = sell_group_runs(&M->S, di, s, true);
+        // and 3 x 3 blocks for the block products
+        if (rc == AFSAI_OK && option(AFSAI_OPT_SELL_RUNS) != 1)
+            rc = sell_node_blocks(A->n, A->nnz, A->row_ptr, A->col_idx, A->val, &M->S, di, s);
     }
     if (rc == AFSAI_OK && hipStreamSynchronize(s) != hipSuccess) rc = set_error_code(AFSAI_ERR_HIP, "afsai_matrix_prepare: synchronisation failed");
     if (rc != AFSAI_OK) {

@@ -1065,3 +1065,36 @@ def test_pcg_one_launch_continued(af):
         af.set_option(af.OPT_PCG_FORM, 0)
     assert i.iters == j.iters and i.iters > 1024 and i.converged and i.true_relres == j.true_relres
     np.testing.assert_array_equal(x.cpu().numpy().view(np.int64), y.cpu().numpy().view(np.int64))
+
+
+@pytest.mark.parametrize("make", [
+    lambda: _node_blocks(2, 1, 1), lambda: _node_blocks(22, 1, 2), lambda: _node_blocks(65, 2, 3),
+    lambda: synth.elast27(4, 1.0, 4), lambda: synth.elast27(7, 2.0, 5), lambda: _node_blocks(700, 6, 6),
+    lambda: synth.random_sparse_spd(300, 5, 7)])
+def test_block_products_of_nodes(af, make):
+    """Products and multi-right-hand-side solves over 3 x 3 blocks (two nodes, a slice of 64 nodes and
+    one more, ragged rows, rows ordered by length, a matrix that is not made of such blocks) equal the
+    layouts of single entries bit for bit, also where X holds infinities."""
+    import torch
+
+    A = make()
+    dA = _dev(af, A)
+    M = af.PreparedMatrix(dA)
+    X8 = synth.uniform(19, 5, A.n * 8, -1.0, 1.0).reshape(A.n, 8)
+    I8 = X8.copy()
+    I8[::7, ::3] = np.inf
+    P = af.setup(dA, 3, 1, 1e-2)
+    for k in (1, 2, 4, 8):
+        for X in (X8, I8):
+            Xk = torch.from_numpy(np.ascontiguousarray(X[:, :k])).cuda()
+            np.testing.assert_array_equal(M.spmm(Xk).cpu().numpy(), af.spmm(dA, Xk).cpu().numpy())
+        B = torch.from_numpy(np.ascontiguousarray(X8[:, :k])).cuda()
+        Y, iy = af.pcg_solve_multi(dA, P, B, rtol=1e-9)
+        try:
+            af.set_option(af.OPT_SELL_RUNS, 1)
+            Z, iz = af.pcg_solve_multi(dA, P, B, rtol=1e-9)
+        finally:
+            af.set_option(af.OPT_SELL_RUNS, 0)
+        assert [(i.iters, i.status, i.relres) for i in iy] == [(i.iters, i.status, i.relres) for i in iz]
+        np.testing.assert_array_equal(Y.cpu().numpy(), Z.cpu().numpy())
+    M.close()
