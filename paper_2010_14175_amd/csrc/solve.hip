@@ -365,11 +365,19 @@ __device__ __forceinline__ void window_walk(int nw, int lb, int nb, int nxcd, in
     step = cnt;
 }
 
+// A load of the matrix stream: NT (non-temporal) for matrices that no cache holds until the next
+// iteration, so that they leave the gathered vectors in the L2
+template <bool NT, typename T>
+__device__ __forceinline__ T ldm(const T *p) {
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+
 // One lane's sum over `len` entries stored `stride` apart from base, continuing acc: one
 // sequential fma chain in stored order.  Software pipeline: the columns and values of the
 // next U entries are loaded before the gathers of the current U, so one round trip to memory
 // serves both.
-template <int U, int STRIDE, typename VT>
+template <int U, int STRIDE, bool NT, typename VT>
 __device__ __forceinline__ double lane_chain(const int32_t *__restrict__ col, const VT *__restrict__ val,
                                              const double *__restrict__ x, int64_t base, int len, double acc) {
     int c[U];
@@ -380,8 +388,8 @@ __device__ __forceinline__ double lane_chain(const int32_t *__restrict__ col, co
         v[u] = VT(0);
         if (u < len) {
             const int64_t d = base + (int64_t)u * STRIDE;
-            c[u] = __builtin_nontemporal_load(&col[d]);
-            v[u] = __builtin_nontemporal_load(&val[d]);
+            c[u] = ldm<NT>(&col[d]);
+            v[u] = ldm<NT>(&val[d]);
         }
     }
     for (int k0 = 0; k0 < len; k0 += U) {
@@ -393,8 +401,8 @@ __device__ __forceinline__ double lane_chain(const int32_t *__restrict__ col, co
             vn[u] = VT(0);
             if (k0 + U + u < len) {
                 const int64_t d = base + (int64_t)(k0 + U + u) * STRIDE;
-                cn[u] = __builtin_nontemporal_load(&col[d]);
-                vn[u] = __builtin_nontemporal_load(&val[d]);
+                cn[u] = ldm<NT>(&col[d]);
+                vn[u] = ldm<NT>(&val[d]);
             }
         }
         double xv[U];
@@ -419,7 +427,7 @@ __device__ __forceinline__ double lane_chain(const int32_t *__restrict__ col, co
 // its wavefronts taking the slices in turn, and the sums reach their natural rows through LDS,
 // so that y is written and the dot summed in row order.  The ordered instance keeps twice as many entries in flight
 // (its gathers are scattered over the window's rows and wait longest).
-template <int U, typename VT, bool DOT, bool ORD = false>
+template <int U, typename VT, bool DOT, bool NT, bool ORD = false>
 __global__ __launch_bounds__(kThreads) void k_sell_spmv(int n, int nslices, const uint32_t *__restrict__ sptr,
                                                          const int32_t *__restrict__ srow0,
                                                          const int32_t *__restrict__ perm,
@@ -467,7 +475,7 @@ __global__ __launch_bounds__(kThreads) void k_sell_spmv(int n, int nslices, cons
                 const int r = perm[li];
                 const int len = lens[li];
                 const int64_t base = (int64_t)sptr[sl] * kSlice + lane;
-                const double acc = lane_chain<UO, kSlice>(col, val, x, base, len, 0.0);
+                const double acc = lane_chain<UO, kSlice, NT>(col, val, x, base, len, 0.0);
                 if (r >= 0) sy_win[r - wr0] = acc;
             }
             __syncthreads();
@@ -521,7 +529,7 @@ __global__ __launch_bounds__(kThreads) void k_sell_spmv(int n, int nslices, cons
                 acc = y[ro];
             }
         }
-        acc = lane_chain<U, kSlice>(col, val, x, base, width, acc);
+        acc = lane_chain<U, kSlice, NT>(col, val, x, base, width, acc);
         if (valid) {
             y[ro] = acc;
             if (DOT) part = fma(acc, w[ro], part);
@@ -537,7 +545,7 @@ __global__ __launch_bounds__(kThreads) void k_sell_spmv(int n, int nslices, cons
 // index per run): the values of run j are entries 3j..3j+2 of the lane, stored kSlice apart
 // from vbase, its first column at rbase + j * kSlice.  The same sequential fma chain over the
 // entries in stored order as lane_chain, with UR runs (3 UR entries) in flight.
-template <int UR, typename VT>
+template <int UR, bool NT, typename VT>
 __device__ __forceinline__ double run_chain(const int32_t *__restrict__ col3, const VT *__restrict__ val,
                                             const double *__restrict__ x, int64_t rbase, int64_t vbase, int nr,
                                             double acc) {
@@ -549,9 +557,9 @@ __device__ __forceinline__ double run_chain(const int32_t *__restrict__ col3, co
 #pragma unroll
         for (int e = 0; e < 3; ++e) v[u][e] = VT(0);
         if (u < nr) {
-            c[u] = __builtin_nontemporal_load(&col3[rbase + (int64_t)u * kSlice]);
+            c[u] = ldm<NT>(&col3[rbase + (int64_t)u * kSlice]);
 #pragma unroll
-            for (int e = 0; e < 3; ++e) v[u][e] = __builtin_nontemporal_load(&val[vbase + (int64_t)(3 * u + e) * kSlice]);
+            for (int e = 0; e < 3; ++e) v[u][e] = ldm<NT>(&val[vbase + (int64_t)(3 * u + e) * kSlice]);
         }
     }
     for (int j0 = 0; j0 < nr; j0 += UR) {
@@ -564,10 +572,10 @@ __device__ __forceinline__ double run_chain(const int32_t *__restrict__ col3, co
             for (int e = 0; e < 3; ++e) vn[u][e] = VT(0);
             if (j0 + UR + u < nr) {
                 const int j = j0 + UR + u;
-                cn[u] = __builtin_nontemporal_load(&col3[rbase + (int64_t)j * kSlice]);
+                cn[u] = ldm<NT>(&col3[rbase + (int64_t)j * kSlice]);
 #pragma unroll
                 for (int e = 0; e < 3; ++e)
-                    vn[u][e] = __builtin_nontemporal_load(&val[vbase + (int64_t)(3 * j + e) * kSlice]);
+                    vn[u][e] = ldm<NT>(&val[vbase + (int64_t)(3 * j + e) * kSlice]);
             }
         }
         double xv[UR][3];
@@ -594,7 +602,7 @@ __device__ __forceinline__ double run_chain(const int32_t *__restrict__ col3, co
 // SELL-64 product over the layout with one column index per run of three (plain layouts
 // only: natural row order, no split): the walk, row sums, stores and fused dot of k_sell_spmv,
 // so products and dots are identical to it bit for bit.
-template <int UR, typename VT, bool DOT>
+template <int UR, typename VT, bool DOT, bool NT>
 __global__ __launch_bounds__(kThreads) void k_sell_spmv_runs(int n, const uint32_t *__restrict__ sptr,
                                                              const int32_t *__restrict__ srow0,
                                                              const int32_t *__restrict__ col3,
@@ -620,7 +628,7 @@ __global__ __launch_bounds__(kThreads) void k_sell_spmv_runs(int n, const uint32
         const int r = r0 + lane;
         const uint32_t c0 = sptr[sl];
         const int nr = (int)(sptr[sl + 1] - c0) / 3;
-        const double acc = run_chain<UR, VT>(col3, val, x, (int64_t)(c0 / 3u) * kSlice + lane,
+        const double acc = run_chain<UR, NT, VT>(col3, val, x, (int64_t)(c0 / 3u) * kSlice + lane,
                                              (int64_t)c0 * kSlice + lane, nr, 0.0);
         if (r < r1) {
             y[r] = acc;
@@ -644,7 +652,7 @@ __global__ __launch_bounds__(kThreads) void k_sell_spmv_runs(int n, const uint32
 //             (pa: p.q)
 enum : int { FUSE_AP = 1, FUSE_GR = 2 };
 
-template <int U, typename VT, int MODE>
+template <int U, typename VT, int MODE, bool NT>
 __global__ __launch_bounds__(kThreads) void k_sell_fused(int n, int nslices, const uint32_t *__restrict__ sptr,
                                                           const int32_t *__restrict__ srow0,
                                                           const int32_t *__restrict__ col,
@@ -702,8 +710,8 @@ __global__ __launch_bounds__(kThreads) void k_sell_fused(int n, int nslices, con
             v[u] = VT(0);
             if (u < width) {
                 const int64_t d = base + (int64_t)u * kSlice;
-                c[u] = __builtin_nontemporal_load(&col[d]);
-                v[u] = __builtin_nontemporal_load(&val[d]);
+                c[u] = ldm<NT>(&col[d]);
+                v[u] = ldm<NT>(&val[d]);
             }
         }
         for (int k0 = 0; k0 < width; k0 += U) {
@@ -715,8 +723,8 @@ __global__ __launch_bounds__(kThreads) void k_sell_fused(int n, int nslices, con
                 vn[u] = VT(0);
                 if (k0 + U + u < width) {
                     const int64_t d = base + (int64_t)(k0 + U + u) * kSlice;
-                    cn[u] = __builtin_nontemporal_load(&col[d]);
-                    vn[u] = __builtin_nontemporal_load(&val[d]);
+                    cn[u] = ldm<NT>(&col[d]);
+                    vn[u] = ldm<NT>(&val[d]);
                 }
             }
             double xa[U], xb[U];
@@ -1038,6 +1046,7 @@ struct BatchMaps {
     int nsys = 1;
     Systems sy;
     Shape sell, vec;
+    bool nt = true;  // the matrix stream is larger than the caches
     DevBuf buf;
 };
 
@@ -1103,7 +1112,7 @@ static int make_batch_maps(int n, int nsys, const int32_t *row0, const DeviceInf
 }
 
 // fused: a split layout's tail runs inside the slices' product (else the caller launched it)
-template <int U, typename VT>
+template <int U, bool NT, typename VT>
 static void launch_sell_t(const Sell &S, const double *x, double *y, const double *w, double *partials,
                           PcgScalars *scs, const Map &mp, const Systems &sy, int nb, int nxcd, hipStream_t s,
                           bool fused, const double *rr) {
@@ -1116,62 +1125,74 @@ static void launch_sell_t(const Sell &S, const double *x, double *y, const doubl
         // runs of three: about as many entries in flight as U
         constexpr int UR = U >= 8 ? 3 : 1;
         if (w)
-            hipLaunchKernelGGL((k_sell_spmv_runs<UR, VT, true>), dim3(nb), dim3(kThreads), 0, s, S.n, S.sptr,
+            hipLaunchKernelGGL((k_sell_spmv_runs<UR, VT, true, NT>), dim3(nb), dim3(kThreads), 0, s, S.n, S.sptr,
                                S.srow0, S.col3, (const VT *)S.val, x, y, w, partials, scs, mp, sy, S.nslices, nxcd);
         else
-            hipLaunchKernelGGL((k_sell_spmv_runs<UR, VT, false>), dim3(nb), dim3(kThreads), 0, s, S.n, S.sptr,
+            hipLaunchKernelGGL((k_sell_spmv_runs<UR, VT, false, NT>), dim3(nb), dim3(kThreads), 0, s, S.n, S.sptr,
                                S.srow0, S.col3, (const VT *)S.val, x, y, w, partials, scs, mp, sy, S.nslices, nxcd);
         return;
     }
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(nb), dim3(kThreads), 0, s, S.n, S.nslices, S.sptr, S.srow0, S.perm, S.rowmap, S.init,
+                           S.col, (const VT *)S.val, x, y, w, partials, scs, mp, sy, nxcd, S.lens, S.wsl, S.wofs, tsp, tcl,
+                           tvl, tof, rr);
+    };
     if (S.lens) {
-        if (w)
-            hipLaunchKernelGGL((k_sell_spmv<U, VT, true, true>), dim3(nb), dim3(kThreads), 0, s, S.n, S.nslices,
-                               S.sptr, S.srow0, S.perm, S.rowmap, S.init, S.col, (const VT *)S.val, x, y, w, partials,
-                               scs, mp, sy, nxcd, S.lens, S.wsl, S.wofs, tsp, tcl, tvl, tof, rr);
-        else
-            hipLaunchKernelGGL((k_sell_spmv<U, VT, false, true>), dim3(nb), dim3(kThreads), 0, s, S.n, S.nslices,
-                               S.sptr, S.srow0, S.perm, S.rowmap, S.init, S.col, (const VT *)S.val, x, y, w, partials,
-                               scs, mp, sy, nxcd, S.lens, S.wsl, S.wofs, tsp, tcl, tvl, tof, rr);
-        return;
+        if (w) go(k_sell_spmv<U, VT, true, NT, true>);
+        else go(k_sell_spmv<U, VT, false, NT, true>);
+    } else {
+        if (w) go(k_sell_spmv<U, VT, true, NT>);
+        else go(k_sell_spmv<U, VT, false, NT>);
     }
-    if (w)
-        hipLaunchKernelGGL((k_sell_spmv<U, VT, true>), dim3(nb), dim3(kThreads), 0, s, S.n, S.nslices, S.sptr,
-                           S.srow0, S.perm, S.rowmap, S.init, S.col, (const VT *)S.val, x, y, w, partials, scs, mp,
-                           sy, nxcd, S.lens, S.wsl, S.wofs, tsp, tcl, tvl, tof, rr);
-    else
-        hipLaunchKernelGGL((k_sell_spmv<U, VT, false>), dim3(nb), dim3(kThreads), 0, s, S.n, S.nslices, S.sptr,
-                           S.srow0, S.perm, S.rowmap, S.init, S.col, (const VT *)S.val, x, y, w, partials, scs, mp,
-                           sy, nxcd, S.lens, S.wsl, S.wofs, tsp, tcl, tvl, tof, rr);
 }
 
+// nt: non-temporal loads of the matrix (always with the unrolls of 1 and 2, never with 16: few slices)
 template <typename VT>
-static void launch_sell_v(const Sell &S, int un, const double *x, double *y, const double *w, double *partials,
+static void launch_sell_v(const Sell &S, int un, bool nt, const double *x, double *y, const double *w, double *partials,
                           PcgScalars *scs, const Map &mp, const Systems &sy, int nb, int nxcd, hipStream_t s,
                           bool fused = false, const double *rr = nullptr) {
     switch (un) {
-        case 1: launch_sell_t<1, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr); break;
-        case 2: launch_sell_t<2, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr); break;
-        case 4: launch_sell_t<4, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr); break;
-        default: launch_sell_t<8, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr); break;
+        case 1: launch_sell_t<1, true, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr); break;
+        case 2: launch_sell_t<2, true, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr); break;
+        case 4:
+            if (nt) launch_sell_t<4, true, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr);
+            else launch_sell_t<4, false, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr);
+            break;
+        case 16: launch_sell_t<16, false, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr); break;
+        default:
+            if (nt) launch_sell_t<8, true, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr);
+            else launch_sell_t<8, false, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr);
+            break;
     }
 }
 
 // Entries in flight per lane of a SELL product: 8 (16 in the length-ordered instance), or 4
 // for matrices of at most 8 stored entries per row on average, whose lanes finish within one
 // or two rounds anyway and gain more from the resident wavefronts the smaller register budget
-// allows (a batch of short 7-point systems: its PCG 27.9 -> 25.0 ms).  The sums do not depend
-// on it.
-static int sell_unroll(const Sell &S) {
+// allows (a batch of short 7-point systems: its PCG 27.9 -> 25.0 ms).  Twice as many where there
+// are at most two slices per SIMD: nothing else covers a round trip there (24,000 rows of 81
+// entries: 52.5 -> 45.4 us an iteration, 107,811 rows 68 -> 64, 64,000 rows of 7 24.8 -> 22.4; the
+// registers of 16 would cost the larger ones their second wavefront).  The sums do not depend on it.
+static int sell_unroll(const Sell &S, const DeviceInfo &di) {
     if (option(AFSAI_OPT_SPMV_UNROLL) > 0) return (int)option(AFSAI_OPT_SPMV_UNROLL);
-    return (S.n > 0 && S.entries <= 8 * (int64_t)S.n) ? 4 : 8;
+    const bool few = S.nslices <= 8 * di.num_cus;
+    return ((S.n > 0 && S.entries <= 8 * (int64_t)S.n) ? 4 : 8) * (few ? 2 : 1);
 }
+
+// Matrix bytes of an iteration that the 256 MB memory-side cache still holds in the next one: up to
+// there ordinary loads, else non-temporal ones.  Microseconds an iteration, ordinary and
+// non-temporal: 78 MB 49.8, 53.6; 140 MB 66.7, 74.1; 227 MB 97.7, 98.7; 274 MB 92.3, 92.6; 403 MB
+// 161.7, 152.1; 476 MB 147, 133; 1137 MB 285, 248.  Block products, K = 8, 143 MB of matrix: 67, 85 us;
+// 478 MB: 200, 193.
+constexpr int64_t kCachedBytes = (int64_t)256 << 20;
+static int64_t stream_bytes(const Sell &S) { return S.entries * (4 + (S.f32 ? 4 : 8)); }
 
 // y = S x for a SELL-64 matrix laid out for the batch (optionally fused dot y.w: one partial sum
 // per block, finalised into the systems' scalars when fin says so); a split layout's tail is multiplied first
 static void sell_spmv(const char *name, const Sell &S, const BatchMaps &bm, const double *x, double *y,
                       const double *w, double *partials, PcgScalars *scs, int fin, const DeviceInfo &di,
                       hipStream_t s, const double *rr = nullptr) {
-    const int un = sell_unroll(S);
+    const int un = sell_unroll(S, di);
     // a split layout's tail runs in a launch of its own first; inside the slices' product when
     // asked for (measured slower: the lanes of long rows serialise their tails while the rest of
     // the wavefront waits)
@@ -1183,18 +1204,18 @@ static void sell_spmv(const char *name, const Sell &S, const BatchMaps &bm, cons
         PcgScalars *tsc = (bm.nsys == 1) ? scs : nullptr;
         ProfScope ps("sell_tail", s);
         if (T.f32)
-            launch_sell_v<float>(T, sell_unroll(T), x, y, nullptr, nullptr, tsc, Map(), Systems(), nbt, di.num_xcds, s);
+            launch_sell_v<float>(T, sell_unroll(T, di), bm.nt, x, y, nullptr, nullptr, tsc, Map(), Systems(), nbt, di.num_xcds, s);
         else
-            launch_sell_v<double>(T, sell_unroll(T), x, y, nullptr, nullptr, tsc, Map(), Systems(), nbt, di.num_xcds,
+            launch_sell_v<double>(T, sell_unroll(T, di), bm.nt, x, y, nullptr, nullptr, tsc, Map(), Systems(), nbt, di.num_xcds,
                                   s);
     }
     const int nb = bm.sell.nblocks;
     {
         ProfScope ps(name, s);
         if (S.f32)
-            launch_sell_v<float>(S, un, x, y, w, partials, scs, bm.sell.mp, bm.sy, nb, di.num_xcds, s, fused, rr);
+            launch_sell_v<float>(S, un, bm.nt, x, y, w, partials, scs, bm.sell.mp, bm.sy, nb, di.num_xcds, s, fused, rr);
         else
-            launch_sell_v<double>(S, un, x, y, w, partials, scs, bm.sell.mp, bm.sy, nb, di.num_xcds, s, fused, rr);
+            launch_sell_v<double>(S, un, bm.nt, x, y, w, partials, scs, bm.sell.mp, bm.sy, nb, di.num_xcds, s, fused, rr);
     }
     if (w && fin != FIN_NONE)
         hipLaunchKernelGGL(k_finalize, dim3(bm.nsys), dim3(kThreads), 0, s, Parts{partials, bm.sell.mp, nb}, Parts(), fin,
@@ -1209,11 +1230,11 @@ struct FusedScal {
     Parts pa, pb;
 };
 
-template <int U, typename VT, int MODE>
+template <int U, bool NT, typename VT, int MODE>
 static void launch_fused_t(const Sell &S, const double *va, const double *vb, double *own, double *x,
                            const double *pn, double *y, double *partials, const FusedScal &fs, int first,
                            const BatchMaps &bm, int nxcd, hipStream_t s) {
-    hipLaunchKernelGGL((k_sell_fused<U, VT, MODE>), dim3(bm.sell.nblocks), dim3(kThreads), 0, s, S.n, S.nslices,
+    hipLaunchKernelGGL((k_sell_fused<U, VT, MODE, NT>), dim3(bm.sell.nblocks), dim3(kThreads), 0, s, S.n, S.nslices,
                        S.sptr, S.srow0, S.col, (const VT *)S.val, va, vb, own, x, pn, y, partials, fs.in, fs.out, fs.bad,
                        fs.pa, fs.pb, first, bm.sell.mp, bm.sy, nxcd);
 }
@@ -1223,10 +1244,17 @@ static void launch_fused_v(const Sell &S, int un, const double *va, const double
                            const double *pn, double *y, double *partials, const FusedScal &fs, int first,
                            const BatchMaps &bm, int nxcd, hipStream_t s) {
     switch (un) {
-        case 1: launch_fused_t<1, VT, MODE>(S, va, vb, own, x, pn, y, partials, fs, first, bm, nxcd, s); break;
-        case 2: launch_fused_t<2, VT, MODE>(S, va, vb, own, x, pn, y, partials, fs, first, bm, nxcd, s); break;
-        case 4: launch_fused_t<4, VT, MODE>(S, va, vb, own, x, pn, y, partials, fs, first, bm, nxcd, s); break;
-        default: launch_fused_t<8, VT, MODE>(S, va, vb, own, x, pn, y, partials, fs, first, bm, nxcd, s); break;
+        case 1: launch_fused_t<1, true, VT, MODE>(S, va, vb, own, x, pn, y, partials, fs, first, bm, nxcd, s); break;
+        case 2: launch_fused_t<2, true, VT, MODE>(S, va, vb, own, x, pn, y, partials, fs, first, bm, nxcd, s); break;
+        case 4:
+            if (bm.nt) launch_fused_t<4, true, VT, MODE>(S, va, vb, own, x, pn, y, partials, fs, first, bm, nxcd, s);
+            else launch_fused_t<4, false, VT, MODE>(S, va, vb, own, x, pn, y, partials, fs, first, bm, nxcd, s);
+            break;
+        case 16: launch_fused_t<16, false, VT, MODE>(S, va, vb, own, x, pn, y, partials, fs, first, bm, nxcd, s); break;
+        default:
+            if (bm.nt) launch_fused_t<8, true, VT, MODE>(S, va, vb, own, x, pn, y, partials, fs, first, bm, nxcd, s);
+            else launch_fused_t<8, false, VT, MODE>(S, va, vb, own, x, pn, y, partials, fs, first, bm, nxcd, s);
+            break;
     }
 }
 
@@ -1234,7 +1262,7 @@ template <int MODE>
 static void sell_fused(const char *name, const Sell &S, const BatchMaps &bm, const double *va, const double *vb,
                        double *own, double *x, const double *pn, double *y, double *partials, const FusedScal &fs,
                        int first, const DeviceInfo &di, hipStream_t s) {
-    const int un = sell_unroll(S);
+    const int un = sell_unroll(S, di);
     ProfScope ps(name, s);
     if (S.f32)
         launch_fused_v<float, MODE>(S, un, va, vb, own, x, pn, y, partials, fs, first, bm, di.num_xcds, s);
@@ -1262,7 +1290,7 @@ __device__ __forceinline__ bool all_stopped(const MultiScal *sc) {
 // K values of a gathered row are contiguous.  Each output is the same sequential chain over
 // the row's entries as in the single-vector product.  sc given: nothing is done when every column
 // has stopped.
-template <int K, typename VT, bool DOT = false>
+template <int K, typename VT, bool DOT, bool NT>
 __global__ __launch_bounds__(kThreads) void k_sell_spmm(int n, int nslices, const uint32_t *__restrict__ sptr,
                                                          const int32_t *__restrict__ perm,
                                                          const int32_t *__restrict__ lens,
@@ -1307,8 +1335,8 @@ __global__ __launch_bounds__(kThreads) void k_sell_spmm(int n, int nslices, cons
             v[u] = VT(0);
             if (u < len) {
                 const int64_t d = base + (int64_t)u * kSlice;
-                c[u] = __builtin_nontemporal_load(&col[d]);
-                v[u] = __builtin_nontemporal_load(&val[d]);
+                c[u] = ldm<NT>(&col[d]);
+                v[u] = ldm<NT>(&val[d]);
             }
         }
         for (int k0 = 0; k0 < len; k0 += U) {
@@ -1320,8 +1348,8 @@ __global__ __launch_bounds__(kThreads) void k_sell_spmm(int n, int nslices, cons
                 vn[u] = VT(0);
                 if (k0 + U + u < len) {
                     const int64_t d = base + (int64_t)(k0 + U + u) * kSlice;
-                    cn[u] = __builtin_nontemporal_load(&col[d]);
-                    vn[u] = __builtin_nontemporal_load(&val[d]);
+                    cn[u] = ldm<NT>(&col[d]);
+                    vn[u] = ldm<NT>(&val[d]);
                 }
             }
 #pragma unroll
@@ -1359,7 +1387,7 @@ __global__ __launch_bounds__(kThreads) void k_sell_spmm(int n, int nslices, cons
 // length ordering): a lane reads a run's index and its three values and the 3K consecutive
 // entries of X's rows c..c+2; per column the sum is the same chain over the entries in stored
 // order as k_sell_spmm's, so Y and the partial sums are identical to it bit for bit.
-template <int K, bool DOT = false>
+template <int K, bool DOT, bool NT>
 __global__ __launch_bounds__(kThreads) void k_sell_spmm_runs(int n, int nslices, const uint32_t *__restrict__ sptr,
                                                               const int32_t *__restrict__ col3,
                                                               const double *__restrict__ val,
@@ -1394,9 +1422,9 @@ __global__ __launch_bounds__(kThreads) void k_sell_spmm_runs(int n, int nslices,
 #pragma unroll
             for (int e = 0; e < 3; ++e) v[u][e] = 0.0;
             if (u < nr) {
-                c[u] = __builtin_nontemporal_load(&col3[rbase + (int64_t)u * kSlice]);
+                c[u] = ldm<NT>(&col3[rbase + (int64_t)u * kSlice]);
 #pragma unroll
-                for (int e = 0; e < 3; ++e) v[u][e] = __builtin_nontemporal_load(&val[vbase + (int64_t)(3 * u + e) * kSlice]);
+                for (int e = 0; e < 3; ++e) v[u][e] = ldm<NT>(&val[vbase + (int64_t)(3 * u + e) * kSlice]);
             }
         }
         for (int j0 = 0; j0 < nr; j0 += UR) {
@@ -1409,10 +1437,10 @@ __global__ __launch_bounds__(kThreads) void k_sell_spmm_runs(int n, int nslices,
                 for (int e = 0; e < 3; ++e) vn[u][e] = 0.0;
                 if (j0 + UR + u < nr) {
                     const int jr = j0 + UR + u;
-                    cn[u] = __builtin_nontemporal_load(&col3[rbase + (int64_t)jr * kSlice]);
+                    cn[u] = ldm<NT>(&col3[rbase + (int64_t)jr * kSlice]);
 #pragma unroll
                     for (int e = 0; e < 3; ++e)
-                        vn[u][e] = __builtin_nontemporal_load(&val[vbase + (int64_t)(3 * jr + e) * kSlice]);
+                        vn[u][e] = ldm<NT>(&val[vbase + (int64_t)(3 * jr + e) * kSlice]);
                 }
             }
 #pragma unroll
@@ -1455,7 +1483,7 @@ __global__ __launch_bounds__(kThreads) void k_sell_spmm_runs(int n, int nslices,
 // rows (54 M entries): 231 -> 187 us, 2.5 TB/s of matrix; L = 1 spills and L = 4 takes 249 us (the
 // columns and values come four times); four lanes on one row with two columns each, 423 us.  Per
 // column and row the sum is the chain of k_sell_spmm_runs: Y is identical bit for bit.
-template <int K, int L>
+template <int K, int L, bool NT>
 __global__ __launch_bounds__(kThreads) void k_node_spmm(int n, int nslices, const uint32_t *__restrict__ bptr,
                                                         const int32_t *__restrict__ bcol,
                                                         const double *__restrict__ bval, const double *__restrict__ x,
@@ -1482,9 +1510,9 @@ __global__ __launch_bounds__(kThreads) void k_node_spmm(int n, int nslices, cons
         int c = 0, cn;
         double v[9], vn[9];
         if (b0 < b1) {
-            c = __builtin_nontemporal_load(&bcol[(int64_t)b0 * kSlice + l]);
+            c = ldm<NT>(&bcol[(int64_t)b0 * kSlice + l]);
 #pragma unroll
-            for (int q = 0; q < 9; ++q) v[q] = __builtin_nontemporal_load(&bval[((int64_t)b0 * 9 + q) * kSlice + l]);
+            for (int q = 0; q < 9; ++q) v[q] = ldm<NT>(&bval[((int64_t)b0 * 9 + q) * kSlice + l]);
         }
         cn = c;
         for (int b = b0; b < b1; ++b) {
@@ -1495,9 +1523,9 @@ __global__ __launch_bounds__(kThreads) void k_node_spmm(int n, int nslices, cons
 #pragma unroll
                 for (int j = 0; j < C; ++j) xv[e][j] = xc[e * K + j];
             if (b + 1 < b1) {
-                cn = __builtin_nontemporal_load(&bcol[(int64_t)(b + 1) * kSlice + l]);
+                cn = ldm<NT>(&bcol[(int64_t)(b + 1) * kSlice + l]);
 #pragma unroll
-                for (int q = 0; q < 9; ++q) vn[q] = __builtin_nontemporal_load(&bval[((int64_t)(b + 1) * 9 + q) * kSlice + l]);
+                for (int q = 0; q < 9; ++q) vn[q] = ldm<NT>(&bval[((int64_t)(b + 1) * 9 + q) * kSlice + l]);
             }
             if (c >= 0) {
 #pragma unroll
@@ -1738,27 +1766,35 @@ __global__ __launch_bounds__(kThreads) void k_multi_resid(int n, const double *_
     multi_store<K>(part, sh, partials);
 }
 
-template <int K, bool DOT>
-static void spmm_launch(const Sell &S, const double *x, double *y, const double *w, double *partials, int nb,
-                          const DeviceInfo &di, hipStream_t s, const MultiScal *sc = nullptr) {
+// nt: non-temporal loads of the matrix
+template <int K, bool DOT, bool NT>
+static void spmm_launch_t(const Sell &S, const double *x, double *y, const double *w, double *partials, int nb,
+                          const DeviceInfo &di, hipStream_t s, const MultiScal *sc) {
     const dim3 bt(kThreads);
     if (S.bptr) {
         constexpr int L = K >= 8 ? 2 : 1;
         const int nsl = (S.n / 3 + kSlice - 1) / kSlice;
-        hipLaunchKernelGGL((k_node_spmm<K, L>), dim3(blocks_for_slices(nsl * L, di)), bt, 0, s, S.n, nsl, S.bptr,
+        hipLaunchKernelGGL((k_node_spmm<K, L, NT>), dim3(blocks_for_slices(nsl * L, di)), bt, 0, s, S.n, nsl, S.bptr,
                            S.bcol, S.bval, x, y, di.num_xcds, sc);
         if (DOT)
             hipLaunchKernelGGL((k_window_dot<K>), dim3(nb), bt, 0, s, S.n, (S.n + kSlice - 1) / kSlice, y, w, partials,
                                di.num_xcds, sc);
     } else if (S.col3 && !S.f32 && !S.lens)
-        hipLaunchKernelGGL((k_sell_spmm_runs<K, DOT>), dim3(nb), bt, 0, s, S.n, S.nslices, S.sptr, S.col3,
+        hipLaunchKernelGGL((k_sell_spmm_runs<K, DOT, NT>), dim3(nb), bt, 0, s, S.n, S.nslices, S.sptr, S.col3,
                            (const double *)S.val, x, y, di.num_xcds, w, partials, sc);
     else if (S.f32)
-        hipLaunchKernelGGL((k_sell_spmm<K, float, DOT>), dim3(nb), bt, 0, s, S.n, S.nslices, S.sptr, S.perm, S.lens,
+        hipLaunchKernelGGL((k_sell_spmm<K, float, DOT, NT>), dim3(nb), bt, 0, s, S.n, S.nslices, S.sptr, S.perm, S.lens,
                            S.col, (const float *)S.val, x, y, di.num_xcds, w, partials, sc);
     else
-        hipLaunchKernelGGL((k_sell_spmm<K, double, DOT>), dim3(nb), bt, 0, s, S.n, S.nslices, S.sptr, S.perm, S.lens,
+        hipLaunchKernelGGL((k_sell_spmm<K, double, DOT, NT>), dim3(nb), bt, 0, s, S.n, S.nslices, S.sptr, S.perm, S.lens,
                            S.col, (const double *)S.val, x, y, di.num_xcds, w, partials, sc);
+}
+
+template <int K, bool DOT>
+static void spmm_launch(const Sell &S, bool nt, const double *x, double *y, const double *w, double *partials, int nb,
+                        const DeviceInfo &di, hipStream_t s, const MultiScal *sc = nullptr) {
+    if (nt) spmm_launch_t<K, DOT, true>(S, x, y, w, partials, nb, di, s, sc);
+    else spmm_launch_t<K, DOT, false>(S, x, y, w, partials, nb, di, s, sc);
 }
 
 static int check_csr_arg(const afsai_csr *A, const char *who) {
@@ -1897,6 +1933,7 @@ class PcgRun {
         for (int k = 0; k < nsys_; ++k) nmax = std::max(nmax, row0_[k + 1] - row0_[k]);
         const bool want_fused = form == 2 || (form == 0 && nmax < kFusedMaxRows);
         fused_ = P_ && use_sell_ && want_fused && !As_.tail && !P_->sg.tail && !As_.perm && !P_->sg.perm;
+        bm_.nt = stream_bytes(As_) + (P_ ? stream_bytes(P_->sg) + stream_bytes(P_->sgt) : 0) > kCachedBytes;
         if ((rc = choose_small())) return rc;
         return small_ ? enqueue_small() : start();
     }
@@ -2424,6 +2461,8 @@ static int pcg_multi(const afsai_csr *A, afsai_precond P, const double *B, doubl
             if ((rc = sell_group_runs(&SA, di, s))) return rc;
         }
     }
+    const bool nt = (SA.bptr ? SA.bentries * 9 : stream_bytes(SA)) +
+                        (P ? stream_bytes(P->sg) + stream_bytes(P->sgt) : 0) > kCachedBytes;
     const int nbA = blocks_for_slices((n + kSlice - 1) / kSlice, di), nbv = blocks_for_vec(n, di);
     const int nbG = P ? blocks_for_slices(P->sg.nslices, di) : 0;
     const int nbGT = P ? blocks_for_slices(P->sgt.nslices, di) : 0;
@@ -2442,8 +2481,8 @@ static int pcg_multi(const afsai_csr *A, afsai_precond P, const double *B, doubl
     // Z = M R with partial sums of R.Z; returns the blocks of that launch
     auto precond = [&](const MultiScal *gate) {
         if (P) {
-            spmm_launch<K, false>(P->sg, R, T, nullptr, nullptr, nbG, di, s, gate);
-            spmm_launch<K, true>(P->sgt, T, Z, R, pa, nbGT, di, s, gate);
+            spmm_launch<K, false>(P->sg, nt, R, T, nullptr, nullptr, nbG, di, s, gate);
+            spmm_launch<K, true>(P->sgt, nt, T, Z, R, pa, nbGT, di, s, gate);
             return nbGT;
         }
         hipLaunchKernelGGL((k_multi_dot<K>), dim3(nbv), dim3(kThreads), 0, s, n, R, R, Z, pa);
@@ -2474,7 +2513,7 @@ static int pcg_multi(const afsai_csr *A, afsai_precond P, const double *B, doubl
     // left the GPU idle for about 45 us of 300 at 250,000 rows); the iteration that is then queued past the
     // last column's end returns at once
     for (int it = 0; it < maxit; ++it) {
-        spmm_launch<K, true>(SA, Pv, Q, Pv, pa, nbA, di, s, sc);
+        spmm_launch<K, true>(SA, nt, Pv, Q, Pv, pa, nbA, di, s, sc);
         fin(nbA, MF_PQ);
         hipLaunchKernelGGL((k_multi_xr<K>), dim3(nbv), dim3(kThreads), 0, s, n, X, R, Pv, Q, sc, pa);
         fin(nbv, MF_RR);
@@ -2490,7 +2529,7 @@ static int pcg_multi(const afsai_csr *A, afsai_precond P, const double *B, doubl
         if (all) break;
     }
     // true residuals ||b - A x|| per column
-    spmm_launch<K, false>(SA, X, Q, nullptr, nullptr, nbA, di, s);
+    spmm_launch<K, false>(SA, nt, X, Q, nullptr, nullptr, nbA, di, s);
     hipLaunchKernelGGL((k_multi_resid<K>), dim3(nbv), dim3(kThreads), 0, s, n, B, Q, pa);
     fin(nbv, MF_TRUE);
     std::vector<MultiScal> h(K);
@@ -2554,11 +2593,12 @@ static int spmm_sell(const Sell &S, int32_t k, const double *X, double *Y, const
     {
         ProfScope ps("spmm_A", s);
         const int nb = blocks_for_slices(S.nslices, di);
+        const bool nt = (S.bptr ? S.bentries * 9 : stream_bytes(S)) > kCachedBytes;
         switch (k) {
-            case 1: spmm_launch<1, false>(S, X, Y, nullptr, nullptr, nb, di, s); break;
-            case 2: spmm_launch<2, false>(S, X, Y, nullptr, nullptr, nb, di, s); break;
-            case 4: spmm_launch<4, false>(S, X, Y, nullptr, nullptr, nb, di, s); break;
-            default: spmm_launch<8, false>(S, X, Y, nullptr, nullptr, nb, di, s); break;
+            case 1: spmm_launch<1, false>(S, nt, X, Y, nullptr, nullptr, nb, di, s); break;
+            case 2: spmm_launch<2, false>(S, nt, X, Y, nullptr, nullptr, nb, di, s); break;
+            case 4: spmm_launch<4, false>(S, nt, X, Y, nullptr, nullptr, nb, di, s); break;
+            default: spmm_launch<8, false>(S, nt, X, Y, nullptr, nullptr, nb, di, s); break;
         }
     }
     const hipError_t le = hipGetLastError();
@@ -2685,6 +2725,7 @@ int afsai_apply(afsai_precond P, const double *r, double *z, void *stream) {
     // products only (no dots): the whole matrix as one system
     BatchMaps bm;
     if ((rc = make_batch_maps(P->sg.nslices * kSlice, 1, nullptr, di, s, &bm))) return rc;
+    bm.nt = stream_bytes(P->sg) + stream_bytes(P->sgt) > kCachedBytes;
     bm.sell.nblocks = blocks_for_slices(P->sg.nslices, di);
     sell_spmv("spmv_G", P->sg, bm, r, t, nullptr, nullptr, nullptr, FIN_NONE, di, s);
     bm.sell.nblocks = blocks_for_slices(P->sgt.nslices, di);
@@ -2741,6 +2782,7 @@ int afsai_apply_noalloc(afsai_precond P, const double *r, double *z, void *strea
     hipStream_t s = (hipStream_t)stream;
     // the products of afsai_apply, the whole matrix as one system (no device block maps)
     BatchMaps bm;
+    bm.nt = stream_bytes(P->sg) + stream_bytes(P->sgt) > kCachedBytes;
     bm.sell.nblocks = blocks_for_slices(P->sg.nslices, di);
     sell_spmv("spmv_G", P->sg, bm, r, t, nullptr, nullptr, nullptr, FIN_NONE, di, s);
     bm.sell.nblocks = blocks_for_slices(P->sgt.nslices, di);

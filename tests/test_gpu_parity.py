@@ -1098,3 +1098,46 @@ def test_block_products_of_nodes(af, make):
         assert [(i.iters, i.status, i.relres) for i in iy] == [(i.iters, i.status, i.relres) for i in iz]
         np.testing.assert_array_equal(Y.cpu().numpy(), Z.cpu().numpy())
     M.close()
+
+
+@pytest.mark.parametrize("make,form", [
+    (lambda: synth.elast27(8, 1.0, 1), 1), (lambda: synth.elast27(8, 1.0, 1), 2), (lambda: synth.lap7(57, 57, 57), 2),
+    (lambda: synth.random_sparse_spd(3000, 40, 3), 1), (lambda: synth.elast27(40, 1.0, 2), 2)])
+def test_pcg_matrix_loads(af, make, form):
+    """Matrices that the caches keep and one that they do not (274 MB an iteration), few slices and
+    many: x is the same bit for bit for every number of entries in flight, with ordinary and with
+    non-temporal loads of the matrices (an unroll of 2 always takes those)."""
+    A = make()
+    dA = _dev(af, A)
+    P = af.setup(dA, 10, 2, 1e-2)
+    b = _vec(synth.uniform(5, 1, A.n, -1.0, 1.0))
+    out = []
+    try:
+        af.set_option(af.OPT_PCG_FORM, form)
+        for un in (0, 2, 4, 8):
+            af.set_option(af.OPT_SPMV_UNROLL, un)
+            x, i = af.pcg_solve(dA, P, b, rtol=1e-8)
+            out.append((i.iters, x.cpu().numpy().view(np.int64)))
+    finally:
+        af.set_option(af.OPT_SPMV_UNROLL, 0)
+        af.set_option(af.OPT_PCG_FORM, 0)
+    assert out[0][0] > 5
+    for it, x in out[1:]:
+        assert it == out[0][0]
+        np.testing.assert_array_equal(x, out[0][1])
+
+
+def test_block_products_matrix_loads(af):
+    """A matrix larger than the caches (33 M entries): the products over 3 x 3 blocks and over single
+    entries agree bit for bit, and column by column with the single-vector product."""
+    import torch
+
+    A = synth.elast27(52, 1.0, 3)
+    dA = _dev(af, A)
+    M = af.PreparedMatrix(dA)
+    X = torch.from_numpy(synth.uniform(19, 5, A.n * 4, -1.0, 1.0).reshape(A.n, 4)).cuda()
+    Y = M.spmm(X)
+    assert torch.equal(Y, af.spmm(dA, X))
+    for j in (0, 3):
+        assert torch.equal(Y[:, j], M.spmm(X[:, j:j + 1].contiguous())[:, 0])
+    M.close()
