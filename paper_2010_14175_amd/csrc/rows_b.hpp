@@ -8,9 +8,10 @@
 // serve three entries.  Patterns of up to 32 positions put two rows on a wavefront (32 lanes
 // each); larger ones keep one row per wavefront, whose halves take two member rows (and two
 // gathered rows) at once.  The slot bytes need 6 registers where k_rows_w keeps 24 (48).
-// Measured: this kernel takes 10.4 ms at 64^3 (21 positions) and 594 ms at 150^3 (46 positions),
-// k_rows_w with the same products 20.4 and 985 ms before.  Now bound by instruction issue and
-// LDS alike (each over half busy), with 16 and 11 wavefronts per CU by LDS.
+// Measured: this kernel takes 10.2 ms at 64^3 (21 positions) and 571 ms at 150^3 (46 positions),
+// k_rows_w 20.4 and 985 ms before.  Now bound by the LDS (0.7 of its cycles in use at 64^3, half of
+// that for the gradients' additions) and instruction issue (0.7) alike, with 16 and 11 wavefronts
+// per CU by LDS; a tenth fewer vector instructions alone changed nothing.
 //
 // Layout of one row group (LDS): per table slot the run's first column, a word with one byte
 // per column (0: candidate, p + 1: member at position p) and three gradients (one plane per
@@ -44,7 +45,7 @@ template <int GS, int MMAX, int CAPT, int NB>
 struct Layout {
     static constexpr int VALB = 3 * CAPT * 8;
     static constexpr int LDV = MMAX + 2;  // rows of NR and LV (see rows_w.hpp)
-    static constexpr int ALV = (2 * NB + 1) * LDV + NB;  // NR, LV (with LI), NAI in doubles
+    static constexpr int ALV = 2 * NB * LDV + NB;  // NR, LV, NAI in doubles
     static constexpr int O_KEY = 0;
     static constexpr int O_INF = CAPT * 4;
     static constexpr int O_VAL = CAPT * 8;
@@ -156,8 +157,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
     int32_t *selb = sel + MMAX;                                     // [MMAX] their row starts
     int32_t *sele = selb + MMAX;                                    // [MMAX] their row ends
     double *NR = hval;                                              // [NB][LDV]
-    double *LV = NR + NB * LDV;                                     // [NB+1][LDV]
-    double *NAI = LV + (NB + 1) * LDV;                              // [NB]: a_{u,i}
+    double *LV = NR + NB * LDV;                                     // [NB][LDV]
+    double *NAI = LV + NB * LDV;                                    // [NB]: a_{u,i}
     const uint64_t gm = wform::group_bits<GS>(grp);
     const int zslot = wform::tri_w(wrows);  // of the padding after W, zero for the matrix products
     if (gl == 0) Wm[zslot] = 0.0;
@@ -203,7 +204,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
         const double psi0 = aii;
         double gi = act ? 1.0 / sqrt(aii) : 0.0;
         int r_col = 0, r_beg = 0, r_len = 0;
-        double r_g = 0.0, r_ai = 0.0, r_li = 0.0;
+        double r_g = 0.0, r_ai = 0.0;
+        double yi = 0.0;  // lane j: (W^T l_i)_j
         // slot of this lane's run in member row q (0: row i, q: position q - 1): byte q / HPG, in
         // the half q % HPG
         uint32_t slr[NSL];
@@ -255,39 +257,35 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
             wsync();
             const int mo_u = wu<GS>(m_o);
             if (wu<GS>(act)) {
+                // four member rows (of each half) at a time; lanes without a run load the row's first
+                // (loads under a condition made the ones behind them wait: 150^3 590 -> 571 ms; the next
+                // rows' loads between the additions: 581)
+                double aa[4][3], gg[4];
+                int len[4];
+                auto load = [&](int q, int u) __attribute__((always_inline)) {
+                    const Memb mb = memb[min(q, mo_u)];
+                    len[u] = q <= mo_u ? mb.len : 0;
+                    gg[u] = mb.g;
+                    const double *a = av + mb.beg + (hl < len[u] ? 3 * hl : 0);
+#pragma unroll
+                    for (int y = 0; y < 3; ++y) aa[u][y] = a[y];
+                };
 #pragma unroll
                 for (int qb = 0; qb < MMAX; qb += 4 * HPG) {
                     if (qb <= mo_u) {
-                        double aa[4][3], gg[4];
-                        int len[4];
 #pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const int q = qb + u * HPG + half;
-                            const Memb mb = memb[q];
-                            len[u] = q <= mo_u ? mb.len : 0;
-                            gg[u] = mb.g;
-#pragma unroll
-                            for (int y = 0; y < 3; ++y) aa[u][y] = 0.0;
-                            if (hl < len[u]) {
-                                const double *a = av + mb.beg + 3 * hl;
-#pragma unroll
-                                for (int y = 0; y < 3; ++y) aa[u][y] = a[y];
-                            }
-                        }
+                        for (int u = 0; u < 4; ++u) load(qb + u * HPG + half, u);
                         const uint32_t sw = slr[qb / (4 * HPG)];
 #pragma unroll
                         for (int u = 0; u < 4; ++u) {
                             double *h = hval + ((sw >> (8 * u)) & 0xFFu);
-                            double p[3];
-#pragma unroll
-                            for (int y = 0; y < 3; ++y) p[y] = aa[u][y] * gg[u];
                             // the halves in turn: a slot's terms in the order of the members
 #pragma unroll
                             for (int hh = 0; hh < HPG; ++hh) {
                                 if (half == hh && hl < len[u]) {
 #pragma unroll
                                     for (int y = 0; y < 3; ++y)
-                                        __hip_atomic_fetch_add(h + y * CAPT, p[y], __ATOMIC_RELAXED,
+                                        __hip_atomic_fetch_add(h + y * CAPT, aa[u][y] * gg[u], __ATOMIC_RELAXED,
                                                                __HIP_MEMORY_SCOPE_WORKGROUP);
                                 }
                                 if constexpr (HPG > 1) wsync();
@@ -382,9 +380,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
 
             // ---- 3./4. gather the new rows and extend W, NB rows at a time
             bool spd = true;
-            double yi = 0.0;  // lane j: (W^T l_i)_j, accumulated over the blocks of this step
             int nsd = 0;
-            bool first = true;
             // the last step's rows are looked up but not entered: no product pass follows
             const bool more = k < kmax;
             const int nsw = GS == 64 ? wu<GS>(ns)
@@ -477,12 +473,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, 8))) vo
                 const bool go = blk && act;
                 // a_{u,i} of the new positions
                 if (go && gl >= mo && gl < mo + nbk) r_ai = NAI[gl - mo];
-                wform::extend_w<GS, MMAX, NB, LDV>(go, mo, mwb, nbk, gl, first, gbytes / 8, zslot, wrows, s >= 4, Wm,
-                                                   NR, LV, r_ai, r_li, yi, psi, spd, status, act);
+                wform::extend_w<GS, MMAX, NB, LDV>(go, mo, mwb, nbk, gl, gbytes / 8, zslot, wrows, Wm, NR, LV, r_ai, yi, psi,
+                                                   spd, status, act);
                 if (blk) {
                     m_o += nbk;
                     nsd += nbk;
-                    first = false;
                 }
                 wsync();
             }

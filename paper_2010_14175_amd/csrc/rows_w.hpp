@@ -73,8 +73,8 @@ struct Layout {
     // of padding (the four rows read at once then fall in distinct banks) if the vectors still fit
     // in the gradient array
     static constexpr int LDM = GS >= 32 ? (MMAX + GS / 4 - 1) / (GS / 4) * (GS / 4) : MMAX;
-    static constexpr int LDV = LDM + (GS >= 32 && ((2 * NB + 1) * (LDM + 2) + NB) * 8 + 12 * MMAX <= CAP * 8 ? 2 : 0);
-    static constexpr int ALV = (2 * NB + 1) * LDV + NB;            // NR, LV (with LI), NAI in doubles
+    static constexpr int LDV = LDM + (GS >= 32 && (2 * NB * (LDM + 2) + NB) * 8 + 12 * MMAX <= CAP * 8 ? 2 : 0);
+    static constexpr int ALV = 2 * NB * LDV + NB;                  // NR, LV, NAI in doubles
     static constexpr bool ALIAS = ALV * 8 + 12 * MMAX <= CAP * 8;  // beside the selected columns
     static constexpr int O_HKEY = 0;
     static constexpr int O_HVAL = al16(CAP * 4);
@@ -95,7 +95,8 @@ struct Memb {
 // ---- moves and group reductions -------------------------------------------------------
 template <int CTRL>
 __device__ __forceinline__ int dmov(int v) {
-    return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, false);
+    // (every lane has a source: without an old value no copy of v is made for one)
+    return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true);
 }
 template <int CTRL>
 __device__ __forceinline__ double dmov(double v) {
@@ -336,18 +337,17 @@ __device__ __forceinline__ void top2(const uint32_t *hkey, const double *hval, i
 }
 
 // Both products with W of a block of new rows, on the matrix cores (groups of 32 or 64 lanes):
-// la[v] = (W a_v)_gl, yb[v] = (W^T l_v)_gl and, for the first block of a step, yi = (W^T l_i)_gl.
+// la[v] = (W a_v)_gl and yb[v] = (W^T l_v)_gl.
 // v_mfma_f64_4x4x4_4b holds four 4 x 4 x 4 products (operand lanes i + 4 block + 16 k, results
 // j + 4 block + 16 i): the blocks of a group take tiles of four rows of W (columns, for W^T), the
-// four columns of a tile are the new rows and l_i.  It adds its four terms in ascending order
+// columns of a tile are the new rows.  It adds its four terms in ascending order
 // with one rounding each, so with the tiles in order every result is the same fma chain as a
 // lane's loop over j (or t), bit for bit.  NC: chunks of 4 tiles (2 with 32 lanes) that hold old
 // positions.  Against that loop (eight LDS reads, selects and up to 24 fma per eight entries,
 // half of them above the diagonal): 64^3 setup 15.7 -> 14.5 ms, 150^3 step 1,305 -> 1,101 ms.
 template <int GS, int MMAX, int NB, int LDV, int NC>
 __device__ __forceinline__ void w_products(const double *Wb, const double *NRb, double *LVb, double *LV, int mo_b, int mo,
-                                           int zslot, bool go, bool first, bool sep, int gl, double (&la)[NB],
-                                           double (&yb)[NB], double &yi) {
+                                           int zslot, bool go, int gl, double (&la)[NB], double (&yb)[NB]) {
     constexpr int BPG = GS / 16;  // blocks of a group
     int lane = threadIdx.x & 63;
     // (opaque: the addresses of every tile are otherwise computed once for the whole kernel and
@@ -380,13 +380,11 @@ __device__ __forceinline__ void w_products(const double *Wb, const double *NRb, 
 #pragma unroll
         for (int tp = 0; tp < NC; ++tp) LVb[mj * LDV + 4 * (tp * BPG + sub) + mi] = acc[tp];
     wsync();
-    // pass B: columns j of tile jp * BPG + sub; column 3 of a tile is l_i (a pass of its own
-    // when four new rows may fill the tile)
+    // pass B: columns j of tile jp * BPG + sub
     double y[NC];
 #pragma unroll
     for (int jp = 0; jp < NC; ++jp) y[jp] = 0.0;
-    const int lrow = mj < NB && (mj < 3 || sep) ? mj : NB;
-    const double *lv = LVb + lrow * LDV + mi;
+    const double *lv = LVb + (mj < NB ? mj : NB - 1) * LDV + mi;
 #pragma unroll
     for (int c = 0; c < NC; ++c)
 #pragma unroll
@@ -401,48 +399,28 @@ __device__ __forceinline__ void w_products(const double *Wb, const double *NRb, 
                 y[jp] = __builtin_amdgcn_mfma_f64_4x4x4f64(Wb[in && (jp < c || j <= t) ? row + j : zslot], bv, y[jp], 0, 0, 0);
             }
         }
-    double yl[NC];
-#pragma unroll
-    for (int jp = 0; jp < NC; ++jp) yl[jp] = 0.0;
-    if (NB == 4 && sep) {
-        const double *li = LVb + NB * LDV + mi;
-        for (int tt = 0; tt < NC * BPG; ++tt) {
-            const int t = 4 * tt + mi;
-            const double bl = li[4 * tt];
-#pragma unroll
-            for (int jp = 0; jp < NC; ++jp) {
-                const int j = 4 * (jp * BPG + sub) + mj;
-                yl[jp] = __builtin_amdgcn_mfma_f64_4x4x4f64(Wb[t < mo_b && j <= t ? tri_w(t) + j : zslot], bl, yl[jp], 0, 0, 0);
-            }
-        }
-    }
 #pragma unroll
     for (int v = 0; v < NB; ++v) la[v] = go && gl < mo ? LV[v * LDV + gl] : 0.0;
     wsync();
-    const int yrow = mj == 3 && !sep ? NB : mj;
+    if (mj < NB)
 #pragma unroll
-    for (int jp = 0; jp < NC; ++jp) {
-        const int j = 4 * (jp * BPG + sub) + mi;
-        if (yrow <= NB) LVb[yrow * LDV + j] = y[jp];
-        if (NB == 4 && sep && mj == 0) LVb[NB * LDV + j] = yl[jp];
-    }
+        for (int jp = 0; jp < NC; ++jp) LVb[mj * LDV + 4 * (jp * BPG + sub) + mi] = y[jp];
     wsync();
 #pragma unroll
     for (int v = 0; v < NB; ++v) yb[v] = go && gl < mo ? LV[v * LDV + gl] : 0.0;
-    if (go && first) yi = gl < mo ? LV[NB * LDV + gl] : 0.0;
 }
 
 // Step 4 of a block of nbk <= NB new rows (positions mo .. mo + nbk - 1, their entries at the
-// old and new positions in NR, a_{u,i} in r_ai): the rows of W, l_i's new entries (r_li), psi and
-// yi = W^T l_i of this step so far.  Rows of W from position wrows on are not stored (no later
-// block reads them).  go: this group takes part; mwb: the most old positions of a
-// group of the wavefront; first: the step's first block (l_i's old entries are added to yi then);
-// gst: doubles from one group's LDS to the next; zslot: an entry of W that holds zero; sep: steps
-// of four or more new rows.  NR and LV have rows of LDV entries.
+// old and new positions in NR, a_{u,i} in r_ai): the rows of W, l_i's new entries, psi and
+// yi = W^T l_i, which grows by one term per new row: W's and l_i's old entries stay (7-point rows,
+// 21 positions: the setup kernel 33.1 -> 30.6 ms against adding up all terms at every step).  Rows of W
+// from position wrows on are not stored (no later block reads them).  go: this group takes part; mwb: the most old positions of a
+// group of the wavefront; gst: doubles from one group's LDS to the next; zslot: an entry of W that
+// holds zero.  NR and LV have rows of LDV entries.
 template <int GS, int MMAX, int NB, int LDV>
-__device__ __forceinline__ void extend_w(bool go, int mo, int mwb, int nbk, int gl, bool first, int gst, int zslot,
-                                         int wrows, bool sep, double *Wm, const double *NR, double *LV, double r_ai, double &r_li,
-                                         double &yi, double &psi, bool &spd, int8_t &status, bool &act) {
+__device__ __forceinline__ void extend_w(bool go, int mo, int mwb, int nbk, int gl, int gst, int zslot, int wrows,
+                                         double *Wm, const double *NR, double *LV, double r_ai, double &yi, double &psi,
+                                         bool &spd, int8_t &status, bool &act) {
     double la[NB], yb[NB];
 #pragma unroll
     for (int v = 0; v < NB; ++v) la[v] = yb[v] = 0.0;
@@ -459,18 +437,17 @@ __device__ __forceinline__ void extend_w(bool go, int mo, int mwb, int nbk, int 
         }
         const double *Wb = Wm + (bg - grp) * gst, *NRb = NR + (bg - grp) * gst;
         double *LVb = LV + (bg - grp) * gst;
-        if (gl < LDV) LV[NB * LDV + gl] = (go && first && gl < mo) ? r_li : 0.0;
         const int nc = (mwb + TPC - 1) / TPC;
         if (nc == 1) {
-            w_products<GS, MMAX, NB, LDV, 1>(Wb, NRb, LVb, LV, mo_b, mo, zslot, go, first, sep, gl, la, yb, yi);
+            w_products<GS, MMAX, NB, LDV, 1>(Wb, NRb, LVb, LV, mo_b, mo, zslot, go, gl, la, yb);
         } else if (nc == 2) {
-            w_products<GS, MMAX, NB, LDV, 2>(Wb, NRb, LVb, LV, mo_b, mo, zslot, go, first, sep, gl, la, yb, yi);
+            w_products<GS, MMAX, NB, LDV, 2>(Wb, NRb, LVb, LV, mo_b, mo, zslot, go, gl, la, yb);
         } else if (nc == 3) {
             if constexpr (MMAX > 2 * TPC)
-                w_products<GS, MMAX, NB, LDV, 3>(Wb, NRb, LVb, LV, mo_b, mo, zslot, go, first, sep, gl, la, yb, yi);
+                w_products<GS, MMAX, NB, LDV, 3>(Wb, NRb, LVb, LV, mo_b, mo, zslot, go, gl, la, yb);
         } else if (nc == 4) {
             if constexpr (MMAX > 3 * TPC)
-                w_products<GS, MMAX, NB, LDV, 4>(Wb, NRb, LVb, LV, mo_b, mo, zslot, go, first, sep, gl, la, yb, yi);
+                w_products<GS, MMAX, NB, LDV, 4>(Wb, NRb, LVb, LV, mo_b, mo, zslot, go, gl, la, yb);
         }
     } else {
         // pass A: l_v[t] = sum_{j <= t} W[t][j] a_v[j] for the old positions t < m_o
@@ -499,10 +476,9 @@ __device__ __forceinline__ void extend_w(bool go, int mo, int mwb, int nbk, int 
             // unrolled reads
 #pragma unroll
             for (int v = 0; v < NB; ++v) LV[v * LDV + gl] = gl < mo ? la[v] : 0.0;
-            LV[NB * LDV + gl] = (first && gl < mo) ? r_li : 0.0;
         }
         wsync();
-        // pass B: y_v[j] = sum_{j <= t < m_o} W[t][j] l_v[t], and the same with l_i
+        // pass B: y_v[j] = sum_{j <= t < m_o} W[t][j] l_v[t]
         {
             // all loads first: rows t of the chunk past the old positions read the last
             // old row, lanes without an old position column 0 (in bounds); then the
@@ -526,8 +502,6 @@ __device__ __forceinline__ void extend_w(bool go, int mo, int mwb, int nbk, int 
                     if (v < nbk)
 #pragma unroll
                         for (int u = 0; u < kPU; ++u) yb[v] = fma(wv[u], LV[v * LDV + t0 + u], yb[v]);
-#pragma unroll
-                for (int u = 0; u < kPU; ++u) yi = fma(wv[u], LV[NB * LDV + t0 + u], yi);
             }
         }
     }
@@ -569,7 +543,6 @@ __device__ __forceinline__ void extend_w(bool go, int mo, int mwb, int nbk, int 
 #pragma unroll
                 for (int w = 0; w < NB; ++w) {
                     const double li = gred<GS, OpSum>(wn[w] * r_ai);
-                    if (w < nbk && gl == mo + w) r_li = li;
                     psi = psi - li * li;
                     yi = fma(wn[w], li, yi);
                 }
@@ -616,7 +589,6 @@ __device__ __forceinline__ void extend_w(bool go, int mo, int mwb, int nbk, int 
                 for (int w = 0; w < NB; ++w) {
                     if (w < nbk) {
                         const double li = gred<GS, OpSum>(wn[w] * r_ai);
-                        if (gl == mo + w) r_li = li;
                         psi = psi - li * li;
                         yi = fma(wn[w], li, yi);
                     }
@@ -665,8 +637,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(GS == 8 || (
     int32_t *selb = sel + MMAX;                                     // [MMAX] their row starts
     int32_t *sele = selb + MMAX;                                    // [MMAX] their row ends
     double *NR = LY::ALIAS ? hval : reinterpret_cast<double *>(gbase + LY::O_AL);  // [NB][LDV]
-    double *LV = NR + NB * LDV;                                                    // [NB+1][LDV]
-    double *NAI = LV + (NB + 1) * LDV;                                             // [NB]: a_{u,i}
+    double *LV = NR + NB * LDV;                                                    // [NB][LDV]
+    double *NAI = LV + NB * LDV;                                             // [NB]: a_{u,i}
     const uint64_t gm = group_bits<GS>(grp);
     const double tauv = tau;
     const int zslot = LY::w_entries(mmx);  // of the padding after W, zero for the matrix products
@@ -712,7 +684,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(GS == 8 || (
         const double psi0 = aii;
         double gi = act ? 1.0 / sqrt(aii) : 0.0;
         int r_col = 0, r_beg = 0, r_len = 0;
-        double r_g = 0.0, r_ai = 0.0, r_li = 0.0;
+        double r_g = 0.0, r_ai = 0.0;
+        double yi = 0.0;  // lane j: (W^T l_i)_j
         uint32_t slr[MMAX][SLW];
 #pragma unroll
         for (int q = 0; q < MMAX; ++q)
@@ -766,54 +739,53 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(GS == 8 || (
 #pragma unroll
                 for (int qb = 0; qb < MMAX; qb += QB) {
                     if (qb <= mo_u) {
-                        int slt[QB][SPW];
+                        // (lanes without an entry load the row's first: loads under a condition
+                        // made the ones behind them wait; 46 positions: 60.7 -> 59.4 ms)
                         AVT aa[QB][SPW];
                         double gg[QB];
+                        int ln[QB];
 #pragma unroll
                         for (int u = 0; u < QB; ++u) {
                             const int q = qb + u;
                             int beg = 0, len = 0;
                             gg[u] = 0.0;
-                            if (q < MMAX && q <= mo_u) {
-                                if constexpr (GS == 64) {
-                                    // member q: row i (q = 0) or position q - 1, uniform values
-                                    if (q == 0) {
-                                        beg = ibeg;
-                                        len = ilen;
-                                        gg[u] = gi;
-                                    } else {
-                                        beg = rlane(r_beg, q - 1);
-                                        len = rlane(r_len, q - 1);
-                                        gg[u] = rlane(r_g, q - 1);
-                                    }
+                            if constexpr (GS < 64) {
+                                const Memb mb = memb[min(q, mo_u)];
+                                beg = mb.beg;
+                                len = q <= mo_u ? mb.len : 0;
+                                gg[u] = mb.g;
+                            } else if (q < MMAX && q <= mo_u) {
+                                // member q: row i (q = 0) or position q - 1, uniform values
+                                if (q == 0) {
+                                    beg = ibeg;
+                                    len = ilen;
+                                    gg[u] = gi;
                                 } else {
-                                    const Memb mb = memb[q];
-                                    beg = mb.beg;
-                                    len = mb.len;
-                                    gg[u] = mb.g;
+                                    beg = rlane(r_beg, q - 1);
+                                    len = rlane(r_len, q - 1);
+                                    gg[u] = rlane(r_g, q - 1);
                                 }
                             }
+                            ln[u] = len;
 #pragma unroll
                             for (int h = 0; h < SPW; ++h) {
                                 const int o = gl + GS * h;
-                                slt[u][h] = -1;
-                                aa[u][h] = AVT(0);
-                                if (q < MMAX && o < len) {
-                                    slt[u][h] = (int)((slr[q < MMAX ? q : 0][h >> 1] >> (16 * (h & 1))) & 0xffffu);
-                                    // cached loads (rows are read again at later steps); FP32 values
-                                    // for the precision form's gradient
-                                    if constexpr (G32) aa[u][h] = av32[beg + o];
-                                    else aa[u][h] = av[beg + o];
-                                }
+                                // cached loads (rows are read again at later steps); FP32 values
+                                // for the precision form's gradient
+                                const int e = beg + (o < len ? o : 0);
+                                if constexpr (G32) aa[u][h] = av32[e];
+                                else aa[u][h] = av[e];
                             }
                         }
 #pragma unroll
                         for (int u = 0; u < QB; ++u)
 #pragma unroll
                             for (int h = 0; h < SPW; ++h)
-                                if (slt[u][h] >= 0)
-                                    __hip_atomic_fetch_add(&hval[slt[u][h]], (double)aa[u][h] * gg[u], __ATOMIC_RELAXED,
+                                if (qb + u < MMAX && gl + GS * h < ln[u]) {
+                                    const uint32_t sl = (slr[qb + u < MMAX ? qb + u : 0][h >> 1] >> (16 * (h & 1))) & 0xffffu;
+                                    __hip_atomic_fetch_add(&hval[sl], (double)aa[u][h] * gg[u], __ATOMIC_RELAXED,
                                                            __HIP_MEMORY_SCOPE_WORKGROUP);
+                                }
                     }
                 }
             }
@@ -900,9 +872,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(GS == 8 || (
 
             // ---- 3./4. gather the new rows and extend W, NB rows at a time
             bool spd = true;
-            double yi = 0.0;  // lane j: (W^T l_i)_j, accumulated over the blocks of this step
             int nsd = 0;
-            bool first = true;
             const int nsw = GS == 64 ? wu<GS>(ns)
                                      : __builtin_amdgcn_readfirstlane((int)gred<64, OpMax>((double)(act ? ns : 0)));
             for (int nw = 0; nw < nsw; nw += NB) {
@@ -1049,11 +1019,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(GS == 8 || (
                 // a_{u,i} of the new positions
                 if (go && gl >= mo && gl < mo + nbk) r_ai = NAI[gl - mo];
 
-                extend_w<GS, MMAX, NB, LDV>(go, mo, mwb, nbk, gl, first, LY::bytes(mmx) / 8, zslot, mmx, s >= 4, Wm, NR, LV, r_ai, r_li, yi, psi, spd, status, act);
+                extend_w<GS, MMAX, NB, LDV>(go, mo, mwb, nbk, gl, LY::bytes(mmx) / 8, zslot, mmx, Wm, NR, LV, r_ai, yi, psi, spd,
+                                            status, act);
                 if (blk) {
                     m_o += nbk;
                     nsd += nbk;
-                    first = false;
                 }
                 wsync();
             }
