@@ -107,8 +107,13 @@ inline int grid1d(int64_t work, const DeviceInfo &di, int threads = 256) {
     return (int)(b < 1 ? 1 : b);
 }
 
+// a few words (4-byte aligned, bytes a multiple of 4) from device memory to the host; synchronous on
+// s.  A one-wavefront kernel stores them to pinned memory: a copy to pageable memory is a kernel
+// as well, but also waits for it inside the call and costs the host twice the time.
+int fetch_words(void *host, const void *dev, size_t bytes, hipStream_t s);
+
 // exclusive scan of cnt[0..n) into out[0..n] (out[n] = total, int32); *total (host) gets the
-// 64-bit total; synchronous on s
+// 64-bit total, synchronous on s (total = nullptr: only enqueued)
 int scan_counts(int n, const int32_t *cnt, int32_t *out, int64_t *total, const DeviceInfo &di, hipStream_t s);
 
 // Blocks of a launch are dealt to the XCDs round robin (block b runs on XCD b % num_xcds).

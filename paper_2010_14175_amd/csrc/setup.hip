@@ -498,8 +498,7 @@ static int build_transpose(afsai_precond_s *P, const DeviceInfo &di, hipStream_t
         hipLaunchKernelGGL(k_fill_i32, dim3(grid1d(n, di)), dim3(256), 0, s, (int64_t)n, cnt.as<int32_t>(), 0);
         hipLaunchKernelGGL(k_count_cols, dim3(grid1d(nnz, di)), dim3(256), 0, s, (int)nnz, P->g_ci, cnt.as<int32_t>());
     }
-    int64_t tot = 0;
-    if ((rc = scan_counts(n, cnt.as<int32_t>(), rp.as<int32_t>(), &tot, di, s))) return rc;
+    if ((rc = scan_counts(n, cnt.as<int32_t>(), rp.as<int32_t>(), nullptr, di, s))) return rc;
     {
         // the fill's pairs, released (after the sort) before the SELL layout takes its memory
         DevBuf pairs;
@@ -585,8 +584,7 @@ static int setup_core(const afsai_csr *A, const afsai_params *p, int nsys, const
         // row pointers must be sane before rows are scanned
         hipLaunchKernelGGL(k_row_ptr_check, dim3((n + 256) / 256), dim3(256), 0, s, n, A->row_ptr, A->nnz,
                            scanb.as<ScanOut>());
-        AFSAI_HIP_TRY(hipMemcpyAsync(&so, scanb.p, sizeof so, hipMemcpyDeviceToHost, s));
-        AFSAI_HIP_TRY(hipStreamSynchronize(s));
+        if ((rc = fetch_words(&so, scanb.p, sizeof so, s))) return rc;
         if (so.bad) AFSAI_FAIL(AFSAI_ERR_BAD_MATRIX, "afsai_setup: row pointers are not monotone from 0 to nnz");
     }
     {
@@ -602,9 +600,7 @@ static int setup_core(const afsai_csr *A, const afsai_params *p, int nsys, const
     if (runs)
         hipLaunchKernelGGL(k_run_check, dim3(grid1d(A->nnz / 3, di)), dim3(256), 0, s, n, (int64_t)A->nnz / 3,
                            A->row_ptr, A->col_idx, scanb.as<ScanOut>());
-    AFSAI_HIP_TRY(hipMemcpyAsync(&so, scanb.p, sizeof so, hipMemcpyDeviceToHost, s));
-    AFSAI_HIP_TRY(hipStreamSynchronize(s));
-    AFSAI_HIP_TRY(hipGetLastError());
+    if ((rc = fetch_words(&so, scanb.p, sizeof so, s))) return rc;
     if (so.bad) AFSAI_FAIL(AFSAI_ERR_BAD_MATRIX, "afsai_setup: CSR structure invalid (columns unsorted, duplicate or out of range)");
     if (so.asym) AFSAI_FAIL(AFSAI_ERR_BAD_MATRIX, "afsai_setup: matrix is not exactly symmetric");
     if (so.nodiag) AFSAI_FAIL(AFSAI_ERR_BAD_MATRIX, "afsai_setup: %d rows without a diagonal entry (or unsorted columns)", so.nodiag);
@@ -620,8 +616,7 @@ static int setup_core(const afsai_csr *A, const afsai_params *p, int nsys, const
         AFSAI_HIP_TRY(hipMemsetAsync(scanb.p, 0, sizeof(ScanOut), s));
         hipLaunchKernelGGL(k_block_check, dim3(grid1d(n, di)), dim3(256), 0, s, n, A->row_ptr, A->col_idx, nsys,
                            r0b.as<int32_t>(), scanb.as<ScanOut>());
-        AFSAI_HIP_TRY(hipMemcpyAsync(&sb, scanb.p, sizeof sb, hipMemcpyDeviceToHost, s));
-        AFSAI_HIP_TRY(hipStreamSynchronize(s));
+        if ((rc = fetch_words(&sb, scanb.p, sizeof sb, s))) return rc;
         if (sb.bad) AFSAI_FAIL(AFSAI_ERR_BAD_MATRIX, "afsai_setup_batched: a row has entries outside its system");
     }
     const int maxlen = so.maxlen > 0 ? so.maxlen : 1;
@@ -723,9 +718,23 @@ static int setup_core(const afsai_csr *A, const afsai_params *p, int nsys, const
                           steps.as<int32_t>(), reason.as<int32_t>(), st.as<int8_t>(), ovf_count, ovf.as<int32_t>(), di,
                           s)))
         return rc;
-    int32_t novf = 0;
-    AFSAI_HIP_TRY(hipMemcpyAsync(&novf, ovf_count, sizeof novf, hipMemcpyDeviceToHost, s));
-    AFSAI_HIP_TRY(hipStreamSynchronize(s));
+    // ---- status summary (of the first launch's rows: how many overflowed their table)
+    const int nsb = grid1d(n, di);
+    DevBuf sumb;
+    if ((rc = dalloc(sumb, sizeof(Summary) * (size_t)(nsb + 1), s))) return rc;
+    Summary sm{};
+    auto summarise = [&]() -> int {
+        Summary *sum_out = sumb.as<Summary>() + nsb;
+        {
+            ProfScope ps("summary", s);
+            hipLaunchKernelGGL(k_summary, dim3(nsb), dim3(256), 0, s, n, mcnt.as<int32_t>(), st.as<int8_t>(),
+                               reason.as<int32_t>(), psi.as<double>(), sumb.as<Summary>());
+            hipLaunchKernelGGL(k_summary_final, dim3(1), dim3(256), 0, s, nsb, sumb.as<Summary>(), sum_out);
+        }
+        return fetch_words(&sm, sum_out, sizeof sm, s);
+    };
+    if ((rc = summarise())) return rc;
+    const int32_t novf = (int32_t)sm.novf;
     int32_t retried = 0;
     if (novf > 0 && cap2 > cap1) {
         retried = novf;
@@ -744,24 +753,8 @@ static int setup_core(const afsai_csr *A, const afsai_params *p, int nsys, const
                               psi.as<double>(), steps.as<int32_t>(), reason.as<int32_t>(), st.as<int8_t>(), cnt2,
                               ovf.as<int32_t>(), di, s)))
             return rc;
-        AFSAI_HIP_TRY(hipStreamSynchronize(s));
+        if ((rc = summarise())) return rc;
     }
-
-    // ---- status summary
-    const int nsb = grid1d(n, di);
-    DevBuf sumb;
-    if ((rc = dalloc(sumb, sizeof(Summary) * (size_t)(nsb + 1), s))) return rc;
-    Summary *sum_out = sumb.as<Summary>() + nsb;
-    {
-        ProfScope ps("summary", s);
-        hipLaunchKernelGGL(k_summary, dim3(nsb), dim3(256), 0, s, n, mcnt.as<int32_t>(), st.as<int8_t>(),
-                           reason.as<int32_t>(), psi.as<double>(), sumb.as<Summary>());
-        hipLaunchKernelGGL(k_summary_final, dim3(1), dim3(256), 0, s, nsb, sumb.as<Summary>(), sum_out);
-    }
-    Summary sm{};
-    AFSAI_HIP_TRY(hipMemcpyAsync(&sm, sum_out, sizeof sm, hipMemcpyDeviceToHost, s));
-    AFSAI_HIP_TRY(hipStreamSynchronize(s));
-    AFSAI_HIP_TRY(hipGetLastError());
     if (sm.nbad) AFSAI_FAIL(AFSAI_ERR_BAD_MATRIX, "afsai_setup: %lld rows without a diagonal entry", (long long)sm.nbad);
     if (sm.nnotspd)
         AFSAI_FAIL(AFSAI_ERR_NOT_SPD, "afsai_setup: %lld rows met a non-positive pivot (A not SPD)", (long long)sm.nnotspd);
@@ -787,8 +780,8 @@ static int setup_core(const afsai_csr *A, const afsai_params *p, int nsys, const
         set_error("afsai_setup: out of device memory");
         return fail(AFSAI_ERR_NO_MEMORY);
     }
-    int64_t nnz = 0;
-    if ((rc = scan_counts(n, mcnt.as<int32_t>(), P->g_rp, &nnz, di, s))) return fail(rc);
+    const int64_t nnz = sm.nnz;
+    if ((rc = scan_counts(n, mcnt.as<int32_t>(), P->g_rp, nullptr, di, s))) return fail(rc);
     P->nnz_g = nnz;
     const size_t vsz = f32 ? sizeof(float) : sizeof(double);
     P->g_ci = (int32_t *)pool_alloc(sizeof(int32_t) * (size_t)nnz);

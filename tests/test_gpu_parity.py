@@ -1141,3 +1141,25 @@ def test_block_products_matrix_loads(af):
     for j in (0, 3):
         assert torch.equal(Y[:, j], M.spmm(X[:, j:j + 1].contiguous())[:, 0])
     M.close()
+
+
+@pytest.mark.parametrize("make,kmax", [
+    (lambda: synth.lap7(3, 1, 1), 1), (lambda: synth.lap7(2048, 1, 1), 2), (lambda: synth.lap7(2049, 1, 1), 2),
+    (lambda: synth.lap7(8192, 1, 1), 2), (lambda: synth.lap7(8193, 1, 1), 2), (lambda: synth.lap7(13, 11, 9), 15),
+    (lambda: synth.random_sparse_spd(1500, 12, 3), 8), (lambda: synth.random_sparse_spd(1501, 60, 4), 12)])
+def test_factor_layouts(af, make, kmax):
+    """Row counts around the tiles of the device scan and around those of the scan by one block; rows of
+    G^T below, at and above 16 entries side by side: G^T G r equals the product with the exported
+    factor within the rounding of its sums."""
+    import scipy.sparse as sp
+
+    A = make()
+    P = af.setup(_dev(af, A), kmax, 1, 1e-3)
+    rp, ci, val = _gpu_factor(af, P)[:3]
+    G = sp.csr_matrix((val, ci, rp), shape=(A.n, A.n))
+    assert G.has_sorted_indices and P.info().nnz_g == rp[-1]
+    r = synth.uniform(7, 9, A.n, -1.0, 1.0)
+    z = P.apply(_vec(r)).cpu().numpy()
+    Ga = abs(G)
+    bound = Ga.T @ (Ga @ abs(r)) * (np.diff(rp).max() + np.diff(G.tocsc().indptr).max() + 4) * 2.0 ** -53
+    assert (abs(z - G.T @ (G @ r)) <= 2 * bound).all()
