@@ -396,7 +396,9 @@ const char *afsai_last_error(void);
  *   AFSAI_OPT_PCG_CSR_A       1: pcg_solve multiplies by A in CSR (group per row) instead of
  *                             converting it to the SELL-64 layout first
  *   AFSAI_OPT_PCG_FORM        0: automatic (products that also form the updated vectors
- *                             below 200,000 rows, separate update kernels above); 1: separate
+ *                             up to 7 M entries of A and G, in a batch below 200,000 rows a
+ *                             system, and a small system's whole solve in one launch where
+ *                             that is faster; separate update kernels above); 1: separate
  *                             update kernels; 2: fused products (used only when no SELL
  *                             matrix of the solve is split, see AFSAI_OPT_SELL_WIDTH); all
  *                             forms give identical results

@@ -36,7 +36,13 @@
 namespace afsai {
 
 constexpr int kThreads = 256;
-constexpr int kFusedMaxRows = 200000;  // automatic PCG form: fused products below this size
+// automatic PCG form: fused products up to these entries of A and G (of one system; their second gather
+// is paid per entry, the update kernels they save per row and per launch), and for the systems of a
+// batch, where the launches are shared, up to these rows.  Microseconds an iteration, fused and
+// separate: 7-point rows, 4.5 M entries 41.6, 48.9; 8.0 M 65.3, 65.8; 13 M 170, 94; 81-entry rows,
+// 6.1 M 50.3, 55.0; 11 M 64.1, 63.8; 20 M 92.3, 87.3
+constexpr int64_t kFusedEntries = 7 << 20;
+constexpr int kFusedMaxRows = 200000;
 constexpr int64_t kSmallBytes = 4 << 20;       // one-launch solve: matrix bytes of an iteration at most
 constexpr int kSmallIters = 1024;              // and iterations of a launch
 constexpr int64_t kGateEntries = 1 << 26;  // factors whose products look at r.r before they start
@@ -1931,7 +1937,8 @@ class PcgRun {
         const int64_t form = option(AFSAI_OPT_PCG_FORM);
         int nmax = 0;
         for (int k = 0; k < nsys_; ++k) nmax = std::max(nmax, row0_[k + 1] - row0_[k]);
-        const bool want_fused = form == 2 || (form == 0 && nmax < kFusedMaxRows);
+        const bool small = nsys_ > 1 ? nmax < kFusedMaxRows : As_.entries + (P_ ? P_->sg.entries : 0) <= kFusedEntries;
+        const bool want_fused = form == 2 || (form == 0 && small);
         fused_ = P_ && use_sell_ && want_fused && !As_.tail && !P_->sg.tail && !As_.perm && !P_->sg.perm;
         bm_.nt = stream_bytes(As_) + (P_ ? stream_bytes(P_->sg) + stream_bytes(P_->sgt) : 0) > kCachedBytes;
         if ((rc = choose_small())) return rc;

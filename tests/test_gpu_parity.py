@@ -1163,3 +1163,25 @@ def test_factor_layouts(af, make, kmax):
     Ga = abs(G)
     bound = Ga.T @ (Ga @ abs(r)) * (np.diff(rp).max() + np.diff(G.tocsc().indptr).max() + 4) * 2.0 ** -53
     assert (abs(z - G.T @ (G @ r)) <= 2 * bound).all()
+
+
+@pytest.mark.parametrize("make", [lambda: synth.lap7(81, 81, 81), lambda: synth.lap7(82, 83, 82),
+                                  lambda: synth.elast27(28, 1.0, 1), lambda: synth.elast27(30, 1.0, 1)])
+def test_pcg_form_by_entries(af, make):
+    """On both sides of the entries up to which the products form the vectors: the automatic form, and
+    both forms asked for, give the same iterates bit for bit."""
+    A = make()
+    dA = _dev(af, A)
+    P = af.setup(dA, 5, 1, 1e-2)
+    b = _vec(synth.uniform(5, 1, A.n, -1.0, 1.0))
+    out = []
+    try:
+        for form in (0, 1, 2):
+            af.set_option(af.OPT_PCG_FORM, form)
+            x, i = af.pcg_solve(dA, P, b, rtol=1e-8)
+            out.append((i.iters, x.cpu().numpy().view(np.int64)))
+    finally:
+        af.set_option(af.OPT_PCG_FORM, 0)
+    for it, x in out[1:]:
+        assert it == out[0][0]
+        np.testing.assert_array_equal(x, out[0][1])
