@@ -534,7 +534,7 @@ def kernel_source_hash(kernel: str) -> str | None:
     import hashlib
 
     files = {"afsai_rows": ["rows.hpp", "rows.hip", "rows_reg.hip", "rows_lds.hip", "rows_f32.hip", "rows_w.hpp",
-                           "rows_w.hip", "rows_w_inst.hpp", "rows_w_g32.hip"]}.get(kernel)
+                           "rows_w.hip", "rows_w_inst.hpp", "rows_w_g32.hip", "rows_b.hpp", "rows_b.hip"]}.get(kernel)
     if not files:
         return None
     h = hashlib.sha256()
