@@ -1772,12 +1772,17 @@ __global__ __launch_bounds__(kThreads) void k_multi_resid(int n, const double *_
     multi_store<K>(part, sh, partials);
 }
 
+// Whether the block form is the faster one: with one or two columns and few nodes its wavefronts, a third
+// as many, only wait longer (K = 1: 41,472 rows 25.2, with blocks 29.4 us; 65,856 rows 32.1, 30.9;
+// K = 4: 24,000 rows 33.7, 32.1)
+static bool blocks_pay(int K, int n) { return K >= 4 || n >= 50000; }
+
 // nt: non-temporal loads of the matrix
 template <int K, bool DOT, bool NT>
 static void spmm_launch_t(const Sell &S, const double *x, double *y, const double *w, double *partials, int nb,
                           const DeviceInfo &di, hipStream_t s, const MultiScal *sc) {
     const dim3 bt(kThreads);
-    if (S.bptr) {
+    if (S.bptr && (!S.val || blocks_pay(K, S.n))) {
         constexpr int L = K >= 8 ? 2 : 1;
         const int nsl = (S.n / 3 + kSlice - 1) / kSlice;
         hipLaunchKernelGGL((k_node_spmm<K, L, NT>), dim3(blocks_for_slices(nsl * L, di)), bt, 0, s, S.n, nsl, S.bptr,
@@ -2450,7 +2455,7 @@ static int pcg_multi(const afsai_csr *A, afsai_precond P, const double *B, doubl
         Sell *S;
         ~Free() { sell_free(S); }
     } free_sa{&SA};
-    if (option(AFSAI_OPT_SELL_RUNS) != 1 && option(AFSAI_OPT_SELL_WIDTH) == 0 && n % 3 == 0) {
+    if (blocks_pay(K, n) && option(AFSAI_OPT_SELL_RUNS) != 1 && option(AFSAI_OPT_SELL_WIDTH) == 0 && n % 3 == 0) {
         // 3 x 3 blocks, unless the rows would be ordered by length (the dots of that layout are
         // summed in another order)
         ProfScope ps("sell_A_blocks", s);
@@ -2601,7 +2606,7 @@ static int spmm_sell(const Sell &S, int32_t k, const double *X, double *Y, const
     {
         ProfScope ps("spmm_A", s);
         const int nb = blocks_for_slices(S.nslices, di);
-        const bool nt = (S.bptr ? S.bentries * 9 : stream_bytes(S)) > kCachedBytes;
+        const bool nt = (S.bptr && blocks_pay(k, S.n) ? S.bentries * 9 : stream_bytes(S)) > kCachedBytes;
         switch (k) {
             case 1: spmm_launch<1, false>(S, nt, X, Y, nullptr, nullptr, nb, di, s); break;
             case 2: spmm_launch<2, false>(S, nt, X, Y, nullptr, nullptr, nb, di, s); break;
