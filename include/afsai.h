@@ -436,7 +436,9 @@ const char *afsai_last_error(void);
  *                             differ by rounding only
  *   AFSAI_OPT_SETUP_LANES     inverse-factor form: lanes that own one row (8, 16, 32 or 64;
  *                             64 / lanes rows per wavefront; 0 automatic: 8 or 16 when they hold
- *                             the pattern, else 64; 32 only when asked for).  A request smaller
+ *                             the pattern, else 64, 32 only when asked for; matrices whose rows
+ *                             are made of aligned runs of three columns take a kernel over the
+ *                             runs, 32 or 64 lanes, while this and AFSAI_OPT_SETUP_TABLE are 0).  A request smaller
  *                             than the pattern takes the next size that holds it.  Any choice
  *                             gives identical G
  *   AFSAI_OPT_SETUP_CLAIM     wavefronts' worth of rows one atomic claim of the setup kernel takes
@@ -446,8 +448,9 @@ const char *afsai_last_error(void);
  *   AFSAI_OPT_SELL_RUNS       pcg_solve's SELL-64 layout of A (separate-update form): 0
  *                             (automatic) one column index per run of three consecutive
  *                             columns when every row of A is made of such runs (3 x 3 blocks
- *                             of a 3-dof discretisation), 1 one index per entry.  Identical
- *                             results.  A prepared matrix takes the setting in force at
+ *                             of a 3-dof discretisation), 1 one index per entry.  Also the 3 x 3
+ *                             blocks of afsai_spmm_prepared and pcg_solve_multi (1: none).
+ *                             Identical results.  A prepared matrix takes the setting in force at
  *                             afsai_matrix_prepare
  * Returns AFSAI_ERR_INVALID_ARG for an unknown option or value.  Not thread safe against
  * concurrent calls of the library.
