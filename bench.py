@@ -432,6 +432,7 @@ def kernel_bytes(name: str, n: int, nnz_a: int, nnz_g: int, w_g: int, kmax: int,
         "spmv_A_dot": 12.0 * nnz_a + rp + 3 * vec,       # + w for the fused dot
         "spmv_G": (4.0 + w_g) * nnz_g + rp + 2 * vec,
         "spmv_GT_dot": (4.0 + w_g) * nnz_g + rp + 3 * vec,
+        "spmv_G_upd": (4.0 + w_g) * nnz_g + rp + 7 * vec,  # G, r q p x; r x t
         "update_xr": 6 * vec,                            # read x p r q, write x r
         "update_p": 3 * vec,                             # read z p, write p
         # setup: every growth step reads the rows of the pattern once (k_max passes over A at
