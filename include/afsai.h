@@ -452,6 +452,9 @@ const char *afsai_last_error(void);
  *                             blocks of afsai_spmm_prepared and pcg_solve_multi (1: none).
  *                             Identical results.  A prepared matrix takes the setting in force at
  *                             afsai_matrix_prepare
+ *   AFSAI_OPT_PCG_ONE_LAUNCH  what the one-launch solves of small systems meet, for tests of what
+ *                             follows: 0 the device as it is; 3 an XCD that no block runs on.
+ *                             Identical results
  * Returns AFSAI_ERR_INVALID_ARG for an unknown option or value.  Not thread safe against
  * concurrent calls of the library.
  */
@@ -470,6 +473,7 @@ const char *afsai_last_error(void);
 #define AFSAI_OPT_SETUP_LANES 13
 #define AFSAI_OPT_SETUP_CLAIM 14
 #define AFSAI_OPT_SELL_RUNS 15
+#define AFSAI_OPT_PCG_ONE_LAUNCH 16
 int afsai_set_option(int32_t option, int64_t value);
 
 /*

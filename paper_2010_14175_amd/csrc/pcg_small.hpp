@@ -23,6 +23,9 @@ namespace afsai {
 constexpr int kSmallWin = 2;                        // windows of a block at most (8 wavefronts)
 constexpr long long kSmallWait = 20LL * 100000000;  // longest wait at a barrier: 20 s of the 100 MHz clock
 
+// what a launch leaves in the record's last word; the host puts SMALL_ABSENT there before it
+enum : int { SMALL_RAN = 0, SMALL_UNMET = 1, SMALL_LOST = 2, SMALL_ABSENT = 3 };
+
 // control words of a solve (zeroed before its launch)
 struct SmallCtl {
     int32_t ticket;   // ranks given out
@@ -370,8 +373,8 @@ __global__ __launch_bounds__(kSmallWin * kThreads) __attribute__((amdgpu_waves_p
     };
     const bool ok = solve();
     if (threadIdx.x == 0 && (rank == 0 || !ok)) {
-        // given up: 1 before anything but the work vectors was written (the start's four barriers), else 2
-        st.pad = ok ? 0 : (a.iter0 == 0 && phase <= 4 ? 1 : 2);
+        // given up: UNMET before anything but the work vectors was written (the start's four barriers)
+        st.pad = ok ? SMALL_RAN : (a.iter0 == 0 && phase <= 4 ? SMALL_UNMET : SMALL_LOST);
         *a.sc = st;
         *a.host = st;
     }

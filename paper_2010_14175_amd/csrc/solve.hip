@@ -2170,6 +2170,7 @@ class PcgRun {
                         (const double *)As_.val, P_->sg.val, P_->sgt.val, P_->sgt.perm, P_->sgt.lens, b_, x_, r_, r2_, z_,
                         p_, p2_, q_, t_, partials_, pa_rr_, pa_rz_, sc_, dhs_[0], (SmallCtl *)ctl_, blocks, xcc,
                         bm_.vec.nblocks, 0, kSmallIters};
+        if (option(AFSAI_OPT_PCG_ONE_LAUNCH) == 3) sa_.xcc = __builtin_ctz(~mask);  // (bit 16 at the latest)
         small_grid_ = dim3((unsigned)(blocks * nx));
         small_block_ = dim3((unsigned)(ng * kThreads));
         small_ = true;
@@ -2178,6 +2179,10 @@ class PcgRun {
 
     // up to kSmallIters iterations from sa_.iter0 on
     int enqueue_small() {
+        // the record comes from a cache and may hold an earlier solve's end: marked, so that a launch
+        // of which no block reached the XCD is seen (its stream is idle here)
+        hs_[0][0] = PcgScalars{};
+        hs_[0][0].pad = SMALL_ABSENT;
         if (sa_.iter0 == 0)
             hipLaunchKernelGGL(k_set_scalars, dim3(1), dim3(256), 0, s_, sc_, bad_, ctl_, 1, rtol_, maxit_, 0);
         else
@@ -2204,11 +2209,12 @@ class PcgRun {
             if (q != hipSuccess) AFSAI_HIP_TRY(q);
         }
         const PcgScalars &st = hs_[0][0];
-        if (st.pad == 1) {  // its blocks did not come together (x is untouched): the usual launches
+        // no block ran, or they did not come together (x is untouched): the usual launches
+        if (sa_.iter0 == 0 && (st.pad == SMALL_UNMET || st.pad == SMALL_ABSENT)) {
             small_ = false;
             return start();
         }
-        if (st.pad) AFSAI_FAIL(AFSAI_ERR_HIP, "pcg_solve: the blocks of a one-launch solve lost each other");
+        if (st.pad != SMALL_RAN) AFSAI_FAIL(AFSAI_ERR_HIP, "pcg_solve: the blocks of a one-launch solve lost each other");
         if (st.done != DONE_NO) {
             done_ = true;
             *finished = true;
