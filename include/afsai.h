@@ -345,6 +345,19 @@ int pcg_solve_prepared(afsai_matrix M, afsai_precond P, const double *b, double 
 int pcg_solve_multi(const afsai_csr *A, afsai_precond P, int32_t k, const double *B, double *X, double rtol,
                     int32_t maxit, void *stream, afsai_pcg_info *info);
 
+/*
+ * afsai_pcg_form_counts -- how the calls of pcg_solve, pcg_solve_prepared and pcg_solve_batched and
+ *   the requests of servers have been solved since the library was loaded (host, all threads):
+ *   counts[AFSAI_PCG_ONE_LAUNCH] solves begun in one launch, counts[AFSAI_PCG_UNMET] those of them that
+ *   went on with the launches of the fused form, counts[AFSAI_PCG_FUSED] solves with fused products
+ *   (the former among them), counts[AFSAI_PCG_SEPARATE] solves with separate update kernels.
+ */
+#define AFSAI_PCG_ONE_LAUNCH 0
+#define AFSAI_PCG_UNMET 1
+#define AFSAI_PCG_FUSED 2
+#define AFSAI_PCG_SEPARATE 3
+int afsai_pcg_form_counts(int64_t counts[4]);
+
 /* afsai_get_setup_info -- diagnostics of a handle (host struct). */
 int afsai_get_setup_info(afsai_precond P, afsai_setup_info *info);
 

@@ -34,7 +34,7 @@ EXPORTS = ("afsai_setup", "afsai_apply", "afsai_apply_noalloc", "pcg_solve", "af
            "afsai_server_create", "afsai_server_submit", "afsai_server_poll", "afsai_server_pending",
            "afsai_server_destroy", "afsai_spmv", "afsai_spmm", "pcg_solve_multi",
            "afsai_matrix_prepare", "afsai_matrix_destroy", "afsai_spmm_prepared", "pcg_solve_prepared",
-           "afsai_get_setup_info", "afsai_export",
+           "afsai_pcg_form_counts", "afsai_get_setup_info", "afsai_export",
            "afsai_export_rows", "afsai_import", "afsai_destroy", "afsai_last_error", "afsai_set_option",
            "afsai_release_cache",
            "afsai_profile_enable", "afsai_profile_only", "afsai_profile_read")
@@ -124,6 +124,7 @@ def lib():
         L.afsai_setup_batched.argtypes = [P(CsrStruct), i32, P(i32), P(ParamsStruct), vp, P(vp)]
         L.pcg_solve_batched.argtypes = [P(CsrStruct), vp, i32, P(i32), vp, vp, ctypes.c_double, i32, vp,
                                         P(PcgInfoStruct)]
+        L.afsai_pcg_form_counts.argtypes = [P(ctypes.c_int64)]
         L.afsai_get_setup_info.argtypes = [vp, P(SetupInfoStruct)]
         L.afsai_export.argtypes = [vp, vp, vp, vp, vp]
         L.afsai_export_rows.argtypes = [vp, vp, vp, vp, vp]
@@ -581,6 +582,14 @@ def release_cache():
 def set_option(option: int, value: int):
     """Process-wide tuning knob (``afsai_set_option``); 0 restores the automatic choice."""
     _check(lib().afsai_set_option(int(option), int(value)), "afsai_set_option")
+
+
+def pcg_form_counts() -> dict:
+    """Solves begun in one launch, those that went on otherwise, solves with fused products and with
+    separate updates, since the library was loaded (``afsai_pcg_form_counts``)."""
+    c = (ctypes.c_int64 * 4)()
+    _check(lib().afsai_pcg_form_counts(c), "afsai_pcg_form_counts")
+    return dict(zip(("one_launch", "unmet", "fused", "separate"), c))
 
 
 def profile_enable(on: bool = True):

@@ -954,6 +954,8 @@ static int blocks_for_slices(int nslices, const DeviceInfo &di) {
     return (int)nb;
 }
 
+static std::atomic<int64_t> g_forms[4];  // afsai_pcg_form_counts
+
 // the device's XCDs as bits of their hardware numbers (looked up on the first call)
 static int xcc_mask(const DeviceInfo &di, hipStream_t s, uint32_t *mask) {
     constexpr int kMaxDev = 64;
@@ -1947,13 +1949,16 @@ class PcgRun {
         fused_ = P_ && use_sell_ && want_fused && !As_.tail && !P_->sg.tail && !As_.perm && !P_->sg.perm;
         bm_.nt = stream_bytes(As_) + (P_ ? stream_bytes(P_->sg) + stream_bytes(P_->sgt) : 0) > kCachedBytes;
         if ((rc = choose_small())) return rc;
-        return small_ ? enqueue_small() : start();
+        if (!small_) return start();
+        ++g_forms[AFSAI_PCG_ONE_LAUNCH];
+        return enqueue_small();
     }
 
     // The start of the iteration and its first chunk
     int start() {
         const int n = A_.n;
         int rc;
+        ++g_forms[fused_ ? AFSAI_PCG_FUSED : AFSAI_PCG_SEPARATE];
         const dim3 gv(bm_.vec.nblocks), gs(bm_.nsys);
         const int plain = P_ ? 0 : 1;
         hipLaunchKernelGGL(k_set_scalars, dim3((nsys_ + 255) / 256), dim3(256), 0, s_, sc_, bad_, ctl_, nsys_, rtol_,
@@ -2212,6 +2217,7 @@ class PcgRun {
         // no block ran, or they did not come together (x is untouched): the usual launches
         if (sa_.iter0 == 0 && (st.pad == SMALL_UNMET || st.pad == SMALL_ABSENT)) {
             small_ = false;
+            ++g_forms[AFSAI_PCG_UNMET];
             return start();
         }
         if (st.pad != SMALL_RAN) AFSAI_FAIL(AFSAI_ERR_HIP, "pcg_solve: the blocks of a one-launch solve lost each other");
@@ -2434,6 +2440,12 @@ static int pcg_batch(const afsai_csr *A, afsai_precond P, int nsys, const int32_
 using namespace afsai;
 
 extern "C" {
+
+int afsai_pcg_form_counts(int64_t counts[4]) {
+    if (!counts) AFSAI_FAIL(AFSAI_ERR_INVALID_ARG, "afsai_pcg_form_counts: null argument");
+    for (int k = 0; k < 4; ++k) counts[k] = g_forms[k].load(std::memory_order_relaxed);
+    return AFSAI_OK;
+}
 
 int afsai_spmv(const afsai_csr *A, const double *x, double *y, void *stream) {
     int rc = check_csr_arg(A, "afsai_spmv");

@@ -42,6 +42,25 @@ def _solve(af, dA, P, b, x0=None, options=(), **kw):
     return i.status, i.iters, i.converged, i.relres, i.true_relres, x.cpu().numpy().view(np.int64)
 
 
+class _Forms:
+    """What the solves inside the block added to the counts of the forms."""
+
+    def __init__(self, af):
+        self.af = af
+
+    def __enter__(self):
+        self.before = self.af.pcg_form_counts()
+        return self
+
+    def __exit__(self, *a):
+        now = self.af.pcg_form_counts()
+        self.one_launch, self.unmet, self.fused, self.separate = (
+            now[k] - self.before[k] for k in ("one_launch", "unmet", "fused", "separate"))
+
+    def __call__(self):
+        return self.one_launch, self.unmet, self.fused, self.separate
+
+
 def _same(p, q):
     assert p[:5] == q[:5], (p[:5], q[:5])
     np.testing.assert_array_equal(p[5], q[5])
@@ -58,4 +77,44 @@ def test_no_block_on_the_xcd(af, sides):
     x0 = _vec(synth.uniform(9, 2, A.n))
     want = _solve(af, dA, P, b2, x0, [(af.OPT_PCG_FORM, 2)], rtol=1e-8)
     _solve(af, dA, P, b1, rtol=1e-8)
-    _same(_solve(af, dA, P, b2, x0, [(af.OPT_PCG_ONE_LAUNCH, 3)], rtol=1e-8), want)
+    with _Forms(af) as forms:
+        got = _solve(af, dA, P, b2, x0, [(af.OPT_PCG_ONE_LAUNCH, 3)], rtol=1e-8)
+    _same(got, want)
+    assert forms() == (1, 1, 1, 0)
+
+
+@pytest.mark.parametrize("make,kmax,g,want", [
+    (lambda: synth.lap7(1, 1, 1), 1, 0, (1, 0, 0, 0)), (lambda: synth.lap7(320, 1, 1), 2, 0, (1, 0, 0, 0)),
+    (lambda: synth.lap7(20, 20, 20), 5, 1, (1, 0, 0, 0)), (lambda: synth.lap7(16, 32, 16), 0, 0, (1, 0, 0, 0)),
+    (lambda: synth.lap7(25, 25, 26), 5, 0, (1, 0, 0, 0)), (lambda: synth.lap7(26, 26, 26), 5, 0, (0, 0, 1, 0)),
+    (lambda: synth.lap7(20, 20, 41), 5, 0, (0, 0, 1, 0)), (lambda: synth.elast27(24, 1.0, 2), 10, 0, (0, 0, 1, 0)),
+    (lambda: synth.lap7(99, 100, 101), 5, 0, (0, 0, 0, 1))])
+def test_form_of_a_solve(af, make, kmax, g, want):
+    """Which form the automatic choice takes on both sides of its limits (one launch up to 16,384 rows of 7
+    entries, fused products up to 7 M entries; whole slices, as other layouts order A's rows by length
+    and take separate updates), a solve at a time; the option takes the others."""
+    A = make()
+    dA = af.DeviceCSR.from_host(A)
+    P = af.setup(dA, kmax, 1, 1e-2, g_prec=g)
+    b = _vec(synth.uniform(5, 1, A.n, -1.0, 1.0))
+    with _Forms(af) as forms:
+        auto = _solve(af, dA, P, b, rtol=1e-8)
+    assert forms() == want
+    for form, other in ((1, (0, 0, 0, 1)), (2, (0, 0, 1, 0))):
+        with _Forms(af) as forms:
+            got = _solve(af, dA, P, b, options=[(af.OPT_PCG_FORM, form)], rtol=1e-8)
+        assert forms() == other
+        assert got[1] == auto[1]
+        np.testing.assert_array_equal(got[5], auto[5])
+
+
+def test_continued_launch_form(af):
+    """A solve of more iterations than a launch takes stays in its form, launch after launch."""
+    A = synth.lap7(3000, 1, 1, (1.0, 1e-9, 1e-9))
+    dA = af.DeviceCSR.from_host(A)
+    P = af.setup(dA, 0, 1, 1e-2)
+    b = _vec(synth.uniform(5, 1, A.n))
+    with _Forms(af) as forms:
+        got = _solve(af, dA, P, b, rtol=1e-10)
+    assert forms() == (1, 0, 0, 0) and got[1] > 1024
+    _same(got, _solve(af, dA, P, b, options=[(af.OPT_PCG_FORM, 2)], rtol=1e-10))
