@@ -466,8 +466,8 @@ const char *afsai_last_error(void);
  *                             Identical results.  A prepared matrix takes the setting in force at
  *                             afsai_matrix_prepare
  *   AFSAI_OPT_PCG_ONE_LAUNCH  what the one-launch solves of small systems meet, for tests of what
- *                             follows: 0 the device as it is; 3 an XCD that no block runs on.
- *                             Identical results
+ *                             follows: 0 the device as it is; 1 a block that does not come to the
+ *                             first meeting; 3 an XCD that no block runs on.  Identical results
  * Returns AFSAI_ERR_INVALID_ARG for an unknown option or value.  Not thread safe against
  * concurrent calls of the library.
  */

@@ -10,8 +10,8 @@
 // find themselves on the chosen XCD (its number is read from the hardware register, not assumed) take
 // a rank each, the others return.  Vectors are written with plain stores, which reach the shared
 // L2 before a thread arrives at the barrier (vmcnt(0)), and read with agent-scope loads, which pass
-// the CU's own L1 by and hit in that L2.  Every wait is bounded: a block that waits longer than
-// kSmallWait gives up, all others then do, and the host solves the system the usual way.
+// the CU's own L1 by and hit in that L2.  Every wait is bounded: a block that waits too
+// long gives up, all others then do, and the host solves the system the usual way.
 //
 // The arithmetic is the fused products' (k_sell_fused, k_sell_spmv): the same windows of four
 // slices (one partial sum each), the same vector blocks at the start and for the final
@@ -21,7 +21,11 @@
 namespace afsai {
 
 constexpr int kSmallWin = 2;                        // windows of a block at most (8 wavefronts)
-constexpr long long kSmallWait = 20LL * 100000000;  // longest wait at a barrier: 20 s of the 100 MHz clock
+// Longest waits, in ticks of the 100 MHz clock.  At a launch's first barrier, where blocks that found no room may be
+// missing (three solves' blocks on one XCD can keep each other out) and giving up costs nothing: 10 ms.  At
+// the later ones all blocks are there and run; only a stopped queue is waited for: 20 s.
+constexpr long long kSmallMeet = 1000000;
+constexpr long long kSmallWait = 20LL * 100000000;
 
 // what a launch leaves in the record's last word; the host puts SMALL_ABSENT there before it
 enum : int { SMALL_RAN = 0, SMALL_UNMET = 1, SMALL_LOST = 2, SMALL_ABSENT = 3 };
@@ -48,6 +52,7 @@ struct SmallArgs {
     SmallCtl *ctl;
     int blocks, xcc, nbv;  // blocks that take part, their XCD, vector blocks
     int iter0, iters;      // iterations done before this launch, and most of it
+    int miss;              // arrivals that the first barrier waits for and nobody makes (0 but in tests)
 };
 
 // pointers in the global address space (a flat load would also wait for LDS)
@@ -187,7 +192,8 @@ __global__ __launch_bounds__(kSmallWin * kThreads) __attribute__((amdgpu_waves_p
         ++phase;
         if (threadIdx.x == 0) {
             __hip_atomic_fetch_add(glob(&a.ctl->arrive), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const uint32_t want = phase * (uint32_t)a.blocks;
+            const uint32_t want = phase * (uint32_t)a.blocks + (phase == 1 ? (uint32_t)a.miss : 0u);
+            const long long longest = phase == 1 ? kSmallMeet : kSmallWait;
             int dead = 0;
             // (the clock and the other blocks' state only now and then: both are slow to read)
             long long t0 = 0;
@@ -197,7 +203,7 @@ __global__ __launch_bounds__(kSmallWin * kThreads) __attribute__((amdgpu_waves_p
                 const long long now = wall_clock64();
                 if (t0 == 0) t0 = now;
                 if (__hip_atomic_load(glob(&a.ctl->dead), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ||
-                    now - t0 > kSmallWait) {
+                    now - t0 > longest) {
                     __hip_atomic_store(glob(&a.ctl->dead), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     dead = 1;
                     break;

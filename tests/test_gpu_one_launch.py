@@ -4,6 +4,8 @@ those of that form (AFSAI_OPT_PCG_FORM = 2) bit for bit.
 
 What the launch meets is set from the host (AFSAI_OPT_PCG_ONE_LAUNCH); every kernel ends by itself.
 """
+import time
+
 import numpy as np
 import pytest
 
@@ -118,3 +120,21 @@ def test_continued_launch_form(af):
         got = _solve(af, dA, P, b, rtol=1e-10)
     assert forms() == (1, 0, 0, 0) and got[1] > 1024
     _same(got, _solve(af, dA, P, b, options=[(af.OPT_PCG_FORM, 2)], rtol=1e-10))
+
+
+@pytest.mark.parametrize("sides", [(1, 1, 1), (13, 13, 13), (25, 25, 26)])
+def test_blocks_that_do_not_meet(af, sides):
+    """A block that never comes to the first barrier (as when other solves hold its place): the others give
+    up within milliseconds and the solve runs with the ordinary launches from the given x0."""
+    A = synth.lap7(*sides)
+    dA = af.DeviceCSR.from_host(A)
+    P = af.setup(dA, 5, 1, 1e-2)
+    b = _vec(synth.uniform(5, 1, A.n, -1.0, 1.0))
+    x0 = _vec(synth.uniform(9, 2, A.n))
+    want = _solve(af, dA, P, b, x0, [(af.OPT_PCG_FORM, 2)], rtol=1e-8)
+    t0 = time.monotonic()
+    with _Forms(af) as forms:
+        got = _solve(af, dA, P, b, x0, [(af.OPT_PCG_ONE_LAUNCH, 1)], rtol=1e-8)
+    assert time.monotonic() - t0 < 2.0
+    assert forms() == (1, 1, 1, 0)
+    _same(got, want)
