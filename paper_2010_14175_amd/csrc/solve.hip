@@ -24,6 +24,8 @@
 // release per block, which on this 8-XCD part writes back the L2 and cost more than the extra
 // launch.)  A device flag ends the iteration: kernels that see it return at once, so the host
 // enqueues chunks of iterations and reads the flag once per chunk, one chunk behind.
+#include <unistd.h>
+
 #include <algorithm>
 #include <atomic>
 #include <chrono>
@@ -45,6 +47,7 @@ constexpr int64_t kFusedEntries = 7 << 20;
 constexpr int kFusedMaxRows = 200000;
 constexpr int64_t kSmallBytes = 4 << 20;       // one-launch solve: matrix bytes of an iteration at most
 constexpr int kSmallIters = 1024;              // and iterations of a launch
+constexpr int kSmallPause = 64;                // solves that do not try it after one whose blocks did not meet
 constexpr int64_t kGateEntries = 1 << 26;  // factors whose products look at r.r before they start
 // resumable solver: iterations of the first chunk, least GPU time of a chunk and its share of
 // the GPU time so far
@@ -979,6 +982,44 @@ static int xcc_mask(const DeviceInfo &di, hipStream_t s, uint32_t *mask) {
     return AFSAI_OK;
 }
 
+// The one-launch solves in flight on each XCD.  Two fit as a whole (pcg_small.hpp), and blocks of a third could keep
+// each other and theirs out, so no more than two are let there; a further solve takes the ordinary launches.
+// Where blocks did not meet all the same (another process on the device), the next kSmallPause solves of the
+// device do not try.  A process's first XCD follows from its number, so that processes start on different ones.
+class SmallPlaces {
+  public:
+    // an XCD of the mask for another solve: of those with the fewest solves the next in turn; -1: none
+    int take(uint32_t mask) {
+        std::lock_guard<std::mutex> lk(mu_);
+        if (pause_ > 0) {
+            --pause_;
+            return -1;
+        }
+        int best = -1;
+        for (int j = 0; j < 16; ++j) {
+            const int x = (int)((turn_ + j) % 16);
+            if ((mask >> x & 1) && used_[x] < 2 && (best < 0 || used_[x] < used_[best])) best = x;
+        }
+        if (best >= 0) {
+            ++used_[best];
+            turn_ = best + 1;
+        }
+        return best;
+    }
+    void give(int x, bool unmet) {
+        std::lock_guard<std::mutex> lk(mu_);
+        --used_[x];
+        if (unmet) pause_ = kSmallPause;
+    }
+
+  private:
+    std::mutex mu_;
+    int used_[16] = {};
+    unsigned turn_ = (unsigned)getpid();
+    int pause_ = 0;
+};
+static SmallPlaces g_places[64];  // by device
+
 struct Csr {
     int n = 0;
     int64_t nnz = 0;
@@ -1868,6 +1909,7 @@ class PcgRun {
     }
     ~PcgRun() {
         if (started_) (void)hipStreamSynchronize(s_);
+        leave_place(false);
         for (int k = 0; k < 2; ++k) {
             if (gexec_[k]) (void)hipGraphExecDestroy(gexec_[k]);
             if (graph_[k]) (void)hipGraphDestroy(graph_[k]);
@@ -2164,13 +2206,9 @@ class PcgRun {
         const int ng = std::min(kSmallWin, (nw + cus - 1) / cus);
         const int blocks = std::min(cus, (nw + ng - 1) / ng);
         if (nw > blocks * ng) return AFSAI_OK;
-        // solves take the XCDs in turn
-        static std::atomic<uint32_t> turn{0};
-        int pick = (int)(turn.fetch_add(1, std::memory_order_relaxed) % (uint32_t)nx), xcc = 0;
-        for (uint32_t m = mask;; m &= m - 1) {
-            xcc = __builtin_ctz(m);
-            if (pick-- == 0) break;
-        }
+        const int xcc = g_places[di_.device].take(mask);
+        if (xcc < 0) return AFSAI_OK;
+        place_ = xcc;
         sa_ = SmallArgs{A_.n, As_.nslices, (int)As_.entries, (int)P_->sg.entries, (int)P_->sgt.entries, As_.sptr, P_->sg.sptr, P_->sgt.sptr, As_.col, P_->sg.col, P_->sgt.col,
                         (const double *)As_.val, P_->sg.val, P_->sgt.val, P_->sgt.perm, P_->sgt.lens, b_, x_, r_, r2_, z_,
                         p_, p2_, q_, t_, partials_, pa_rr_, pa_rz_, sc_, dhs_[0], (SmallCtl *)ctl_, blocks, xcc,
@@ -2180,6 +2218,11 @@ class PcgRun {
         small_block_ = dim3((unsigned)(ng * kThreads));
         small_ = true;
         return AFSAI_OK;
+    }
+
+    void leave_place(bool unmet) {
+        if (place_ >= 0) g_places[di_.device].give(place_, unmet);
+        place_ = -1;
     }
 
     // up to kSmallIters iterations from sa_.iter0 on
@@ -2218,11 +2261,13 @@ class PcgRun {
         // no block ran, or they did not come together (x is untouched): the usual launches
         if (sa_.iter0 == 0 && (st.pad == SMALL_UNMET || st.pad == SMALL_ABSENT)) {
             small_ = false;
+            leave_place(true);
             ++g_forms[AFSAI_PCG_UNMET];
             return start();
         }
         if (st.pad != SMALL_RAN) AFSAI_FAIL(AFSAI_ERR_HIP, "pcg_solve: the blocks of a one-launch solve lost each other");
         if (st.done != DONE_NO) {
+            leave_place(false);
             done_ = true;
             *finished = true;
             return AFSAI_OK;
@@ -2388,6 +2433,7 @@ class PcgRun {
     int32_t *bad_ = nullptr;    // [nsys]
     int32_t *ctl_ = nullptr;
     bool small_ = false;        // the whole solve in one launch (pcg_small.hpp)
+    int place_ = -1;            // its XCD among g_places
     SmallArgs sa_{};
     dim3 small_grid_, small_block_;
     PcgScalars *hsc_ = nullptr;

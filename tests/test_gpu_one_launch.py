@@ -26,6 +26,23 @@ def af():
     return af
 
 
+PAUSE = 64  # solves that take the ordinary launches after blocks that did not meet
+
+
+@pytest.fixture(autouse=True)
+def _one_launch_again(af):
+    """Every test starts where small systems are tried in one launch."""
+    A = synth.lap7(1, 1, 1)
+    dA = af.DeviceCSR.from_host(A)
+    P = af.setup(dA, 1, 1, 1e-2)
+    for _ in range(PAUSE + 1):
+        with _Forms(af) as forms:
+            af.pcg_solve(dA, P, _vec([1.0]))
+        if forms.one_launch:
+            break
+    assert forms() == (1, 0, 0, 0)
+
+
 def _vec(x):
     import torch
 
@@ -138,3 +155,56 @@ def test_blocks_that_do_not_meet(af, sides):
     assert time.monotonic() - t0 < 2.0
     assert forms() == (1, 1, 1, 0)
     _same(got, want)
+
+
+def test_pause_after_blocks_that_did_not_meet(af):
+    """Blocks that did not meet once: the next solves do not try, the one after them does."""
+    A = synth.lap7(5, 4, 3)
+    dA = af.DeviceCSR.from_host(A)
+    P = af.setup(dA, 5, 1, 1e-2)
+    b = _vec(synth.uniform(5, 1, A.n, -1.0, 1.0))
+    want = _solve(af, dA, P, b, options=[(af.OPT_PCG_FORM, 2)], rtol=1e-8)
+    _solve(af, dA, P, b, options=[(af.OPT_PCG_ONE_LAUNCH, 1)], rtol=1e-8)
+    for k in range(PAUSE + 1):
+        with _Forms(af) as forms:
+            got = _solve(af, dA, P, b, rtol=1e-8)
+        assert forms() == ((1, 0, 0, 0) if k == PAUSE else (0, 0, 1, 0)), k
+        _same(got, want)
+
+
+def test_places_on_the_xcds(af):
+    """24 solves from as many threads, on streams of their own, each in flight for milliseconds because an
+    arrival is missing: two go to each of the 8 XCDs at most, the others take the ordinary launches."""
+    import threading
+
+    import torch
+
+    A = synth.lap7(13, 13, 13)
+    dA = af.DeviceCSR.from_host(A)
+    b = _vec(synth.uniform(5, 1, A.n, -1.0, 1.0))
+    Ps = [af.setup(dA, 5, 1, 1e-2) for _ in range(24)]
+    want = _solve(af, dA, Ps[0], b, options=[(af.OPT_PCG_FORM, 2)], rtol=1e-8)
+    streams = [torch.cuda.Stream() for _ in Ps]
+    xs = [torch.zeros_like(b) for _ in Ps]
+    torch.cuda.synchronize()
+    out, gate = [None] * len(Ps), threading.Barrier(len(Ps))
+
+    def work(k):
+        gate.wait()
+        _, i = af.pcg_solve(dA, Ps[k], b, x=xs[k], rtol=1e-8, stream=streams[k])
+        out[k] = (i.status, i.iters, i.converged, i.relres, i.true_relres)
+
+    try:
+        af.set_option(af.OPT_PCG_ONE_LAUNCH, 1)
+        with _Forms(af) as forms:
+            ts = [threading.Thread(target=work, args=(k,)) for k in range(len(Ps))]
+            for t in ts:
+                t.start()
+            for t in ts:
+                t.join()
+    finally:
+        af.set_option(af.OPT_PCG_ONE_LAUNCH, 0)
+    torch.cuda.synchronize()
+    assert 1 <= forms.one_launch <= 16 and forms.unmet == forms.one_launch and forms.fused == len(Ps)
+    for k in range(len(Ps)):
+        _same(out[k] + (xs[k].cpu().numpy().view(np.int64),), want)
