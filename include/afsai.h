@@ -467,7 +467,8 @@ const char *afsai_last_error(void);
  *                             afsai_matrix_prepare
  *   AFSAI_OPT_PCG_ONE_LAUNCH  what the one-launch solves of small systems meet, for tests of what
  *                             follows: 0 the device as it is; 1 a block that does not come to the
- *                             first meeting; 3 an XCD that no block runs on.  Identical results
+ *                             first meeting; 2 the same in a launch that continues a solve; 3 an
+ *                             XCD that no block runs on.  Identical results
  * Returns AFSAI_ERR_INVALID_ARG for an unknown option or value.  Not thread safe against
  * concurrent calls of the library.
  */

@@ -379,8 +379,9 @@ __global__ __launch_bounds__(kSmallWin * kThreads) __attribute__((amdgpu_waves_p
     };
     const bool ok = solve();
     if (threadIdx.x == 0 && (rank == 0 || !ok)) {
-        // given up: UNMET before anything but the work vectors was written (the start's four barriers)
-        st.pad = ok ? SMALL_RAN : (a.iter0 == 0 && phase <= 4 ? SMALL_UNMET : SMALL_LOST);
+        // given up: UNMET while x, r, z, p and the scalars are those from before the launch (its first
+        // barrier; of the first launch, which can be begun anew, the start's four)
+        st.pad = ok ? SMALL_RAN : (phase <= (a.iter0 == 0 ? 4u : 1u) ? SMALL_UNMET : SMALL_LOST);
         *a.sc = st;
         *a.host = st;
     }

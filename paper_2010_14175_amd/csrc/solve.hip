@@ -2033,6 +2033,20 @@ class PcgRun {
         if (!fused_)
             hipLaunchKernelGGL(k_update_p, gv, dim3(kThreads), 0, s_, n, p_, zz_, sc_, (PcgScalars *)nullptr, bad_,
                                Parts(), Parts(), 1, bm_.vec.mp, bm_.sy, di_.num_xcds);
+        return start_chunks();
+    }
+
+    // The launches of the fused form from iteration `done` on, an even number of iterations after the start: p and r
+    // are in the first of their buffers, the scalars, with the last step taken, too
+    int go_on(int done) {
+        static_assert(kSmallIters % 2 == 0, "the buffers of a continued solve");
+        ++g_forms[AFSAI_PCG_FUSED];
+        iter_no_ = enqueued_ = done;
+        return start_chunks();
+    }
+
+    int start_chunks() {
+        int rc;
         mark0_ = prof_mark();
         prev_it_.assign(nsys_, 0);
         prev_rr_.assign(nsys_, 0.0);
@@ -2231,7 +2245,7 @@ class PcgRun {
         // of which no block reached the XCD is seen (its stream is idle here)
         hs_[0][0] = PcgScalars{};
         hs_[0][0].pad = SMALL_ABSENT;
-        sa_.miss = option(AFSAI_OPT_PCG_ONE_LAUNCH) == 1 && sa_.iter0 == 0;
+        sa_.miss = option(AFSAI_OPT_PCG_ONE_LAUNCH) == (sa_.iter0 == 0 ? 1 : 2);
         if (sa_.iter0 == 0)
             hipLaunchKernelGGL(k_set_scalars, dim3(1), dim3(256), 0, s_, sc_, bad_, ctl_, 1, rtol_, maxit_, 0);
         else
@@ -2258,12 +2272,13 @@ class PcgRun {
             if (q != hipSuccess) AFSAI_HIP_TRY(q);
         }
         const PcgScalars &st = hs_[0][0];
-        // no block ran, or they did not come together (x is untouched): the usual launches
-        if (sa_.iter0 == 0 && (st.pad == SMALL_UNMET || st.pad == SMALL_ABSENT)) {
+        // no block ran, or they did not come together: the usual launches, from the start or from the
+        // iteration where the launch before ended
+        if (st.pad == SMALL_UNMET || st.pad == SMALL_ABSENT) {
             small_ = false;
             leave_place(true);
             ++g_forms[AFSAI_PCG_UNMET];
-            return start();
+            return sa_.iter0 == 0 ? start() : go_on(sa_.iter0);
         }
         if (st.pad != SMALL_RAN) AFSAI_FAIL(AFSAI_ERR_HIP, "pcg_solve: the blocks of a one-launch solve lost each other");
         if (st.done != DONE_NO) {
