@@ -468,7 +468,8 @@ const char *afsai_last_error(void);
  *   AFSAI_OPT_PCG_ONE_LAUNCH  what the one-launch solves of small systems meet, for tests of what
  *                             follows: 0 the device as it is; 1 a block that does not come to the
  *                             first meeting; 2 the same in a launch that continues a solve; 3 an
- *                             XCD that no block runs on.  Identical results
+ *                             XCD that no block runs on; 4 as 2, but the block comes when the others
+ *                             have given up.  Identical results
  * Returns AFSAI_ERR_INVALID_ARG for an unknown option or value.  Not thread safe against
  * concurrent calls of the library.
  */

@@ -53,6 +53,7 @@ struct SmallArgs {
     int blocks, xcc, nbv;  // blocks that take part, their XCD, vector blocks
     int iter0, iters;      // iterations done before this launch, and most of it
     int miss;              // arrivals that the first barrier waits for and nobody makes (0 but in tests)
+    int late;              // the last block comes after the others have given up (tests)
 };
 
 // pointers in the global address space (a flat load would also wait for LDS)
@@ -184,8 +185,12 @@ __global__ __launch_bounds__(kSmallWin * kThreads) __attribute__((amdgpu_waves_p
     int rperm = -1;  // with ordered windows: the row this lane multiplies
     if (ORD && on) rperm = glob(a.t_perm)[(int64_t)sl * kSlice + lane];
     uint32_t phase = 0;
+    if (a.late && rank == a.blocks - 1)
+        for (const long long t0 = wall_clock64(); wall_clock64() - t0 < 3 * kSmallMeet;) __builtin_amdgcn_s_sleep(64);
 
-    // all blocks' stores before it are in the L2 after it; false: a block gave up
+    // all blocks' stores before it are in the L2 after it; false: given up.  A block that gives up takes its
+    // arrival back, if the barrier is still short of one: then it stays short for every block, also for one that
+    // comes late, and either all pass a barrier or none does.
     auto barrier = [&]() __attribute__((always_inline)) -> bool {
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
@@ -204,8 +209,11 @@ __global__ __launch_bounds__(kSmallWin * kThreads) __attribute__((amdgpu_waves_p
                 if (t0 == 0) t0 = now;
                 if (__hip_atomic_load(glob(&a.ctl->dead), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ||
                     now - t0 > longest) {
-                    __hip_atomic_store(glob(&a.ctl->dead), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    dead = 1;
+                    uint32_t seen = __hip_atomic_load(glob(&a.ctl->arrive), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    while (seen < want && !dead)  // (a failed exchange reads seen anew)
+                        dead = __hip_atomic_compare_exchange_strong(glob(&a.ctl->arrive), &seen, seen - 1, __ATOMIC_RELAXED,
+                                                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (dead) __hip_atomic_store(glob(&a.ctl->dead), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     break;
                 }
             }

@@ -298,7 +298,7 @@ int afsai_set_option(int32_t opt, int64_t value) {
         case AFSAI_OPT_SETUP_LANES: ok = value == 0 || (pow2(value) && value >= 8 && value <= 64); break;
         case AFSAI_OPT_SETUP_CLAIM: ok = (value >= 0 && value <= 64); break;
         case AFSAI_OPT_SELL_RUNS: ok = (value == 0 || value == 1); break;
-        case AFSAI_OPT_PCG_ONE_LAUNCH: ok = (value >= 0 && value <= 3); break;
+        case AFSAI_OPT_PCG_ONE_LAUNCH: ok = (value >= 0 && value <= 4); break;
         default: ok = false;
     }
     if (!ok) AFSAI_FAIL(AFSAI_ERR_INVALID_ARG, "afsai_set_option: bad option %d / value %lld", opt, (long long)value);

@@ -2226,7 +2226,7 @@ class PcgRun {
         sa_ = SmallArgs{A_.n, As_.nslices, (int)As_.entries, (int)P_->sg.entries, (int)P_->sgt.entries, As_.sptr, P_->sg.sptr, P_->sgt.sptr, As_.col, P_->sg.col, P_->sgt.col,
                         (const double *)As_.val, P_->sg.val, P_->sgt.val, P_->sgt.perm, P_->sgt.lens, b_, x_, r_, r2_, z_,
                         p_, p2_, q_, t_, partials_, pa_rr_, pa_rz_, sc_, dhs_[0], (SmallCtl *)ctl_, blocks, xcc,
-                        bm_.vec.nblocks, 0, kSmallIters, 0};
+                        bm_.vec.nblocks, 0, kSmallIters, 0, 0};
         if (option(AFSAI_OPT_PCG_ONE_LAUNCH) == 3) sa_.xcc = __builtin_ctz(~mask);  // (bit 16 at the latest)
         small_grid_ = dim3((unsigned)(blocks * nx));
         small_block_ = dim3((unsigned)(ng * kThreads));
@@ -2246,6 +2246,7 @@ class PcgRun {
         hs_[0][0] = PcgScalars{};
         hs_[0][0].pad = SMALL_ABSENT;
         sa_.miss = option(AFSAI_OPT_PCG_ONE_LAUNCH) == (sa_.iter0 == 0 ? 1 : 2);
+        sa_.late = option(AFSAI_OPT_PCG_ONE_LAUNCH) == 4 && sa_.iter0 > 0;
         if (sa_.iter0 == 0)
             hipLaunchKernelGGL(k_set_scalars, dim3(1), dim3(256), 0, s_, sc_, bad_, ctl_, 1, rtol_, maxit_, 0);
         else

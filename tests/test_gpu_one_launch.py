@@ -210,10 +210,11 @@ def test_places_on_the_xcds(af):
         _same(out[k] + (xs[k].cpu().numpy().view(np.int64),), want)
 
 
-@pytest.mark.parametrize("maxit", [None, 1030, 1025])
-def test_blocks_that_do_not_meet_again(af, maxit):
-    """A block missing in the second launch of a solve: the launches of the fused form go on from
-    iteration 1,024, to the end or to a maxit just behind it."""
+@pytest.mark.parametrize("meets,maxit", [(2, None), (2, 1030), (2, 1025), (4, None)])
+def test_blocks_that_do_not_meet_again(af, meets, maxit):
+    """A block missing in the second launch of a solve, or coming when the others have given up (it must not
+    pass the barrier and step its part of x): the launches of the fused form go on from iteration 1,024, to the
+    end or to a maxit just behind it."""
     A = synth.lap7(3000, 1, 1, (1.0, 1e-9, 1e-9))
     dA = af.DeviceCSR.from_host(A)
     P = af.setup(dA, 0, 1, 1e-2)
@@ -222,6 +223,6 @@ def test_blocks_that_do_not_meet_again(af, maxit):
     want = _solve(af, dA, P, b, x0, [(af.OPT_PCG_FORM, 2)], rtol=1e-10, maxit=maxit)
     assert want[1] > 1024
     with _Forms(af) as forms:
-        got = _solve(af, dA, P, b, x0, [(af.OPT_PCG_ONE_LAUNCH, 2)], rtol=1e-10, maxit=maxit)
+        got = _solve(af, dA, P, b, x0, [(af.OPT_PCG_ONE_LAUNCH, meets)], rtol=1e-10, maxit=maxit)
     assert forms() == (1, 1, 1, 0)
     _same(got, want)
