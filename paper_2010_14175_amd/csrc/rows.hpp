@@ -373,7 +373,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(!RSL ? 1 : (
                     lm = fmax(lm, ar[j]);
                 }
                 const T M = wave_max_dpp(lm);
-                if (M > T(0)) {
+                if (M > T(0) && M < T(INFINITY)) {  // (beside an infinite one no gradient is eligible)
                     const T thr = T(0x1.0p-40) * M;
                     for (int round = 0; round < s; ++round) {
                         // the first round's largest eligible value is M itself (M > thr)
@@ -425,7 +425,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(!RSL ? 1 : (
                     if (kk != kEmpty && !(kk & kPBit)) lm = fmax(lm, fabs(hval[j]));
                 }
                 const T M = wave_max_dpp(lm);
-                if (M > T(0)) {
+                if (M > T(0) && M < T(INFINITY)) {
                     const T thr = T(0x1.0p-40) * M;
                     for (int round = 0; round < s; ++round) {
                         T Mp = M;

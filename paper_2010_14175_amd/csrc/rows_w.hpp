@@ -808,7 +808,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(GS == 8 || (
                 int e1, e2;
                 top2<GS, SPL>(hkey, hval, gl, a1, a2, k1, k2, e1, e2);
                 const double M = gred<GS, OpMax>(a1);
-                if (wu<GS>(M > 0.0)) {
+                // (beside an infinite gradient none is eligible: the row stops)
+                if (wu<GS>(M > 0.0 && M < INFINITY)) {
                     const double thr = 0x1.0p-40 * M;
                     bool partial = false;
                     for (int round = 0; round < s; ++round) {

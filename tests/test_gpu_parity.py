@@ -1185,3 +1185,29 @@ def test_pcg_form_by_entries(af, make):
     for it, x in out[1:]:
         assert it == out[0][0]
         np.testing.assert_array_equal(x, out[0][1])
+
+
+@pytest.mark.parametrize("make,kmax,form,option,value", [
+    (lambda: synth.elast27(5, 1.0, 2), 3, 0, 0, 0), (lambda: synth.elast27(5, 1.0, 2), 40, 0, 0, 0),
+    (lambda: synth.elast27(5, 1.0, 2), 3, 0, "OPT_SETUP_LANES", 64), (lambda: synth.elast27(5, 1.0, 2), 3, 0, "OPT_SETUP_LANES", 32),
+    (lambda: synth.lap7(6), 3, 0, 0, 0), (lambda: synth.lap7(6), 12, 0, 0, 0), (lambda: synth.elast27(5, 1.0, 2), 3, 1, 0, 0),
+    (lambda: synth.lap7(6), 3, 1, "OPT_SETUP_SLOTS", 1)])
+def test_setup_infinite_gradient(af, make, kmax, form, option, value):
+    """A symmetric pair of infinite entries: where it makes a gradient infinite no candidate is eligible
+    (each is within 2^-40 of the largest), so the row stops there, and nothing is read for it. G, psi, steps and
+    stop reasons are the oracle's in every form of the setup."""
+    A = make()
+    row = np.repeat(np.arange(A.n), np.diff(A.row_ptr))
+    i = A.n // 2
+    j = int(A.col[(row == i) & (A.col < i)][0])
+    val = A.val.copy()
+    val[((row == i) & (A.col == j)) | ((row == j) & (A.col == i))] = -np.inf
+    B = synth.CSR(A.row_ptr, A.col, val)
+    assert int((oracle.setup_rows(B, kmax, 1, 1e-9).reason == af.STOP_NOCAND).sum()) > 1
+    try:
+        if option:
+            af.set_option(getattr(af, option), value)
+        compare_factor(af, B, kmax, 1, 1e-9, form=form)
+    finally:
+        if option:
+            af.set_option(getattr(af, option), 0)
