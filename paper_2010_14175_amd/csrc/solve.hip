@@ -158,7 +158,9 @@ struct Parts {
 
 // The sums of system k's partials of two launches, each in block order (every thread adds a
 // contiguous run, then the runs are added in thread order); every thread of the block gets
-// them.  b without partials: its sum is 0.
+// them.  b without partials: its sum is 0.  U: partials of each loaded before they are added, two by two (the
+// lanes' runs lie apart, so that a block alone is bound by its loads' round trips and cache lines).
+template <int U = 1>
 __device__ __forceinline__ void parts_sum(const Parts &a, const Parts &b, int k, double *sh /* 2 * kThreads / 64 */,
                                           double &sa, double &sb) {
     if (a.nblocks == 0) {  // added before
@@ -167,15 +169,43 @@ __device__ __forceinline__ void parts_sum(const Parts &a, const Parts &b, int k,
         return;
     }
     double v[2] = {0.0, 0.0};
+    const double *p[2];
+    int len[2];
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         const Parts &pt = q ? b : a;
+        p[q] = pt.p;
+        len[q] = 0;
         if (pt.p) {
             const int b0 = pt.mp.blk_sys ? pt.mp.sys_b0[k] : 0;
             const int np = pt.mp.blk_sys ? pt.mp.sys_nb[k] : pt.nblocks;
             const int per = (np + kThreads - 1) / kThreads;
-            const int lo = threadIdx.x * per, hi = min(np, lo + per);
-            for (int j = lo; j < hi; ++j) v[q] += pt.p[b0 + j];
+            const int lo = threadIdx.x * per;
+            p[q] += b0 + lo;
+            len[q] = min(per, np - lo);
+        }
+        if (U == 1)
+            for (int j = 0; j < len[q]; ++j) v[q] += p[q][j];
+    }
+    if constexpr (U > 1) {
+        for (int j = 0; j < max(len[0], len[1]); j += U) {
+            double t[2][U];
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int u = 0; u < U; u += 2) {
+                    typedef double Two __attribute__((ext_vector_type(2), aligned(8)));
+                    Two w = {0.0, 0.0};
+                    if (j + u + 2 <= len[q]) w = *reinterpret_cast<const Two *>(p[q] + j + u);
+                    else if (j + u < len[q]) w.x = p[q][j + u];
+                    t[q][u] = w.x;
+                    t[q][u + 1] = w.y;
+                }
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (j + u < len[q]) v[q] += t[q][u];
         }
     }
     const int w = threadIdx.x >> 6;
@@ -199,11 +229,11 @@ __device__ __forceinline__ void parts_sum(const Parts &a, const Parts &b, int k,
 // system's sums of one or two launches
 __global__ __launch_bounds__(kThreads) void k_reduce(Parts a, Parts b, double *oa, double *ob, const PcgScalars *scs) {
     const int k = blockIdx.x;
-    if (scs[k].done) return;
+    const int done = scs[k].done;  // (loaded beside the partials)
     __shared__ double sh[2 * kThreads / 64];
     double sa, sb;
-    parts_sum(a, b, k, sh, sa, sb);
-    if (threadIdx.x == 0) {
+    parts_sum<16>(a, b, k, sh, sa, sb);
+    if (threadIdx.x == 0 && !done) {
         oa[k] = sa;
         if (b.p) ob[k] = sb;
     }
@@ -369,8 +399,16 @@ __device__ __forceinline__ void window_walk(int nw, int lb, int nb, int nxcd, in
         off = extra * (per + 1) + ((lb - extra * (per + 1)) / per) * per;
         cnt = per;
     }
-    w0 = (int)((int64_t)nw * off / nb) + (lb - off);
-    w1 = (int)((int64_t)nw * (off + cnt) / nb);
+    if (nw == nb) {
+        w0 = lb;
+        w1 = off + cnt;
+    } else if (nw < (1 << 19) && nb <= (1 << 12)) {  // (a division of 64 bits takes some hundred instructions)
+        w0 = (int)((uint32_t)nw * (uint32_t)off / (uint32_t)nb) + (lb - off);
+        w1 = (int)((uint32_t)nw * (uint32_t)(off + cnt) / (uint32_t)nb);
+    } else {
+        w0 = (int)((int64_t)nw * off / nb) + (lb - off);
+        w1 = (int)((int64_t)nw * (off + cnt) / nb);
+    }
     step = cnt;
 }
 
@@ -795,7 +833,7 @@ __global__ __launch_bounds__(kThreads) void k_init_residual(int n, const double 
     store_partials(partials, 2, mine, jb.gb);
 }
 
-// x += alpha p ; r -= alpha q ; partials of ||r||^2  (pq: the partials of p.q)
+// x += alpha p ; r -= alpha q ; partials of ||r||^2  (M = I; pq: the partials of p.q)
 __global__ __launch_bounds__(kThreads) void k_update_xr(int n, double *__restrict__ x,
                                                          double *__restrict__ r,
                                                          const double *__restrict__ p,
@@ -817,6 +855,41 @@ __global__ __launch_bounds__(kThreads) void k_update_xr(int n, double *__restric
         const double ri = fma(-alpha, q[i], r[i]);
         r[i] = ri;
         pr = fma(ri, ri, pr);
+    }
+    const double bs = block_sum(pr, sh);
+    store_partials(partials, 1, &bs, jb.gb);
+}
+
+// The same with a preconditioner: r.r summed over the windows of a SELL product, block by block and row by row as
+// k_sell_fused sums it, so that the forms, and a system alone and in a batch of another form, stop at the same iteration
+// with the same ||r|| bit for bit.  (With M = I r.r is rho and keeps its order; only one form has it.)
+__global__ __launch_bounds__(kThreads) void k_update_xr_win(int n, double *__restrict__ x, double *__restrict__ r,
+                                                             const double *__restrict__ p, const double *__restrict__ q,
+                                                             double *__restrict__ partials, const PcgScalars *scs,
+                                                             int32_t *bad, Parts pq, Map mp, Systems sy, int nxcd) {
+    static_assert(kWin * kSlice == kThreads, "one row of a window per thread");
+    const Job jb = block_job(mp, nxcd);
+    const double rho = scs[jb.k].rho, v = pq.p[jb.k];
+    if (scs[jb.k].done) return;
+    if (!(v > 0.0) || !isfinite(v)) {
+        if (jb.lb == 0 && threadIdx.x == 0) bad[jb.k] = 1;
+        return;
+    }
+    const double alpha = rho / v;
+    __shared__ double sh[kThreads / 64];
+    int a0, a1, w0, w1, step;
+    sys_rows(sy, n, jb.k, a0, a1);
+    const int64_t len = a1 - a0;
+    window_walk((int)((len + kThreads - 1) / kThreads), jb.lb, jb.nb, nxcd, w0, w1, step);
+    double pr = 0.0;
+    for (int w = w0; w < w1; w += step) {
+        const int64_t i = (int64_t)w * kThreads + threadIdx.x;
+        if (i < len) {
+            x[a0 + i] = fma(alpha, p[a0 + i], x[a0 + i]);
+            const double ri = fma(-alpha, q[a0 + i], r[a0 + i]);
+            r[a0 + i] = ri;
+            pr = fma(ri, ri, pr);
+        }
     }
     const double bs = block_sum(pr, sh);
     store_partials(partials, 1, &bs, jb.gb);
@@ -2297,8 +2370,8 @@ class PcgRun {
     Parts sell_parts(const double *p) const { return Parts{p, bm_.sell.mp, bm_.sell.nblocks}; }
     Parts vec_parts(const double *p) const { return Parts{p, bm_.vec.mp, bm_.vec.nblocks}; }
     Parts red_parts(int j) const { return Parts{red_ + (size_t)j * nsys_, Map(), 0}; }
-    // partials of r.r (the fused form's product sums it, else the vector update) and of r.z
-    Parts rr_parts() const { return fused_ ? sell_parts(pa_rr_) : vec_parts(pa_rr_); }
+    // partials of r.r (over the windows but with M = I, see k_update_xr_win) and of r.z
+    Parts rr_parts() const { return P_ ? sell_parts(pa_rr_) : vec_parts(pa_rr_); }
     Parts rz_parts() const { return P_ ? sell_parts(pa_rz_) : Parts(); }
 
     // products inside the iteration stop with their system (gate: its scalars); the first and the
@@ -2377,15 +2450,19 @@ class PcgRun {
         hipLaunchKernelGGL(k_reduce, gs, dim3(kThreads), 0, s_, pq, Parts(), red_, (double *)nullptr, s_in);
         {
             ProfScope ps("update_xr", s_);
-            hipLaunchKernelGGL(k_update_xr, gv, dim3(kThreads), 0, s_, n, x_, r_, p_, q_, pa_rr_, s_in, bad_,
-                               red_parts(0), bm_.vec.mp, bm_.sy, di_.num_xcds);
+            if (P_)
+                hipLaunchKernelGGL(k_update_xr_win, dim3(bm_.sell.nblocks), dim3(kThreads), 0, s_, n, x_, r_, p_, q_, pa_rr_,
+                                   s_in, bad_, red_parts(0), bm_.sell.mp, bm_.sy, di_.num_xcds);
+            else
+                hipLaunchKernelGGL(k_update_xr, gv, dim3(kThreads), 0, s_, n, x_, r_, p_, q_, pa_rr_, s_in, bad_,
+                                   red_parts(0), bm_.vec.mp, bm_.sy, di_.num_xcds);
         }
         marks_.push_back(prof_mark());
         // the iteration that converges needs no z: with a large G (the two products cost more than a
         // launch per iteration) r.r is summed before them and they return; else with r.z
         const bool gate = P_ && P_->sg.entries >= kGateEntries;
         if (gate)
-            hipLaunchKernelGGL(k_reduce, gs, dim3(kThreads), 0, s_, vec_parts(pa_rr_), Parts(), red_ + nsys_,
+            hipLaunchKernelGGL(k_reduce, gs, dim3(kThreads), 0, s_, rr_parts(), Parts(), red_ + nsys_,
                                (double *)nullptr, s_in);
         if (P_) {
             const double *rr = gate ? red_ + nsys_ : nullptr;
@@ -2396,7 +2473,7 @@ class PcgRun {
             hipLaunchKernelGGL(k_reduce, gs, dim3(kThreads), 0, s_, rz_parts(), Parts(), red_ + 2 * (size_t)nsys_,
                                (double *)nullptr, s_in);
         else
-            hipLaunchKernelGGL(k_reduce, gs, dim3(kThreads), 0, s_, vec_parts(pa_rr_), rz_parts(), red_ + nsys_,
+            hipLaunchKernelGGL(k_reduce, gs, dim3(kThreads), 0, s_, rr_parts(), rz_parts(), red_ + nsys_,
                                red_ + 2 * (size_t)nsys_, s_in);
         {
             ProfScope ps("update_p", s_);

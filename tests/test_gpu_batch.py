@@ -244,3 +244,31 @@ def test_full_batch512_against_oracle(af):
         ro = oracle.pcg(pb.A, Gk, pb.b, 1e-8)
         assert infos[k].converged and infos[k].iters == ro.iters, (k, infos[k].iters, ro.iters)
         assert np.linalg.norm(xh[o0:o1] - ro.x) <= 1e-10 * np.linalg.norm(ro.x), k
+
+
+@pytest.mark.parametrize("make,kmax,alone", [(lambda: synth.elast27(32, 1.0, 1), 10, "separate"),
+                                             (lambda: synth.lap7(60, 60, 61), 5, "fused")])
+def test_batched_form_other_than_alone(af, make, kmax, alone):
+    """Systems that take one form of the PCG alone (by their entries) and the other in a batch (by their rows):
+    iterations, both residuals and x are the same bit for bit."""
+    A1 = make()
+    m = A1.to_scipy()
+    import scipy.sparse as sp
+
+    A = synth.CSR.from_scipy(sp.block_diag([m, m], format="csr"))
+    b = synth.uniform(5, 1, A.n, -1.0, 1.0)
+    off = [0, A1.n, A.n]
+    dA = af.DeviceCSR.from_host(A)
+    P = af.setup_batched(dA, off, kmax, 1, 1e-2)
+    before = af.pcg_form_counts()
+    x, infos = af.pcg_solve_batched(dA, P, off, _vec(b), rtol=1e-8)
+    mid = af.pcg_form_counts()
+    d1 = af.DeviceCSR.from_host(A1)
+    P1 = af.setup(d1, kmax, 1, 1e-2)
+    for k in range(2):
+        x1, i1 = af.pcg_solve(d1, P1, _vec(b[off[k]:off[k + 1]]), rtol=1e-8)
+        assert (infos[k].iters, infos[k].relres, infos[k].true_relres) == (i1.iters, i1.relres, i1.true_relres)
+        np.testing.assert_array_equal(x[off[k]:off[k + 1]].cpu().numpy().view(np.int64), x1.cpu().numpy().view(np.int64))
+    after = af.pcg_form_counts()
+    batched = "fused" if alone == "separate" else "separate"
+    assert (mid[batched] - before[batched], after[alone] - mid[alone]) == (1, 2)

@@ -1211,3 +1211,24 @@ def test_setup_infinite_gradient(af, make, kmax, form, option, value):
     finally:
         if option:
             af.set_option(getattr(af, option), 0)
+
+
+@pytest.mark.parametrize("make,kmax", [(lambda: synth.lap7(5, 4, 3), 5), (lambda: synth.lap7(20, 20, 41), 5),
+                                       (lambda: synth.lap7(82, 83, 82), 5), (lambda: synth.elast27(30, 1.0, 1), 5)])
+def test_pcg_forms_stop_alike(af, make, kmax):
+    """Every form sums r.r in the same order: iterations and both residuals are equal bit for bit (one window
+    of rows, one to a block, several, and more than blocks), also from a solve that maxit ends."""
+    A = make()
+    dA = _dev(af, A)
+    P = af.setup(dA, kmax, 1, 1e-2)
+    b = _vec(synth.uniform(5, 1, A.n, -1.0, 1.0))
+    out = []
+    try:
+        for form in (0, 1, 2):
+            af.set_option(af.OPT_PCG_FORM, form)
+            for maxit in (None, 3):
+                x, i = af.pcg_solve(dA, P, b, rtol=1e-8, maxit=maxit)
+                out.append((maxit, i.status, i.iters, i.relres, i.true_relres, x.cpu().numpy().tobytes()))
+    finally:
+        af.set_option(af.OPT_PCG_FORM, 0)
+    assert out[0:2] == out[2:4] == out[4:6]
