@@ -279,6 +279,7 @@ __device__ __forceinline__ void sort_load(const int32_t *ci, const VT *val, cons
     }
 }
 
+constexpr int kRankRow = 256;
 // one row of G^T by the lanes of a wavefront: up to 256 entries are ranked in registers (each lane
 // counts the smaller keys, one, two or four keys per lane); longer rows fall back to an insertion
 // sort by one lane
@@ -320,7 +321,7 @@ __device__ __forceinline__ void sort_row(int lane, int a, int len, int32_t *__re
             ci[a + r1] = k1;
             val[a + r1] = v1;
         }
-    } else if (len <= 256) {
+    } else if (len <= kRankRow) {
         // four keys per lane (rows of G^T past 128 entries: columns chosen by many rows)
         int k[4];
         VT v[4];
@@ -369,13 +370,16 @@ __device__ __forceinline__ void sort_row(int lane, int a, int len, int32_t *__re
 // Sorts every row of G^T by column (= row of G), reading the rows from the fill's pairs (pr)
 // or in place (pr null).  Four rows per wavefront, side by side while none is longer than 16 entries
 // (a wavefront for each left most of its lanes idle: 512 systems with rows of six entries 1.67 ->
-// 0.59 ms), else in turn.
+// 0.59 ms), else in turn.  The rows of the serial sort follow, one at a time to a wavefront and neighbours on
+// different ones (columns that many rows chose lie together; in turn, two nodes of 3,000 entries a row took
+// 1.58 instead of 0.60 s).
 template <typename VT>
 __global__ __launch_bounds__(256) void k_sort_rows(int n, const int32_t *__restrict__ rp, int32_t *__restrict__ ci,
                                                    VT *__restrict__ val, const TPair<VT> *__restrict__ pr) {
     const int lane = threadIdx.x & 63, sub = lane >> 4, sl = lane & 15;
+    const int w = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
     const int nq = (n + 3) / 4;
-    for (int q = (blockIdx.x * blockDim.x + threadIdx.x) >> 6; q < nq; q += (gridDim.x * blockDim.x) >> 6) {
+    for (int q = w; q < nq; q += nw) {
         const int i = 4 * q + sub;
         const int a = i < n ? rp[i] : 0, len = i < n ? rp[i + 1] - a : 0;
         if (!__any(len > 16)) {
@@ -392,8 +396,16 @@ __global__ __launch_bounds__(256) void k_sort_rows(int n, const int32_t *__restr
         } else {
             for (int u = 0; u < 4; ++u) {
                 const int au = __shfl(a, 16 * u, 64), lu = __shfl(len, 16 * u, 64);
-                if (lu > 0) sort_row<VT>(lane, au, lu, ci, val, pr);
+                if (lu > 0 && lu <= kRankRow) sort_row<VT>(lane, au, lu, ci, val, pr);
             }
+        }
+    }
+    for (int64_t i0 = w; i0 < n; i0 += (int64_t)64 * nw) {
+        const int64_t i = i0 + (int64_t)lane * nw;
+        const int a = i < n ? rp[i] : 0, len = i < n ? rp[i + 1] - a : 0;
+        for (uint64_t m = __ballot(len > kRankRow); m; m &= m - 1) {
+            const int u = __builtin_ctzll(m);
+            sort_row<VT>(lane, __shfl(a, u, 64), __shfl(len, u, 64), ci, val, pr);
         }
     }
 }

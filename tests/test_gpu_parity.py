@@ -1232,3 +1232,29 @@ def test_pcg_forms_stop_alike(af, make, kmax):
     finally:
         af.set_option(af.OPT_PCG_FORM, 0)
     assert out[0:2] == out[2:4] == out[4:6]
+
+
+@pytest.mark.parametrize("n,hubs", [(1200, 1), (1200, 4), (5000, 9), (260, 3)])
+def test_long_transpose_rows_together(af, n, hubs):
+    """Neighbouring rows of G^T around the longest that is ranked in registers (256 entries) and far past it, among rows
+    of one to sixteen: G^T G r equals the product with G within the rounding of its sums, and does not depend on the
+    order in which the transpose was filled."""
+    import scipy.sparse as sp
+
+    rows, cols = [np.arange(n)], [np.arange(n)]
+    for h in range(hubs):
+        count = (256, 257, n - 100, 300, 255, n - 50, 2000, 1025, 700)[h]
+        rows.append(n - 1 - np.arange(min(count, n - 101)))
+        cols.append(np.full(rows[-1].size, 60 + h))
+    G = sp.csr_matrix((np.ones(sum(r.size for r in rows)), (np.concatenate(rows), np.concatenate(cols))), shape=(n, n))
+    G.sort_indices()
+    G.data = synth.uniform(3, 9, G.nnz, -1.0, 1.0)
+    lens = np.diff(G.tocsc().indptr)
+    r = synth.uniform(7, 9, n, -1.0, 1.0)
+    dG = af.DeviceCSR.from_host(synth.CSR.from_scipy(G))
+    z = [af.import_factor(dG).apply(_vec(r)).cpu().numpy() for _ in range(3)]
+    Ga = abs(G)
+    bound = Ga.T @ (Ga @ abs(r)) * (np.diff(G.indptr).max() + lens.max() + 4) * 2.0 ** -53
+    assert (abs(z[0] - G.T @ (G @ r)) <= 2 * bound).all()
+    for y in z[1:]:
+        np.testing.assert_array_equal(y.view(np.int64), z[0].view(np.int64))
