@@ -17,7 +17,7 @@ RowsKernel rows_kernel_b(int n, int mmax, int s, int maxlen, int *gs_out, size_t
     // for 11 positions, 90 for 21, 148 for 46), no more: fewer slots are fewer bytes of LDS (64^3:
     // 12.3 ms with 128 slots, 10.4 ms with 92, 16 wavefronts per CU) and fewer to scan.  150^3: 618 ms
     // with 176 slots, 654 with 192 (10 wavefronts per CU), 625 with 160 (longer probes).  Rows that
-    // touch more are redone by the general form.  New rows per block: as the general form's (2, 4),
+    // touch more are redone (rows_kernel_b_large).  New rows per block: as the general form's (2, 4),
     // 3 for three or fewer rows a step (the same blocks).
     // Small systems take the next larger table: redoing even a few rows costs 0.15 ms (a launch and its
     // host round trip), more than 128 slots cost at 24,000 rows (21 positions: kernel 0.39 -> 0.46 ms,
@@ -32,6 +32,19 @@ RowsKernel rows_kernel_b(int n, int mmax, int s, int maxlen, int *gs_out, size_t
     if (mmax <= 48)
         return s <= 3 ? b_inst<64, 48, 176, 3, 3>(mmax, s, gs_out, lds_out) : b_inst<64, 48, 176, 4, 3>(mmax, s, gs_out, lds_out);
     return s <= 3 ? b_inst<64, 64, 256, 3, 2>(mmax, s, gs_out, lds_out) : b_inst<64, 64, 256, 4, 2>(mmax, s, gs_out, lds_out);
+}
+
+// The instance for the rows that overflowed a table of fewer than 176 slots (nullptr: none).  176 runs hold whatever
+// the general form's first table (512 entries) does; patterns on other node orders and on irregular meshes touch more
+// runs than the first table was made for, and the general form's second table is sized for the worst case, one row to
+// a wavefront.  64^3 randomly numbered, 21 positions, 12% of the rows redone: 21.2 -> 15.9 ms (the general form
+// alone 26.1; with 256 slots 16.5); a graph of 13 runs a row, 31 positions, 91% of 120,000 rows redone: 18.8 -> 8.9 ms
+// (14.8; with 176 slots 10.1).  Where most rows touch more than that too, the pass is lost (27 runs a row, 21 positions:
+// 10.9 -> 13.1 ms, the general form alone 16.9).
+RowsKernel rows_kernel_b_large(int mmax, int s, int *gs_out, size_t *lds_out) {
+    if (mmax <= 24) return b_inst<32, 24, 176, 2, 2>(mmax, s, gs_out, lds_out);
+    if (mmax > 32) return nullptr;
+    return s <= 3 ? b_inst<64, 48, 256, 3, 2>(mmax, s, gs_out, lds_out) : b_inst<64, 48, 256, 4, 2>(mmax, s, gs_out, lds_out);
 }
 
 }  // namespace afsai

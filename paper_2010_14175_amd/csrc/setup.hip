@@ -455,6 +455,7 @@ RowsKernel rows_kernel(int mmax_t, int cap, bool rsl, bool f32);
 RowsKernel rows_kernel_w(int mmax, int maxlen, int cap, int lanes, bool g32, int *gs_out, size_t *lds_out);
 RowsKernel rows_kernel_w_large(int mmax, int cap, bool g32, size_t *lds_out);
 RowsKernel rows_kernel_b(int n, int mmax, int s, int maxlen, int *gs_out, size_t *lds_out);
+RowsKernel rows_kernel_b_large(int mmax, int s, int *gs_out, size_t *lds_out);
 
 // Launch of a per-row kernel over `nlist` rows.  Inverse-factor form: wdyn > 0 is its dynamic
 // LDS per block and rpw its rows per wavefront; the Cholesky form sizes its LDS from the
@@ -718,6 +719,7 @@ static int setup_core(const afsai_csr *A, const afsai_params *p, int nsys, const
     // table from 64 slots; rows that overflow it are redone by the Cholesky form below
     const int64_t form = option(AFSAI_OPT_SETUP_FORM);
     RowsKernel k1 = nullptr;
+    bool run_form = false;
     size_t wdyn = 0;
     int wrpw = 1;
     if (form != 1 && !sf32 && rsl) {
@@ -730,6 +732,7 @@ static int setup_core(const afsai_csr *A, const afsai_params *p, int nsys, const
         if (wcap < 128 && (lanes >= 32 || mmax > 16 || maxlen > 64)) wcap = 128;
         int gs = 64;
         if (runs && !so.noruns) k1 = rows_kernel_b(n, mmax, p->s, maxlen, &gs, &wdyn);
+        run_form = k1 != nullptr;
         if (!k1) k1 = rows_kernel_w(mmax, maxlen, wcap, lanes, (p->flags & AFSAI_GRAD_F32) != 0, &gs, &wdyn);
         if (k1) {
             wrpw = 64 / gs;
@@ -775,26 +778,37 @@ static int setup_core(const afsai_csr *A, const afsai_params *p, int nsys, const
         return fetch_words(&sm, sum_out, sizeof sm, s);
     };
     if ((rc = summarise())) return rc;
-    const int32_t novf = (int32_t)sm.novf;
-    int32_t retried = 0;
-    if (novf > 0 && cap2 > cap1) {
-        retried = novf;
+    const int32_t retried = sm.novf > 0 && (run_form || cap2 > cap1) ? (int32_t)sm.novf : 0;
+    // the rows that overflowed, with a larger table
+    auto redo = [&](const char *name, RowsKernel kern, size_t dyn, int rpw, int cap) -> int {
+        const int32_t novf = (int32_t)sm.novf;
         DevBuf list2;
-        if ((rc = dalloc(list2, sizeof(int32_t) * ((size_t)novf + 1), s))) return rc;
+        int rc2;
+        if ((rc2 = dalloc(list2, sizeof(int32_t) * ((size_t)novf + 1), s))) return rc2;
         hipLaunchKernelGGL(k_copy_i32, dim3(grid1d(novf, di)), dim3(256), 0, s, (int64_t)novf, ovf.as<int32_t>(),
                            list2.as<int32_t>());
         int32_t *cnt2 = list2.as<int32_t>() + novf;
         hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, (int64_t)1, cnt2, 0);
-        // the same form as the first launch, with the larger table
-        size_t wdyn2 = 0;
-        RowsKernel k2 = wdyn ? rows_kernel_w_large(mmax, cap2, (p->flags & AFSAI_GRAD_F32) != 0, &wdyn2) : rows_kernel(mmax_t, cap2, rsl, sf32);
-        if (!k2) AFSAI_FAIL(AFSAI_ERR_TOO_LARGE, "afsai_setup: no kernel for table %d", cap2);
-        if ((rc = launch_rows("afsai_rows_retry", k2, wdyn2, 1, mmax_t, mmax, row_work, cap2, rsl, tb, gmax, A, av32, diagb.as<double>(), dlob.as<int32_t>(), p, list2.as<int32_t>(), novf,
-                              ctr.as<int32_t>(), ldell, ell_col.as<int32_t>(), ell_val.as<double>(), mcnt.as<int32_t>(),
-                              psi.as<double>(), steps.as<int32_t>(), reason.as<int32_t>(), st.as<int8_t>(), cnt2,
-                              ovf.as<int32_t>(), di, s)))
-            return rc;
-        if ((rc = summarise())) return rc;
+        if ((rc2 = launch_rows(name, kern, dyn, rpw, mmax_t, mmax, row_work, cap, rsl, tb, gmax, A, av32, diagb.as<double>(), dlob.as<int32_t>(), p, list2.as<int32_t>(), novf,
+                               ctr.as<int32_t>(), ldell, ell_col.as<int32_t>(), ell_val.as<double>(), mcnt.as<int32_t>(),
+                               psi.as<double>(), steps.as<int32_t>(), reason.as<int32_t>(), st.as<int8_t>(), cnt2,
+                               ovf.as<int32_t>(), di, s)))
+            return rc2;
+        return summarise();
+    };
+    // of the run form: first with the run form's larger table
+    if (sm.novf > 0 && run_form) {
+        int gs = 64;
+        size_t dyn = 0;
+        if (RowsKernel k = rows_kernel_b_large(mmax, p->s, &gs, &dyn))
+            if ((rc = redo("afsai_rows_retry_runs", k, dyn, 64 / gs, cap1))) return rc;
+    }
+    // the same form as the first launch, with a table for the worst case
+    if (sm.novf > 0 && cap2 > cap1) {
+        size_t dyn = 0;
+        RowsKernel k = wdyn ? rows_kernel_w_large(mmax, cap2, (p->flags & AFSAI_GRAD_F32) != 0, &dyn) : rows_kernel(mmax_t, cap2, rsl, sf32);
+        if (!k) AFSAI_FAIL(AFSAI_ERR_TOO_LARGE, "afsai_setup: no kernel for table %d", cap2);
+        if ((rc = redo("afsai_rows_retry", k, dyn, 1, cap2))) return rc;
     }
     if (sm.nbad) AFSAI_FAIL(AFSAI_ERR_BAD_MATRIX, "afsai_setup: %lld rows without a diagonal entry", (long long)sm.nbad);
     if (sm.nnotspd)

@@ -1258,3 +1258,38 @@ def test_long_transpose_rows_together(af, n, hubs):
     assert (abs(z[0] - G.T @ (G @ r)) <= 2 * bound).all()
     for y in z[1:]:
         np.testing.assert_array_equal(y.view(np.int64), z[0].view(np.int64))
+
+
+@pytest.mark.parametrize("kmax,s", [(5, 2), (10, 2), (15, 2), (7, 4)])
+def test_setup_runs_other_order(af, kmax, s):
+    """The 27-point operator with randomly numbered nodes, 73,167 rows: rows of patterns of up to 32 positions that
+    overflow the run form's table are redone with its larger one, none by the general form; G, psi, steps and stop
+    reasons equal the general form's (64 lanes a row asked for) bit for bit."""
+    import scipy.sparse as sp
+
+    m = synth.elast27(29, 1.0, 2).to_scipy()
+    node = np.argsort(synth.uniform(3, 5, m.shape[0] // 3))
+    p = (3 * node[:, None] + np.arange(3)).reshape(-1)
+    A = synth.CSR.from_scipy(sp.csr_matrix(m[p][:, p]))
+    dA = _dev(af, A)
+
+    def run():
+        P = af.setup(dA, kmax, s, 1e-3)
+        return P.info().rows_retried, _gpu_factor(af, P) + tuple(t.cpu().numpy() for t in P.export_rows())
+
+    try:
+        af.profile_enable(True)
+        af.profile_read(reset=True)
+        redone, auto = run()
+        names = af.profile_read(reset=True)
+    finally:
+        af.profile_enable(False)
+    assert redone > 0 and "afsai_rows_retry_runs" in names and "afsai_rows_retry" not in names
+    try:
+        af.set_option(af.OPT_SETUP_LANES, 64)
+        _, general = run()
+    finally:
+        af.set_option(af.OPT_SETUP_LANES, 0)
+    for a, b in zip(auto, general):
+        np.testing.assert_array_equal(a.view(np.int64) if a.dtype == np.float64 else a,
+                                      b.view(np.int64) if b.dtype == np.float64 else b)
