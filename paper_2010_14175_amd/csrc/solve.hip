@@ -1888,17 +1888,22 @@ __global__ __launch_bounds__(kThreads) void k_multi_resid(int n, const double *_
     multi_store<K>(part, sh, partials);
 }
 
-// Whether the block form is the faster one: with one or two columns and few nodes its wavefronts, a third
-// as many, only wait longer (K = 1: 41,472 rows 25.2, with blocks 29.4 us; 65,856 rows 32.1, 30.9;
-// K = 4: 24,000 rows 33.7, 32.1)
-static bool blocks_pay(int K, int n) { return K >= 4 || n >= 50000; }
+// Whether the block form is the faster one.  Up to four columns its wavefronts, a third as many, only wait longer
+// while the form with a row to a lane has all its windows on the CUs at once: `windows` of them to each (1: 65,536 rows
+// here).  Calls of the prepared product, microseconds with blocks and without: K = 1, 52,728 rows 31.8, 28.3; 98,304 rows
+// 32.4, 33.2; K = 2 32.6, 28.3; 33.4, 33.6; K = 4 35.0, 34.6; 36.0, 38.6; K = 8, 1,536 rows 30.4, 35.7.
+// pcg_solve_multi, which also converts the matrix, milliseconds (2 windows): K = 1, 98,304 rows 3.96, 3.82; 192,000 rows 6.12,
+// 6.60; K = 4 5.44, 5.42; 9.10, 9.95.
+static bool blocks_pay(int K, int n, int windows, const DeviceInfo &di) {
+    return K > 4 || n / (kSlice * kWin) >= windows * di.num_cus;
+}
 
 // nt: non-temporal loads of the matrix
 template <int K, bool DOT, bool NT>
 static void spmm_launch_t(const Sell &S, const double *x, double *y, const double *w, double *partials, int nb,
                           const DeviceInfo &di, hipStream_t s, const MultiScal *sc) {
     const dim3 bt(kThreads);
-    if (S.bptr && (!S.val || blocks_pay(K, S.n))) {
+    if (S.bptr && (!S.val || blocks_pay(K, S.n, 1, di))) {
         constexpr int L = K >= 8 ? 2 : 1;
         const int nsl = (S.n / 3 + kSlice - 1) / kSlice;
         hipLaunchKernelGGL((k_node_spmm<K, L, NT>), dim3(blocks_for_slices(nsl * L, di)), bt, 0, s, S.n, nsl, S.bptr,
@@ -2613,7 +2618,7 @@ static int pcg_multi(const afsai_csr *A, afsai_precond P, const double *B, doubl
         Sell *S;
         ~Free() { sell_free(S); }
     } free_sa{&SA};
-    if (blocks_pay(K, n) && option(AFSAI_OPT_SELL_RUNS) != 1 && option(AFSAI_OPT_SELL_WIDTH) == 0 && n % 3 == 0) {
+    if (blocks_pay(K, n, 2, di) && option(AFSAI_OPT_SELL_RUNS) != 1 && option(AFSAI_OPT_SELL_WIDTH) == 0 && n % 3 == 0) {
         // 3 x 3 blocks, unless the rows would be ordered by length (the dots of that layout are
         // summed in another order)
         ProfScope ps("sell_A_blocks", s);
@@ -2764,7 +2769,7 @@ static int spmm_sell(const Sell &S, int32_t k, const double *X, double *Y, const
     {
         ProfScope ps("spmm_A", s);
         const int nb = blocks_for_slices(S.nslices, di);
-        const bool nt = (S.bptr && blocks_pay(k, S.n) ? S.bentries * 9 : stream_bytes(S)) > kCachedBytes;
+        const bool nt = (S.bptr && blocks_pay(k, S.n, 1, di) ? S.bentries * 9 : stream_bytes(S)) > kCachedBytes;
         switch (k) {
             case 1: spmm_launch<1, false>(S, nt, X, Y, nullptr, nullptr, nb, di, s); break;
             case 2: spmm_launch<2, false>(S, nt, X, Y, nullptr, nullptr, nb, di, s); break;

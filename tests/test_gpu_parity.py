@@ -1293,3 +1293,33 @@ def test_setup_runs_other_order(af, kmax, s):
     for a, b in zip(auto, general):
         np.testing.assert_array_equal(a.view(np.int64) if a.dtype == np.float64 else a,
                                       b.view(np.int64) if b.dtype == np.float64 else b)
+
+
+@pytest.mark.parametrize("nodes", [21845, 21846, 43690, 43691])
+def test_block_products_line(af, nodes):
+    """Row counts around one and two windows to a CU (65,536 and 131,072 rows), where products and solves
+    of up to four columns change between single entries and 3 x 3 blocks: the same bits on both sides."""
+    import scipy.sparse as sp
+    import torch
+
+    m = sp.kron(sp.diags([1.0] * 5, range(-2, 3), shape=(nodes, nodes)), np.ones((3, 3)), format="csr")
+    u = sp.triu(m, 1, format="csr")
+    u.data = synth.uniform(5, 77, u.nnz)
+    m = (u + u.T).tocsr()
+    A = synth.CSR.from_scipy(m + sp.diags(1.0 + np.asarray(abs(m).sum(axis=1)).ravel()))
+    dA = _dev(af, A)
+    M = af.PreparedMatrix(dA)
+    P = af.setup(dA, 3, 1, 1e-2)
+    X = synth.uniform(19, 5, A.n * 8, -1.0, 1.0).reshape(A.n, 8)
+    for k in (1, 4, 8):
+        Xk = torch.from_numpy(np.ascontiguousarray(X[:, :k])).cuda()
+        np.testing.assert_array_equal(M.spmm(Xk).cpu().numpy(), af.spmm(dA, Xk).cpu().numpy())
+        Y, iy = af.pcg_solve_multi(dA, P, Xk, rtol=1e-3)
+        try:
+            af.set_option(af.OPT_SELL_RUNS, 1)
+            Z, iz = af.pcg_solve_multi(dA, P, Xk, rtol=1e-3)
+        finally:
+            af.set_option(af.OPT_SELL_RUNS, 0)
+        assert [(i.iters, i.status, i.relres) for i in iy] == [(i.iters, i.status, i.relres) for i in iz]
+        np.testing.assert_array_equal(Y.cpu().numpy(), Z.cpu().numpy())
+    M.close()
