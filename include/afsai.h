@@ -302,8 +302,8 @@ typedef struct afsai_matrix_s *afsai_matrix;
  *   A's arrays are read during the call only; the handle owns a device copy (about
  *   12 bytes per entry plus padding, 13.3 when A's rows are made of runs of three
  *   consecutive columns and run indices are kept beside the columns; 8.5 bytes more when A
- *   is made of 3 x 3 blocks that three consecutive rows share, for the block products, if that
- *   memory is there) and A's values may change afterwards without affecting it
+ *   is made of 3 x 3 blocks that three consecutive rows share, for the block products, unless
+ *   that is more than an eighth of the free device memory) and A's values may change afterwards without affecting it
  *   (prepare again to take them).  *out = NULL on failure.  Synchronous on stream.
  *   Errors: AFSAI_ERR_INVALID_ARG, AFSAI_ERR_NO_MEMORY, AFSAI_ERR_TOO_LARGE, AFSAI_ERR_HIP.
  */

@@ -905,13 +905,16 @@ __global__ __launch_bounds__(256) void k_node_fill(int nodes, int nslices, bool 
     }
 }
 
-int sell_node_blocks(int n, int64_t nnz, const int32_t *rp, const int32_t *ci, const double *val, Sell *S,
+int sell_node_blocks(int n, int64_t nnz, const int32_t *rp, const int32_t *ci, const double *val, bool spare, Sell *S,
                      const DeviceInfo &di, hipStream_t s) {
     if (n % 3 != 0 || nnz % 9 != 0) return AFSAI_OK;
     const int nodes = n / 3, nsl = (nodes + kSlice - 1) / kSlice;
     DevBuf width;  // of each slice, then the mark of a matrix that does not qualify
     int rc;
-    if ((rc = dalloc(width, sizeof(int32_t) * ((size_t)nsl + 1), s))) return rc;
+    if (dalloc(width, sizeof(int32_t) * ((size_t)nsl + 1), s)) {
+        clear_error();
+        return AFSAI_OK;
+    }
     std::vector<int32_t> zero((size_t)nsl + 1, 0);
     AFSAI_HIP_TRY(hipMemcpyAsync(width.p, zero.data(), sizeof(int32_t) * zero.size(), hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(k_node_check, dim3(grid1d((int64_t)nodes * 32, di)), dim3(256), 0, s, nodes, rp, ci,
@@ -929,6 +932,13 @@ int sell_node_blocks(int n, int64_t nnz, const int32_t *rp, const int32_t *ci, c
     }
     int32_t *bcol = nullptr;
     double *bval = nullptr;
+    size_t free_b = 0, total_b = 0;
+    if (spare && (hipMemGetInfo(&free_b, &total_b) != hipSuccess ||
+                  (size_t)blocks * kSlice * (9 * sizeof(double) + sizeof(int32_t)) > free_b / 8)) {
+        (void)hipGetLastError();
+        pool_free(bptr);
+        return AFSAI_OK;
+    }
     if (blocks > 0 && blocks < ((int64_t)1 << 31)) {
         bcol = (int32_t *)pool_alloc(sizeof(int32_t) * (size_t)blocks * kSlice);
         bval = bcol ? (double *)pool_alloc(sizeof(double) * 9 * (size_t)blocks * kSlice) : nullptr;

@@ -91,9 +91,10 @@ int sell_group_runs(Sell *S, const DeviceInfo &di, hipStream_t s, bool keep_col 
 int sell_ordered(int n, int64_t nnz, const int32_t *rp, bool *ordered, const DeviceInfo &di, hipStream_t s);
 // Adds the 3 x 3 block form of a CSR matrix (device arrays, FP64) to S when the matrix is made of
 // such blocks: aligned runs of three columns, the same in the three rows of a node.  Leaves S
-// without it when the matrix does not qualify or the memory for it is not there.  Sets S->n.
-// Synchronous on s.
-int sell_node_blocks(int n, int64_t nnz, const int32_t *rp, const int32_t *ci, const double *val, Sell *S,
+// without it when the matrix does not qualify or the memory for it is not there; with `spare`, for blocks that are
+// kept beside another layout, also when they would take more than an eighth of the free device memory (a caller
+// who only solves never reads them).  Sets S->n.  Synchronous on s.
+int sell_node_blocks(int n, int64_t nnz, const int32_t *rp, const int32_t *ci, const double *val, bool spare, Sell *S,
                      const DeviceInfo &di, hipStream_t s);
 
 }  // namespace afsai

@@ -2624,7 +2624,7 @@ static int pcg_multi(const afsai_csr *A, afsai_precond P, const double *B, doubl
         ProfScope ps("sell_A_blocks", s);
         bool ordered = true;
         if ((rc = sell_ordered(n, A->nnz, A->row_ptr, &ordered, di, s))) return rc;
-        if (!ordered && (rc = sell_node_blocks(n, A->nnz, A->row_ptr, A->col_idx, A->val, &SA, di, s))) return rc;
+        if (!ordered && (rc = sell_node_blocks(n, A->nnz, A->row_ptr, A->col_idx, A->val, false, &SA, di, s))) return rc;
     }
     if (!SA.bptr) {
         {
@@ -2835,7 +2835,7 @@ int afsai_matrix_prepare(const afsai_csr *A, void *stream, afsai_matrix *out) {
         if (rc == AFSAI_OK && option(AFSAI_OPT_SELL_RUNS) != 1) rc = sell_group_runs(&M->S, di, s, true);
         // and 3 x 3 blocks for the block products
         if (rc == AFSAI_OK && option(AFSAI_OPT_SELL_RUNS) != 1)
-            rc = sell_node_blocks(A->n, A->nnz, A->row_ptr, A->col_idx, A->val, &M->S, di, s);
+            rc = sell_node_blocks(A->n, A->nnz, A->row_ptr, A->col_idx, A->val, true, &M->S, di, s);
     }
     if (rc == AFSAI_OK && hipStreamSynchronize(s) != hipSuccess) rc = set_error_code(AFSAI_ERR_HIP, "afsai_matrix_prepare: synchronisation failed");
     if (rc != AFSAI_OK) {

@@ -1323,3 +1323,37 @@ def test_block_products_line(af, nodes):
         assert [(i.iters, i.status, i.relres) for i in iy] == [(i.iters, i.status, i.relres) for i in iz]
         np.testing.assert_array_equal(Y.cpu().numpy(), Z.cpu().numpy())
     M.close()
+
+
+def test_prepared_blocks_leave_memory(af):
+    """The 3 x 3 blocks beside a prepared matrix's layout are left out when they would take more than an eighth of the
+    free device memory (0.5 GB of 3); products and a solve are the same bit for bit."""
+    import torch
+
+    A = synth.elast27(64, 1.0, 2)
+    dA = _dev(af, A)
+    X = _vec(synth.uniform(19, 5, A.n * 8, -1.0, 1.0)).reshape(A.n, 8)
+    b = X[:, 0].contiguous()
+
+    def run(keep):
+        af.release_cache()
+        torch.cuda.empty_cache()
+        fill = None
+        if keep:
+            fill = torch.empty(torch.cuda.mem_get_info()[0] - keep, dtype=torch.uint8, device="cuda")
+        before = torch.cuda.mem_get_info()[0]
+        M = af.PreparedMatrix(dA)
+        af.release_cache()
+        used = before - torch.cuda.mem_get_info()[0]
+        del fill
+        torch.cuda.empty_cache()
+        out = M.spmm(X), M.pcg_solve(None, b, maxit=20)[0]
+        M.close()
+        return used, out
+
+    much, a = run(0)
+    little, c = run(3 << 30)
+    blocks = A.nnz // 9 * (9 * 8 + 4)
+    assert 0.95 * blocks < much - little < 1.1 * blocks, (much, little, blocks)
+    for u, v in zip(a, c):
+        assert torch.equal(u, v)
