@@ -1357,3 +1357,30 @@ def test_prepared_blocks_leave_memory(af):
     assert 0.95 * blocks < much - little < 1.1 * blocks, (much, little, blocks)
     for u, v in zip(a, c):
         assert torch.equal(u, v)
+
+
+@pytest.mark.parametrize("form", [1, 2])
+def test_pcg_matrix_loads_few_slices(af, form):
+    """Few slices of long rows, larger than the caches (70,000 rows of 351 entries, 295 MB): x is the same bit for
+    bit for every number of entries in flight."""
+    import scipy.sparse as sp
+
+    n, half = 70000, 175
+    off = np.arange(-half, half + 1)
+    m = sp.diags([-(1.0 + (abs(o) % 7)) / 8 for o in off], off, shape=(n, n), format="csr")
+    m.setdiag(1.0 + np.asarray(abs(m).sum(axis=1)).ravel())
+    A = synth.CSR.from_scipy(m)
+    dA = _dev(af, A)
+    P = af.setup(dA, 2, 1, 1e-2)
+    b = _vec(synth.uniform(5, 1, A.n, -1.0, 1.0))
+    out = []
+    try:
+        af.set_option(af.OPT_PCG_FORM, form)
+        for un in (0, 2, 8):
+            af.set_option(af.OPT_SPMV_UNROLL, un)
+            x, i = af.pcg_solve(dA, P, b, rtol=1e-8, maxit=40)
+            out.append((i.iters, i.relres, x.cpu().numpy().tobytes()))
+    finally:
+        af.set_option(af.OPT_SPMV_UNROLL, 0)
+        af.set_option(af.OPT_PCG_FORM, 0)
+    assert out[0][0] > 5 and out[0] == out[1] == out[2]
