@@ -56,7 +56,7 @@ struct Layout {
     // and product vectors
     static_assert(ALV * 8 <= VALB, "the step's vectors fit in the gradient planes");
     static_assert(CAPT % 4 == 0 && CAPT <= 256, "buckets of four keys, slots in a byte");
-    // (8 doubles after W: the unrolled products read up to 7 entries past a row's diagonal)
+    // (the first of the 8 doubles after W is the matrix products' zero)
     // rows of W kept for patterns of at most mm positions grown s at a time: all but the last block
     // of the last step
     static __host__ __device__ constexpr int w_rows(int mm, int s) { return mm > 1 ? mm - 1 - ((s - 1) % NB + 1) : 0; }

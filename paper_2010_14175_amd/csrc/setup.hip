@@ -287,7 +287,6 @@ template <typename VT>
 __device__ __forceinline__ void sort_row(int lane, int a, int len, int32_t *__restrict__ ci, VT *__restrict__ val,
                                          const TPair<VT> *__restrict__ pr) {
     const int b = a + len;
-    (void)b;
     if (len <= 64) {
         int key = 0x7fffffff;
         VT v = VT(0);

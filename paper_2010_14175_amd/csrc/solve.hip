@@ -149,6 +149,29 @@ __device__ __forceinline__ void store_partials(double *partials, int slots, cons
         for (int k = 0; k < slots; ++k) partials[(size_t)k * gridDim.x + gb] = mine[k];
 }
 
+// block_sum and store of one dot, or of two at once
+template <bool TWO>
+__device__ __forceinline__ void store_dots(double va, double vb, double *sh /* 2 * kThreads / 64 */, double *pa, double *pb,
+                                           int gb) {
+    va = wave_sum(va);
+    if (TWO) vb = wave_sum(vb);
+    const int w = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+        sh[w] = va;
+        if (TWO) sh[kThreads / 64 + w] = vb;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double ta = 0.0, tb = 0.0;
+        for (int k = 0; k < kThreads / 64; ++k) {
+            ta += sh[k];
+            if (TWO) tb += sh[kThreads / 64 + k];
+        }
+        pa[gb] = ta;
+        if (TWO) pb[gb] = tb;
+    }
+}
+
 // The partial sums that a launch of nblocks blocks stored (nblocks = 0: sums, one per system)
 struct Parts {
     const double *p = nullptr;
@@ -226,13 +249,19 @@ __device__ __forceinline__ void parts_sum(const Parts &a, const Parts &b, int k,
 }
 
 // The same, where few kernels or many blocks need a sum: one block per system stores the
-// system's sums of one or two launches
+// system's sums of one or two launches.  Two arrays of 547 partials (139,968 rows) are loaded at once before they are added
+// (65.3 -> 64.0 us an iteration), of 4,096 too (5.1 -> 4.6 us a sum); between them the plain loop is as fast and shorter
+// (2,391: 4.5, 4.1 us).
 __global__ __launch_bounds__(kThreads) void k_reduce(Parts a, Parts b, double *oa, double *ob, const PcgScalars *scs) {
     const int k = blockIdx.x;
     const int done = scs[k].done;  // (loaded beside the partials)
     __shared__ double sh[2 * kThreads / 64];
     double sa, sb;
-    parts_sum<16>(a, b, k, sh, sa, sb);
+    const int na = a.mp.blk_sys ? a.mp.sys_nb[k] : a.nblocks, nb = b.mp.blk_sys ? b.mp.sys_nb[k] : b.nblocks;
+    const int most = max(na, nb);
+    if (most <= 4 * kThreads) parts_sum<4>(a, b, k, sh, sa, sb);
+    else if (most <= 12 * kThreads) parts_sum<1>(a, b, k, sh, sa, sb);
+    else parts_sum<16>(a, b, k, sh, sa, sb);
     if (threadIdx.x == 0 && !done) {
         oa[k] = sa;
         if (b.p) ob[k] = sb;
@@ -468,13 +497,13 @@ __device__ __forceinline__ double lane_chain(const int32_t *__restrict__ col, co
 }
 
 // SELL-64 product: one wavefront per slice of 64 rows, one lane per row; entry k of the 64
-// rows is one contiguous wave load.  Optional fused dot y.w.  For the tail of a split layout
+// rows is one contiguous wave load.  Optional fused dots (DOT 1: y.w; 2: w.w too).  For the tail of a split layout
 // (perm/rowmap set) the launch is not tied to systems (mp, sy empty, scs may be null).  With
 // rows ordered by length (lens set, instance ORD) a block takes whole windows of kWin slices,
 // its wavefronts taking the slices in turn, and the sums reach their natural rows through LDS,
 // so that y is written and the dot summed in row order.  The ordered instance keeps twice as many entries in flight
 // (its gathers are scattered over the window's rows and wait longest).
-template <int U, typename VT, bool DOT, bool NT, bool ORD = false>
+template <int U, typename VT, int DOT, bool NT, bool ORD = false>
 __global__ __launch_bounds__(kThreads) void k_sell_spmv(int n, int nslices, const uint32_t *__restrict__ sptr,
                                                          const int32_t *__restrict__ srow0,
                                                          const int32_t *__restrict__ perm,
@@ -492,10 +521,11 @@ __global__ __launch_bounds__(kThreads) void k_sell_spmv(int n, int nslices, cons
                                                          const int32_t *__restrict__ tcol,
                                                          const VT *__restrict__ tval,
                                                          const int32_t *__restrict__ toff,
-                                                         const double *__restrict__ rr) {
+                                                         const double *__restrict__ rr,
+                                                         double *__restrict__ partials_ww) {
     const Job jb = block_job(mp, nxcd);
     if (scs && scs[jb.k].done) return;
-    __shared__ double sh[kThreads / 64];
+    __shared__ double sh[2 * kThreads / 64];
     // converged by this iteration's r.r (one sum per system): the product is not needed
     if (rr && sqrt(rr[jb.k]) <= scs[jb.k].tol) return;
     const int sb = sy.slice0 ? sy.slice0[jb.k] : 0;
@@ -503,7 +533,7 @@ __global__ __launch_bounds__(kThreads) void k_sell_spmv(int n, int nslices, cons
     static_assert(kWin == kThreads / 64, "a window holds one slice per wavefront of a block");
     // (the ordered instance keeps the thread-derived index: measured faster there)
     const int wv = ORD ? (int)(threadIdx.x >> 6) : wave_index(), lane = threadIdx.x & 63;
-    double part = 0.0;
+    double part = 0.0, part_ww = 0.0;
     if constexpr (ORD) {
         static_assert(kWin * kSlice % kThreads == 0, "the wavefronts of a block take a window's slices in turn");
         constexpr int UO = U >= 8 ? 16 : U;
@@ -534,13 +564,13 @@ __global__ __launch_bounds__(kThreads) void k_sell_spmv(int n, int nslices, cons
                     const double an = sy_win[rn - wr0];
                     y[rn] = an;
                     if (DOT) part = fma(an, w[rn], part);
+                    if (DOT == 2) part_ww = fma(w[rn], w[rn], part_ww);
                 }
             }
             __syncthreads();
         }
         if (DOT) {
-            const double bs = block_sum(part, sh);
-            store_partials(partials, 1, &bs, jb.gb);
+            store_dots<DOT == 2>(part, part_ww, sh, partials, partials_ww, jb.gb);
         }
         return;
     }
@@ -580,11 +610,11 @@ __global__ __launch_bounds__(kThreads) void k_sell_spmv(int n, int nslices, cons
         if (valid) {
             y[ro] = acc;
             if (DOT) part = fma(acc, w[ro], part);
+            if (DOT == 2) part_ww = fma(w[ro], w[ro], part_ww);
         }
     }
     if (DOT) {
-        const double bs = block_sum(part, sh);
-        store_partials(partials, 1, &bs, jb.gb);
+        store_dots<DOT == 2>(part, part_ww, sh, partials, partials_ww, jb.gb);
     }
 }
 
@@ -833,7 +863,8 @@ __global__ __launch_bounds__(kThreads) void k_init_residual(int n, const double 
     store_partials(partials, 2, mine, jb.gb);
 }
 
-// x += alpha p ; r -= alpha q ; partials of ||r||^2  (M = I; pq: the partials of p.q)
+// x += alpha p ; r -= alpha q  (pq: the partials of p.q) ; SUM (M = I): partials of ||r||^2
+template <bool SUM>
 __global__ __launch_bounds__(kThreads) void k_update_xr(int n, double *__restrict__ x,
                                                          double *__restrict__ r,
                                                          const double *__restrict__ p,
@@ -856,13 +887,16 @@ __global__ __launch_bounds__(kThreads) void k_update_xr(int n, double *__restric
         r[i] = ri;
         pr = fma(ri, ri, pr);
     }
-    const double bs = block_sum(pr, sh);
-    store_partials(partials, 1, &bs, jb.gb);
+    if (SUM) {
+        const double bs = block_sum(pr, sh);
+        store_partials(partials, 1, &bs, jb.gb);
+    }
 }
 
-// The same with a preconditioner: r.r summed over the windows of a SELL product, block by block and row by row as
+// With a preconditioner r.r is summed over the windows of a SELL product, block by block and row by row as
 // k_sell_fused sums it, so that the forms, and a system alone and in a batch of another form, stop at the same iteration
-// with the same ||r|| bit for bit.  (With M = I r.r is rho and keeps its order; only one form has it.)
+// with the same ||r|| bit for bit (with M = I it is rho and keeps its order; only one form has it): by G^T's product, or
+// here where the products wait for it.  (Here for every size: four times as many blocks, 612,000 rows of 7 10.01 -> 10.29 ms.)
 __global__ __launch_bounds__(kThreads) void k_update_xr_win(int n, double *__restrict__ x, double *__restrict__ r,
                                                              const double *__restrict__ p, const double *__restrict__ q,
                                                              double *__restrict__ partials, const PcgScalars *scs,
@@ -1237,7 +1271,7 @@ static int make_batch_maps(int n, int nsys, const int32_t *row0, const DeviceInf
 template <int U, bool NT, typename VT>
 static void launch_sell_t(const Sell &S, const double *x, double *y, const double *w, double *partials,
                           PcgScalars *scs, const Map &mp, const Systems &sy, int nb, int nxcd, hipStream_t s,
-                          bool fused, const double *rr) {
+                          bool fused, const double *rr, double *ww) {
     const Sell *T = fused ? S.tail : nullptr;
     const uint32_t *tsp = T ? T->sptr : nullptr;
     const int32_t *tcl = T ? T->col : nullptr;
@@ -1257,14 +1291,16 @@ static void launch_sell_t(const Sell &S, const double *x, double *y, const doubl
     auto go = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3(nb), dim3(kThreads), 0, s, S.n, S.nslices, S.sptr, S.srow0, S.perm, S.rowmap, S.init,
                            S.col, (const VT *)S.val, x, y, w, partials, scs, mp, sy, nxcd, S.lens, S.wsl, S.wofs, tsp, tcl,
-                           tvl, tof, rr);
+                           tvl, tof, rr, ww);
     };
     if (S.lens) {
-        if (w) go(k_sell_spmv<U, VT, true, NT, true>);
-        else go(k_sell_spmv<U, VT, false, NT, true>);
+        if (ww) go(k_sell_spmv<U, VT, 2, NT, true>);
+        else if (w) go(k_sell_spmv<U, VT, 1, NT, true>);
+        else go(k_sell_spmv<U, VT, 0, NT, true>);
     } else {
-        if (w) go(k_sell_spmv<U, VT, true, NT>);
-        else go(k_sell_spmv<U, VT, false, NT>);
+        if (ww) go(k_sell_spmv<U, VT, 2, NT>);
+        else if (w) go(k_sell_spmv<U, VT, 1, NT>);
+        else go(k_sell_spmv<U, VT, 0, NT>);
     }
 }
 
@@ -1274,21 +1310,21 @@ static void launch_sell_t(const Sell &S, const double *x, double *y, const doubl
 template <typename VT>
 static void launch_sell_v(const Sell &S, int un, bool nt, const double *x, double *y, const double *w, double *partials,
                           PcgScalars *scs, const Map &mp, const Systems &sy, int nb, int nxcd, hipStream_t s,
-                          bool fused = false, const double *rr = nullptr) {
+                          bool fused = false, const double *rr = nullptr, double *ww = nullptr) {
     switch (un) {
-        case 1: launch_sell_t<1, true, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr); break;
-        case 2: launch_sell_t<2, true, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr); break;
+        case 1: launch_sell_t<1, true, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr, ww); break;
+        case 2: launch_sell_t<2, true, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr, ww); break;
         case 4:
-            if (nt) launch_sell_t<4, true, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr);
-            else launch_sell_t<4, false, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr);
+            if (nt) launch_sell_t<4, true, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr, ww);
+            else launch_sell_t<4, false, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr, ww);
             break;
         case 16:
-            if (nt) launch_sell_t<16, true, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr);
-            else launch_sell_t<16, false, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr);
+            if (nt) launch_sell_t<16, true, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr, ww);
+            else launch_sell_t<16, false, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr, ww);
             break;
         default:
-            if (nt) launch_sell_t<8, true, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr);
-            else launch_sell_t<8, false, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr);
+            if (nt) launch_sell_t<8, true, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr, ww);
+            else launch_sell_t<8, false, VT>(S, x, y, w, partials, scs, mp, sy, nb, nxcd, s, fused, rr, ww);
             break;
     }
 }
@@ -1314,11 +1350,11 @@ static int sell_unroll(const Sell &S, const DeviceInfo &di) {
 constexpr int64_t kCachedBytes = (int64_t)256 << 20;
 static int64_t stream_bytes(const Sell &S) { return S.entries * (4 + (S.f32 ? 4 : 8)); }
 
-// y = S x for a SELL-64 matrix laid out for the batch (optionally fused dot y.w: one partial sum
+// y = S x for a SELL-64 matrix laid out for the batch (optionally fused dot y.w, and w.w with ww: one partial sum
 // per block, finalised into the systems' scalars when fin says so); a split layout's tail is multiplied first
 static void sell_spmv(const char *name, const Sell &S, const BatchMaps &bm, const double *x, double *y,
                       const double *w, double *partials, PcgScalars *scs, int fin, const DeviceInfo &di,
-                      hipStream_t s, const double *rr = nullptr) {
+                      hipStream_t s, const double *rr = nullptr, double *ww = nullptr) {
     const int un = sell_unroll(S, di);
     // a split layout's tail runs in a launch of its own first; inside the slices' product when
     // asked for (measured slower: the lanes of long rows serialise their tails while the rest of
@@ -1340,9 +1376,9 @@ static void sell_spmv(const char *name, const Sell &S, const BatchMaps &bm, cons
     {
         ProfScope ps(name, s);
         if (S.f32)
-            launch_sell_v<float>(S, un, bm.nt, x, y, w, partials, scs, bm.sell.mp, bm.sy, nb, di.num_xcds, s, fused, rr);
+            launch_sell_v<float>(S, un, bm.nt, x, y, w, partials, scs, bm.sell.mp, bm.sy, nb, di.num_xcds, s, fused, rr, ww);
         else
-            launch_sell_v<double>(S, un, bm.nt, x, y, w, partials, scs, bm.sell.mp, bm.sy, nb, di.num_xcds, s, fused, rr);
+            launch_sell_v<double>(S, un, bm.nt, x, y, w, partials, scs, bm.sell.mp, bm.sy, nb, di.num_xcds, s, fused, rr, ww);
     }
     if (w && fin != FIN_NONE)
         hipLaunchKernelGGL(k_finalize, dim3(bm.nsys), dim3(kThreads), 0, s, Parts{partials, bm.sell.mp, nb}, Parts(), fin,
@@ -2461,26 +2497,29 @@ class PcgRun {
         spmv_A("spmv_A_dot", p_, q_, p_, s_in);
         const Parts pq = use_sell_ ? sell_parts(partials_) : Parts{partials_, Map(), spmv_blocks(csr_of(&A_), di_)};
         hipLaunchKernelGGL(k_reduce, gs, dim3(kThreads), 0, s_, pq, Parts(), red_, (double *)nullptr, s_in);
+        // the iteration that converges needs no z: with a large G (the two products cost more than a
+        // launch per iteration) r.r is summed before them and they return; else by G^T's product, which has r for r.z
+        const bool gate = P_ && P_->sg.entries >= kGateEntries;
         {
             ProfScope ps("update_xr", s_);
-            if (P_)
+            if (gate)
                 hipLaunchKernelGGL(k_update_xr_win, dim3(bm_.sell.nblocks), dim3(kThreads), 0, s_, n, x_, r_, p_, q_, pa_rr_,
                                    s_in, bad_, red_parts(0), bm_.sell.mp, bm_.sy, di_.num_xcds);
+            else if (P_)
+                hipLaunchKernelGGL(k_update_xr<false>, gv, dim3(kThreads), 0, s_, n, x_, r_, p_, q_, (double *)nullptr, s_in,
+                                   bad_, red_parts(0), bm_.vec.mp, bm_.sy, di_.num_xcds);
             else
-                hipLaunchKernelGGL(k_update_xr, gv, dim3(kThreads), 0, s_, n, x_, r_, p_, q_, pa_rr_, s_in, bad_,
+                hipLaunchKernelGGL(k_update_xr<true>, gv, dim3(kThreads), 0, s_, n, x_, r_, p_, q_, pa_rr_, s_in, bad_,
                                    red_parts(0), bm_.vec.mp, bm_.sy, di_.num_xcds);
         }
         marks_.push_back(prof_mark());
-        // the iteration that converges needs no z: with a large G (the two products cost more than a
-        // launch per iteration) r.r is summed before them and they return; else with r.z
-        const bool gate = P_ && P_->sg.entries >= kGateEntries;
         if (gate)
             hipLaunchKernelGGL(k_reduce, gs, dim3(kThreads), 0, s_, rr_parts(), Parts(), red_ + nsys_,
                                (double *)nullptr, s_in);
         if (P_) {
             const double *rr = gate ? red_ + nsys_ : nullptr;
             sell_spmv("spmv_G", P_->sg, bm_, r_, t_, nullptr, nullptr, s_in, FIN_NONE, di_, s_, rr);
-            sell_spmv("spmv_GT_dot", P_->sgt, bm_, t_, z_, r_, pa_rz_, s_in, FIN_NONE, di_, s_, rr);
+            sell_spmv("spmv_GT_dot", P_->sgt, bm_, t_, z_, r_, pa_rz_, s_in, FIN_NONE, di_, s_, rr, gate ? nullptr : pa_rr_);
         }
         if (gate)
             hipLaunchKernelGGL(k_reduce, gs, dim3(kThreads), 0, s_, rz_parts(), Parts(), red_ + 2 * (size_t)nsys_,
