@@ -21,7 +21,7 @@
 // Results are those of k_rows_w bit for bit: every gradient receives its terms in the same
 // order (member rows in turn, the second half of the wavefront after the first, the columns of
 // one member row distinct), the selection takes the same maximum and the same smallest
-// column in the band, and extend_w is shared.
+// column in the band, and extend_w is shared, over the same blocks of new rows.
 #pragma once
 
 #include "rows_w.hpp"

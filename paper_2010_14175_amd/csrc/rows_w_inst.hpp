@@ -31,9 +31,9 @@ static RowsKernel w_cap(int cap, int mm, size_t *lds) {
 }
 
 // 64 lanes per row with the large tables of a second launch (rows that overflowed the first)
-template <bool G32, int MMAX>
+template <bool G32, int MMAX, int NB>
 static RowsKernel w_cap_large(int cap, int mm, size_t *lds) {
-    constexpr int GS = 64, NB = 4;
+    constexpr int GS = 64;
     switch (cap) {
         AFSAI_W_CASE(128)
         AFSAI_W_CASE(256)
@@ -47,6 +47,10 @@ static RowsKernel w_cap_large(int cap, int mm, size_t *lds) {
 }
 #undef AFSAI_W_CASE
 
+inline bool eight_lanes(int mmax, int maxlen, int cap, int lanes) {
+    return lanes <= 8 && mmax <= 8 && maxlen <= 8 * wform::spw_of(8) && cap <= 128;
+}
+
 // Kernel for patterns of at most mmax positions over rows of at most maxlen entries with a
 // first table of `cap` slots: the fewest lanes per row that hold a position per lane and the
 // row entries left of column i in their slot lists.  Returns nullptr when none fits (rows
@@ -59,7 +63,7 @@ RowsKernel rows_kernel_w_t(int mmax, int maxlen, int cap, int lanes, int *gs_out
     int gs = 0;
     // groups of 8 and 16 lanes only with small tables (a selection pass visits CAP / GS slots
     // per lane); `lanes` asks for at least that many lanes per row
-    if (lanes <= 8 && mmax <= 8 && maxlen <= 8 * wform::spw_of(8) && cap <= 128) {
+    if (eight_lanes(mmax, maxlen, cap, lanes)) {
         gs = 8;
         k = w_cap<G32, 8, 8, 1>(cap, mmax, lds_out);
     } else if (lanes <= 16 && mmax <= 16 && maxlen <= 16 * wform::spw_of(16) && cap <= 256) {
@@ -80,11 +84,14 @@ RowsKernel rows_kernel_w_t(int mmax, int maxlen, int cap, int lanes, int *gs_out
 }
 
 // The same form with 64 lanes per row and a table of `cap` slots (128..8192), for the rows
-// that overflowed the first launch's table.
+// that overflowed the first launch's table.  nb: the first launch's rows per block (rows_w_block), so that a row's G
+// does not depend on the table it was done with.
 template <bool G32>
-RowsKernel rows_kernel_w_large_t(int mmax, int cap, size_t *lds_out) {
+RowsKernel rows_kernel_w_large_t(int mmax, int cap, int nb, size_t *lds_out) {
     if (mmax > 64) return nullptr;
-    return mmax <= 48 ? w_cap_large<G32, 48>(cap, mmax, lds_out) : w_cap_large<G32, 64>(cap, mmax, lds_out);
+    if (nb == 1) return w_cap_large<G32, 24, 1>(cap, mmax, lds_out);
+    if (nb == 2) return w_cap_large<G32, 24, 2>(cap, mmax, lds_out);
+    return mmax <= 48 ? w_cap_large<G32, 48, 4>(cap, mmax, lds_out) : w_cap_large<G32, 64, 4>(cap, mmax, lds_out);
 }
 
 }  // namespace winst

@@ -452,9 +452,10 @@ __global__ void k_block_check(int n, const int32_t *__restrict__ rp, const int32
 // form) and rows_b.hip (inverse-factor form over runs of three columns)
 RowsKernel rows_kernel(int mmax_t, int cap, bool rsl, bool f32);
 RowsKernel rows_kernel_w(int mmax, int maxlen, int cap, int lanes, bool g32, int *gs_out, size_t *lds_out);
-RowsKernel rows_kernel_w_large(int mmax, int cap, bool g32, size_t *lds_out);
-RowsKernel rows_kernel_b(int n, int mmax, int s, int maxlen, int *gs_out, size_t *lds_out);
-RowsKernel rows_kernel_b_large(int mmax, int s, int *gs_out, size_t *lds_out);
+RowsKernel rows_kernel_w_large(int mmax, int cap, int nb, bool g32, size_t *lds_out);
+int rows_w_block(int mmax, int maxlen, int cap, int lanes);
+RowsKernel rows_kernel_b(int n, int mmax, int s, int maxlen, int nb, int *gs_out, size_t *lds_out);
+RowsKernel rows_kernel_b_large(int mmax, int s, int nb, int *gs_out, size_t *lds_out);
 
 // Launch of a per-row kernel over `nlist` rows.  Inverse-factor form: wdyn > 0 is its dynamic
 // LDS per block and rpw its rows per wavefront; the Cholesky form sizes its LDS from the
@@ -719,6 +720,7 @@ static int setup_core(const afsai_csr *A, const afsai_params *p, int nsys, const
     const int64_t form = option(AFSAI_OPT_SETUP_FORM);
     RowsKernel k1 = nullptr;
     bool run_form = false;
+    int wnb = 4;  // new rows per block of the inverse-factor form
     size_t wdyn = 0;
     int wrpw = 1;
     if (form != 1 && !sf32 && rsl) {
@@ -730,7 +732,8 @@ static int setup_core(const afsai_csr *A, const afsai_params *p, int nsys, const
         // groups of 32 and 64 lanes take tables from 128 slots
         if (wcap < 128 && (lanes >= 32 || mmax > 16 || maxlen > 64)) wcap = 128;
         int gs = 64;
-        if (runs && !so.noruns) k1 = rows_kernel_b(n, mmax, p->s, maxlen, &gs, &wdyn);
+        wnb = rows_w_block(mmax, maxlen, wcap, lanes);
+        if (runs && !so.noruns) k1 = rows_kernel_b(n, mmax, p->s, maxlen, wnb, &gs, &wdyn);
         run_form = k1 != nullptr;
         if (!k1) k1 = rows_kernel_w(mmax, maxlen, wcap, lanes, (p->flags & AFSAI_GRAD_F32) != 0, &gs, &wdyn);
         if (k1) {
@@ -799,13 +802,13 @@ static int setup_core(const afsai_csr *A, const afsai_params *p, int nsys, const
     if (sm.novf > 0 && run_form) {
         int gs = 64;
         size_t dyn = 0;
-        if (RowsKernel k = rows_kernel_b_large(mmax, p->s, &gs, &dyn))
+        if (RowsKernel k = rows_kernel_b_large(mmax, p->s, wnb, &gs, &dyn))
             if ((rc = redo("afsai_rows_retry_runs", k, dyn, 64 / gs, cap1))) return rc;
     }
     // the same form as the first launch, with a table for the worst case
     if (sm.novf > 0 && cap2 > cap1) {
         size_t dyn = 0;
-        RowsKernel k = wdyn ? rows_kernel_w_large(mmax, cap2, (p->flags & AFSAI_GRAD_F32) != 0, &dyn) : rows_kernel(mmax_t, cap2, rsl, sf32);
+        RowsKernel k = wdyn ? rows_kernel_w_large(mmax, cap2, wnb, (p->flags & AFSAI_GRAD_F32) != 0, &dyn) : rows_kernel(mmax_t, cap2, rsl, sf32);
         if (!k) AFSAI_FAIL(AFSAI_ERR_TOO_LARGE, "afsai_setup: no kernel for table %d", cap2);
         if ((rc = redo("afsai_rows_retry", k, dyn, 1, cap2))) return rc;
     }

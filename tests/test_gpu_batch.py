@@ -272,3 +272,27 @@ def test_batched_form_other_than_alone(af, make, kmax, alone):
     after = af.pcg_form_counts()
     batched = "fused" if alone == "separate" else "separate"
     assert (mid[batched] - before[batched], after[alone] - mid[alone]) == (1, 2)
+
+
+@pytest.mark.parametrize("kmax,s", [(3, 2), (7, 3), (5, 4)])
+@pytest.mark.parametrize("grid", ["line", "7-point"])
+def test_batched_setup_runs_alone(af, kmax, s, grid):
+    """A system of 3 x 3 blocks alone takes the setup's run form, in a batch with one that is not made of them the
+    general form, with other tables: its G is the same bit for bit, also where several positions are added a step and
+    rows overflow a table (7-point rows of 21 entries), and for the shortest rows (9 entries)."""
+    import scipy.sparse as sp
+
+    g = synth.lap7_lognormal(*((300, 1, 1) if grid == "line" else (9, 8, 7)), 1.0, 3).to_scipy()
+    B = np.array([[4.0, 1.25, -0.75], [1.25, 3.5, 0.5], [-0.75, 0.5, 5.0]])
+    A1 = sp.csr_matrix(sp.kron(g, B))
+    A2 = synth.lap7_lognormal(9, 9, 9, 1.0, 4).to_scipy()
+    off = [0, A1.shape[0], A1.shape[0] + A2.shape[0]]
+    one = af.setup(af.DeviceCSR.from_host(synth.CSR.from_scipy(A1)), kmax, s, 1e-9)
+    both = af.setup_batched(af.DeviceCSR.from_host(synth.CSR.from_scipy(sp.csr_matrix(sp.block_diag([A1, A2])))), off, kmax, s,
+                            1e-9)
+    rp, ci, va = _factor(both)
+    r1, c1, v1 = _factor(one)
+    end = rp[off[1]]
+    np.testing.assert_array_equal(rp[:off[1] + 1], r1)
+    np.testing.assert_array_equal(ci[:end], c1)
+    np.testing.assert_array_equal(va[:end].view(np.int64), v1.view(np.int64))
