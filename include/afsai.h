@@ -413,8 +413,9 @@ const char *afsai_last_error(void);
  *                             system, and a small system's whole solve in one launch where
  *                             that is faster; separate update kernels above); 1: separate
  *                             update kernels; 2: fused products (used only when no SELL
- *                             matrix of the solve is split, see AFSAI_OPT_SELL_WIDTH); all
- *                             forms give identical results
+ *                             matrix of the solve is split or ordered by length, see
+ *                             AFSAI_OPT_SELL_WIDTH); all forms give identical results, residuals
+ *                             and iterations included
  *   AFSAI_OPT_SELL_WIDTH      entries per row held by the 64-row slices of every SELL layout
  *                             built afterwards; longer rows keep their leading entries in a
  *                             second, length-sorted layout multiplied first (0: split only
@@ -452,8 +453,10 @@ const char *afsai_last_error(void);
  *                             the pattern, else 64, 32 only when asked for; matrices whose rows
  *                             are made of aligned runs of three columns take a kernel over the
  *                             runs, 32 or 64 lanes, while this and AFSAI_OPT_SETUP_TABLE are 0).  A request smaller
- *                             than the pattern takes the next size that holds it.  Any choice
- *                             gives identical G
+ *                             than the pattern takes the next size that holds it.  With s = 1 any
+ *                             choice gives identical G; with more, the positions entered together
+ *                             (one with 8 lanes, two up to 24 positions and with 32 lanes, else
+ *                             four; the same in every launch of a setup) enter its rounding
  *   AFSAI_OPT_SETUP_CLAIM     wavefronts' worth of rows one atomic claim of the setup kernel takes
  *                             from its XCD's counter (1..64; 0 automatic: enough rows for about
  *                             4,000 table entries of work, at most 16).  Any choice gives
