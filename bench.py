@@ -137,7 +137,14 @@ def batch_bench(args):
     if kern_timed:
         dom, (launches, ms) = max(kern_timed.items(), key=lambda kv: kv[1][1])
         avg_s = ms / launches * 1e-3
-        byt = kernel_bytes(dom, A.n, A.nnz, int(g_rp[-1]), 8, 5, 6)
+        if dom.startswith(("spmv_", "update_")):
+            # a kernel of the iteration: a system that has stopped moves nothing, so its bytes count as often as
+            # it iterates, spread over the launches of the slowest one
+            byt = sum(kernel_bytes(dom, int(off[k + 1] - off[k]), int(a_rp[off[k + 1]] - a_rp[off[k]]),
+                                   int(g_rp[off[k + 1]] - g_rp[off[k]]), 8, 5, 6) * int(infos[k].iters)
+                      for k in range(nsys)) / max(1, int(its.max()))
+        else:
+            byt = kernel_bytes(dom, A.n, A.nnz, int(g_rp[-1]), 8, 5, 6)
         ach = byt / avg_s / 1e9
         roof = {"kernel": dom, "bound": "hbm", "achieved": round(ach, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                 "frac": round(ach / PEAK_HBM_GBS, 4), "traffic": measured_traffic(dom, args.workload),
