@@ -166,3 +166,13 @@ def test_binding_rejects_host_and_misshapen_blocks(L):
         af.spmv(A, torch.zeros(2, dtype=torch.float64))
     with pytest.raises(ValueError, match="CUDA"):
         af.pcg_solve(A, None, torch.zeros(2, dtype=torch.float64))
+
+
+def test_one_launch_option_and_counts_on_host(L):
+    for v in (-1, 5):
+        assert L.afsai_set_option(af.OPT_PCG_ONE_LAUNCH, v) == af.ERR_INVALID_ARG
+    for v in (1, 2, 3, 4, 0):
+        assert L.afsai_set_option(af.OPT_PCG_ONE_LAUNCH, v) == af.OK
+    assert L.afsai_set_option(17, 0) == af.ERR_INVALID_ARG
+    assert L.afsai_pcg_form_counts(None) == af.ERR_INVALID_ARG
+    assert set(af.pcg_form_counts()) == {"one_launch", "unmet", "fused", "separate"}
