@@ -186,7 +186,9 @@ int pcg_solve(const afsai_csr *A, afsai_precond P, const double *b, double *x, d
  *   set up independently (Sec. 2) and gradients never leave a block, the setup of the batch is
  *   one launch of the setup over the whole matrix; the candidate tie rule (smallest column) does
  *   not depend on where a system sits, so each system's G is the one a separate afsai_setup of
- *   that system gives, bit for bit.  The solver then runs all systems together, each with its
+ *   that system gives, bit for bit (where the batch's size and longest row leave it the form it
+ *   takes alone, see AFSAI_OPT_SETUP_FORM, and, for patterns of up to 8 positions grown several at a
+ *   time, the lanes).  The solver then runs all systems together, each with its
  *   own scalars and stopping test; a system's iterates and x are those of a separate pcg_solve
  *   of it, bit for bit (its dot products are summed over the same partition).
  *   offsets (host) nsys + 1 entries, offsets[0] = 0, strictly increasing, offsets[nsys] = n.
